@@ -360,6 +360,19 @@ uint64_t apply_chunks_per_bucket(uint64_t cap, uint64_t be) {
     return (slots + kApplyChunk - 1) / kApplyChunk;
 }
 
+// The scatter.  Up to kWalkGrid chunk slots every workgroup looks at its own slot, live or not; above that a fixed grid
+// walks the live chunks (the walk's bucket table holds kWalkBuckets buckets; longer lists of buckets keep the slots).
+template <bool MULTI, int EB>
+int launch_apply(const ApplyArgs &a, hipStream_t st) {
+    const uint64_t slots = (uint64_t)a.nb * a.chunks_per_bucket;
+    if (slots > kWalkGrid && a.nb <= kWalkBuckets)
+        hipLaunchKernelGGL((apply_walk_kernel<MULTI, EB>), dim3(kWalkGrid), dim3(kThreads), 0, st, a);
+    else
+        hipLaunchKernelGGL((apply_kernel<MULTI, EB>), dim3((uint32_t)slots), dim3(kThreads), 0, st, a);
+    SRS_HIP(hipGetLastError());
+    return SRS_OK;
+}
+
 // do the grids of the second-pass snapshot refresh fit a launch?  (checked before anything is launched)
 bool second_pass_fits(uint64_t nb, uint64_t cap, uint64_t be) {
     return nb * apply_chunks_per_bucket(cap, be) <= 0x7fffffffull && nb * kOverflowSplit <= 0x7fffffffull;
@@ -383,14 +396,11 @@ int launch_second_pass(const srs_ctx *ctx, const srs_plan *plan, const ExtractAr
     }
     s.be = (uint32_t)be; s.nb = a.nb; s.chunks_per_bucket = (uint32_t)cpb;
     s.I = a.I; s.V = a.V; s.counts = a.counts; s.cap = a.cap; s.flags = ctx->flags;
-    const dim3 grid((uint32_t)((uint64_t)a.nb * cpb)), ogrid(a.nb * kOverflowSplit), block(kThreads);
-    if (eb == 1) {
-        hipLaunchKernelGGL((apply_kernel<MULTI, 1>), grid, block, 0, st, s);
-        hipLaunchKernelGGL((refresh_overflow_kernel<MULTI, 1>), ogrid, block, 0, st, a, tile_elems);
-    } else {
-        hipLaunchKernelGGL((apply_kernel<MULTI, 2>), grid, block, 0, st, s);
-        hipLaunchKernelGGL((refresh_overflow_kernel<MULTI, 2>), ogrid, block, 0, st, a, tile_elems);
-    }
+    const dim3 ogrid(a.nb * kOverflowSplit), block(kThreads);
+    const int rc = (eb == 1) ? launch_apply<MULTI, 1>(s, st) : launch_apply<MULTI, 2>(s, st);
+    if (rc != SRS_OK) return rc;
+    if (eb == 1) hipLaunchKernelGGL((refresh_overflow_kernel<MULTI, 1>), ogrid, block, 0, st, a, tile_elems);
+    else hipLaunchKernelGGL((refresh_overflow_kernel<MULTI, 2>), ogrid, block, 0, st, a, tile_elems);
     SRS_HIP(hipGetLastError());
     return SRS_OK;
 }
@@ -603,10 +613,7 @@ static int apply_single(srs_ctx *ctx, void *weights, uint64_t n, uint64_t bucket
     a.w = (uint16_t *)weights; a.n = n; a.be = (uint32_t)bucket_elems; a.nb = (uint32_t)nb;
     a.chunks_per_bucket = (uint32_t)cpb;
     a.I = I; a.V = (const uint16_t *)V; a.counts = counts; a.cap = cap; a.flags = ctx->flags;
-    if (eb == 1) hipLaunchKernelGGL((apply_kernel<false, 1>), dim3((uint32_t)(nb * cpb)), dim3(kThreads), 0, st, a);
-    else hipLaunchKernelGGL((apply_kernel<false>), dim3((uint32_t)(nb * cpb)), dim3(kThreads), 0, st, a);
-    SRS_HIP(hipGetLastError());
-    return SRS_OK;
+    return (eb == 1) ? launch_apply<false, 1>(a, st) : launch_apply<false, 2>(a, st);
 }
 
 int srs_apply(srs_ctx *ctx, void *weights, uint64_t n, uint64_t bucket_elems,
@@ -780,11 +787,7 @@ static int apply_multi(srs_ctx *ctx, srs_plan *plan, const srs_tensor *t,
     a.segs = plan->d_segs; a.seg_begin = plan->d_seg_begin; a.wptrs = plan->d_wptrs; a.total = plan->total;
     a.be = (uint32_t)plan->be; a.nb = plan->nbuckets; a.chunks_per_bucket = (uint32_t)cpb;
     a.I = I; a.V = (const uint16_t *)V; a.counts = counts; a.cap = cap; a.flags = ctx->flags;
-    const dim3 grid((uint32_t)((uint64_t)plan->nbuckets * cpb));
-    if (eb == 1) hipLaunchKernelGGL((apply_kernel<true, 1>), grid, dim3(kThreads), 0, st, a);
-    else hipLaunchKernelGGL((apply_kernel<true>), grid, dim3(kThreads), 0, st, a);
-    SRS_HIP(hipGetLastError());
-    return SRS_OK;
+    return (eb == 1) ? launch_apply<true, 1>(a, st) : launch_apply<true, 2>(a, st);
 }
 
 int srs_apply_multi(srs_ctx *ctx, srs_plan *plan, const srs_tensor *t,
