@@ -71,11 +71,10 @@ typedef enum {
 #define SRS_OPT_SPIN_LIMIT 1   /* max polls of a predecessor tile before SRS_FLAG_TIMEOUT (default 1<<24) */
 #define SRS_OPT_TILE_ELEMS 2   /* elements per extract tile: 4096, 8192, 16384 or 32768 (default; tuning; affects
                                   plans created afterwards) */
-#define SRS_OPT_REFRESH_GROUP 3 /* snapshot refresh: 8 (default) = a full tile of 16-byte-aligned weights rewrites
-                                  every 128-byte run of the snapshot that holds a change (a whole line when the tensor
-                                  starts on a 128-byte boundary, which is where the gain comes from), from the
-                                  new weights (unchanged elements get the value they have), other tiles store element
-                                  by element; 0 = a store per changed element everywhere.  Same result; tuning.
+#define SRS_OPT_REFRESH_GROUP 3 /* snapshot refresh: 8 (default) = every aligned 128-byte line of the snapshot that
+                                  holds a change is rewritten from the new weights (unchanged elements get the value
+                                  they have; only elements of the tensor are stored); 0 = a store per changed
+                                  element everywhere.  Same result; tuning.
                                   Applies to the extract calls of every element width and to the fused cast. */
 #define SRS_OPT_INTERLEAVE 4   /* buckets whose tiles are interleaved over consecutive workgroups, 1..4096
                                   (default 64; tuning; affects plans created afterwards) */

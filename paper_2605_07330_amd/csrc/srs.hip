@@ -62,7 +62,7 @@ struct srs_ctx {
     uint32_t spin_limit = 1u << 24;
     uint32_t tile_elems = 32768;
     uint32_t group = 64;                    // buckets whose tiles are interleaved over consecutive workgroups
-    uint32_t refresh_group = 8;             // 8: snapshot refreshed by whole 128-byte lines (full, aligned tiles); 0: element by element
+    uint32_t refresh_group = 8;             // 8: snapshot refreshed by whole 128-byte lines; 0: element by element
     uint32_t snapshot_mode = 0;             // 0: refreshed inside the scan; 1: left alone, the caller swaps buffers;
                                             // 2: left alone by the scan, then refreshed from the payload (second pass)
 };

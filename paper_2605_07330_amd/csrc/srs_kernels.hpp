@@ -156,6 +156,16 @@ __device__ __forceinline__ u32x4 load16(gptr<const void> p) {
     if (NT) return __builtin_nontemporal_load(q);
     return *q;
 }
+// the same at any address: one global_load_dwordx4 all the same (unaligned access is on for every HSA process)
+typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(1)));
+template <bool NT>
+__device__ __forceinline__ u32x4 load16_any(gptr<const void> p) {
+    gptr<const u32x4_any> q = (gptr<const u32x4_any>)p;
+    u32x4_any v;
+    if (NT) v = __builtin_nontemporal_load(q);
+    else v = *q;
+    return (u32x4)v;
+}
 __device__ __forceinline__ void store16_nt(gptr<void> p, u32x4 v) { __builtin_nontemporal_store(v, (gptr<u32x4>)p); }
 
 // 8 patterns starting at element e of a run of len elements, as 4 dwords; elements at or beyond
@@ -183,6 +193,27 @@ __device__ __forceinline__ u32x4 round8_bf16(u32x4 f0, u32x4 f1) {
     r.y = round_bf16(f0.z) | (round_bf16(f0.w) << 16);
     r.z = round_bf16(f1.x) | (round_bf16(f1.y) << 16);
     r.w = round_bf16(f1.z) | (round_bf16(f1.w) << 16);
+    return r;
+}
+
+// The elements lo .. hi-1 (of the vector's 8) at p, which may lie before the first element that exists; the others
+// read as 0.
+__device__ __forceinline__ u32x4 load8_window(gptr<const uint16_t> p, uint32_t lo, uint32_t hi) {
+    uint32_t h[8];
+#pragma unroll
+    for (uint32_t k = 0; k < 8; ++k) h[k] = (k >= lo && k < hi) ? (uint32_t)p[k] : 0u;
+    u32x4 r;
+    r.x = h[0] | (h[1] << 16); r.y = h[2] | (h[3] << 16);
+    r.z = h[4] | (h[5] << 16); r.w = h[6] | (h[7] << 16);
+    return r;
+}
+__device__ __forceinline__ u32x4 load8_window_cast(gptr<const uint32_t> p, uint32_t lo, uint32_t hi) {
+    uint32_t h[8];
+#pragma unroll
+    for (uint32_t k = 0; k < 8; ++k) h[k] = (k >= lo && k < hi) ? round_bf16(p[k]) : 0u;
+    u32x4 r;
+    r.x = h[0] | (h[1] << 16); r.y = h[2] | (h[3] << 16);
+    r.z = h[4] | (h[5] << 16); r.w = h[6] | (h[7] << 16);
     return r;
 }
 
@@ -215,14 +246,14 @@ __device__ __forceinline__ uint32_t pattern_at(u32x4 v, uint32_t e) {
     return (e & 1u) ? (w >> 16) : (w & 0xFFFFu);
 }
 
-// 16 one-byte patterns starting at element e of a run of len elements; elements at or beyond len read as 0
-__device__ __forceinline__ u32x4 load16_guarded_u8(gptr<const uint8_t> p, uint32_t e, uint32_t len) {
+// 16 one-byte patterns: elements lo .. hi-1 at p, the others read as 0
+__device__ __forceinline__ u32x4 load16_window_u8(gptr<const uint8_t> p, uint32_t lo, uint32_t hi) {
     uint32_t d[4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
+    for (uint32_t q = 0; q < 4; ++q) {
         uint32_t w = 0;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) w |= ((e + 4 * q + k < len) ? (uint32_t)p[e + 4 * q + k] : 0u) << (8 * k);
+        for (uint32_t k = 0; k < 4; ++k) w |= ((4 * q + k >= lo && 4 * q + k < hi) ? (uint32_t)p[4 * q + k] : 0u) << (8 * k);
         d[q] = w;
     }
     u32x4 r;
@@ -244,8 +275,8 @@ template <> struct Elem<2> {
     typedef uint16_t type;
     static __device__ __forceinline__ uint32_t diff_mask(u32x4 a, u32x4 b) { return diff_mask8(a, b); }
     static __device__ __forceinline__ uint32_t pattern(u32x4 v, uint32_t e) { return pattern_at(v, e); }
-    static __device__ __forceinline__ u32x4 load_guarded(gptr<const uint16_t> p, uint32_t e, uint32_t len) {
-        return load8_guarded(p, e, len);
+    static __device__ __forceinline__ u32x4 load_window(gptr<const uint16_t> p, uint32_t lo, uint32_t hi) {
+        return load8_window(p, lo, hi);
     }
 };
 template <> struct Elem<1> {
@@ -260,8 +291,8 @@ template <> struct Elem<1> {
         const uint32_t w = (e & 8u) ? hi : lo;
         return (w >> ((e & 3u) * 8u)) & 0xFFu;
     }
-    static __device__ __forceinline__ u32x4 load_guarded(gptr<const uint8_t> p, uint32_t e, uint32_t len) {
-        return load16_guarded_u8(p, e, len);
+    static __device__ __forceinline__ u32x4 load_window(gptr<const uint8_t> p, uint32_t lo, uint32_t hi) {
+        return load16_window_u8(p, lo, hi);
     }
 };
 
@@ -329,7 +360,7 @@ __device__ __forceinline__ uint32_t look_back(const ExtractArgs &a, uint32_t til
 // ---------------------------------------------------------------------------------------------
 // extract
 // ---------------------------------------------------------------------------------------------
-// RG = how the snapshot is refreshed.  8: by whole lines -- a full tile of 16-byte-aligned weights rewrites every
+// RG = how the snapshot is refreshed.  8: by whole lines -- the tile rewrites every
 // aligned 128-byte line of the snapshot that holds a change (8 lanes x 16 bytes of one store instruction) from the
 // new weights it has in registers; unchanged elements get the value they already hold.  The snapshot's loads and
 // these stores carry the non-temporal hint: a line written in full needs no read-modify-write behind the L2, and
@@ -337,8 +368,7 @@ __device__ __forceinline__ uint32_t look_back(const ExtractArgs &a, uint32_t til
 // in one process, ms: 21.8 / 22.4 at 0.1 % changed, 25.8 / 28.7 at 1 %, 30.1 / 36.2 at 3 %, 33.6 / 40.4 at 10 %.
 // The two hints only pay together (at 1 %: stores alone 27.6, loads alone 28.3; 64-byte blocks 28.8, 256-byte
 // blocks 30.5).  The new weights are hinted as well (read once; worth 1 % on one-byte and on sparse data, nothing
-// at 1 %), except the FP32 master weights of CAST, where the hint costs 1 ms of 38.  Tiles that are ragged or not
-// 16-byte aligned refresh element by element with ordinary loads.
+// at 1 %), except the FP32 master weights of CAST, where the hint costs 1 ms of 38.
 // 0: element by element everywhere (2-byte stores from the write-out loop).  -1: the snapshot is not touched at all
 // (the caller rotates buffers: `new` is the next call's `old`).
 // CAST: `new` is not a BF16 buffer but the FP32 master weights; each element is rounded to BF16
@@ -349,7 +379,7 @@ __device__ __forceinline__ uint32_t look_back(const ExtractArgs &a, uint32_t til
 constexpr int kSrcBf16 = 0, kSrcFp32 = 1, kSrcBitmap = 2;
 
 template <int V, bool MULTI, int RG, int SRC = kSrcBf16, int EB = 2>
-__global__ __launch_bounds__(kThreads) void extract_kernel(const ExtractArgs a) {
+__global__ __launch_bounds__(kThreads, (V >= 16 && SRC == kSrcBf16) ? 3 : 1) void extract_kernel(const ExtractArgs a) {
     // A snapshot that is not written is read exactly once, like the new weights: both streams then carry the
     // non-temporal hint (measured 4 % faster).  With element-wise refresh the hint on either stream measures slower,
     // on the snapshot by 5 ms: 2-byte refresh stores must find their line still cached, hinted or not.
@@ -370,6 +400,8 @@ __global__ __launch_bounds__(kThreads) void extract_kernel(const ExtractArgs a) 
     __shared__ uint32_t s_wave_total[kWaves];
     __shared__ uint32_t s_excl;
     __shared__ uint32_t s_stage[kStage];
+    __shared__ u32x4 s_tail;               // the tile's last, incomplete vector (see below) and its change mask
+    __shared__ uint32_t s_tail_mask;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
 
@@ -422,20 +454,29 @@ __global__ __launch_bounds__(kThreads) void extract_kernel(const ExtractArgs a) 
         idx_base = (uint32_t)(b0 + bucket_off);         // index = tensor-flat position
     }
 
-    // ---- stream the tile.  Layout: wave w owns elements [w*V*ROW, (w+1)*V*ROW); inside it vector j
-    // of lane l holds elements (j*64 + l)*VE .. +VE, so ascending order is (wave, j, lane, element).
+    // ---- stream the tile in 16-byte vectors on a grid that starts at the 16-byte boundary at or before its first
+    // snapshot element, h elements earlier.  Wave w owns grid positions [w*V*ROW, (w+1)*V*ROW); inside it vector j of
+    // lane l holds positions (j*64 + l)*VE .. +VE, so ascending order is (wave, j, lane, element).  Vectors that lie
+    // wholly in the tile are one load each whatever the alignment of the new weights.  What is left over is at most one
+    // incomplete vector in front (thread 0's first) and one behind the last whole vector (thread kThreads-1 takes it, as
+    // a vector of its own that ranks after all others); those two are read element by element.
+    // The sizes of real parameter lists put most tiles off the 16-byte boundaries, or make them incomplete: 300 odd-sized
+    // tensors end to end (108 M elements, 1 % changed) took 283 us when each vector of such a tile was read element by
+    // element, and 116 us now.
     u32x4 xo[V], xn[V];
-    const uint32_t e0 = (uint32_t)wave * (V * ROW) + (uint32_t)lane * VE;
-    // with CAST pn addresses 32-bit elements: pf is the same position in the master weights
-    const gptr<const uint32_t> pf = (gptr<const uint32_t>)pn_raw + pn_off;
-    const gptr<const T> pn = (gptr<const T>)pn_raw + pn_off;
-    const bool aligned = CAST ? (((((uintptr_t)po) | ((uintptr_t)pf)) & 15u) == 0)
-                              : (((((uintptr_t)po) | ((uintptr_t)pn)) & 15u) == 0);
+    const uint32_t h = (uint32_t)((uintptr_t)po & 15u) / EB;
+    const uint32_t glen = len + h;                                      // grid positions h .. glen-1 exist
+    const uint32_t nbody = (glen < TILE ? glen : TILE) / VE * VE;       // positions below it form whole vectors (but for h)
+    const uint32_t g0 = (uint32_t)wave * (V * ROW) + (uint32_t)lane * VE;
+    // bases of the grid: only positions h .. glen-1 are ever accessed
+    const gptr<T> og = po - h;
+    const gptr<const uint32_t> fg = (gptr<const uint32_t>)pn_raw + pn_off - h;     // with CAST: the master weights
+    const gptr<const T> ng = (gptr<const T>)pn_raw + pn_off - h;
+    const bool in_head = h != 0 && tid == 0;                            // this thread's first vector is the incomplete one in front
     uint32_t m[V];
-    // Whole-line refresh: any full tile of 16-byte vectors.  (A tile that does not start on a 128-byte boundary
-    // writes the same bytes in runs of 128 that straddle two lines: correct, only without the benefit.)
-    const bool by_lines = LINES && aligned && len == TILE;              // uniform over the workgroup
-    if (aligned && len == TILE) {
+    if (glen >= TILE) {                                                 // uniform over the workgroup
+        // the thread of the incomplete vector reads its neighbour's instead (and its own below): no branch between the loads
+        const uint32_t g_first = in_head ? VE : g0;
         auto stream_tile = [&](auto hint) {                // all loads of the tile issued back to back
             constexpr bool H = decltype(hint)::value;
             if (CAST) {
@@ -445,14 +486,14 @@ __global__ __launch_bounds__(kThreads) void extract_kernel(const ExtractArgs a) 
                 // the benchmark set at 1 %: 36.2 ms against 37.4 unpaced (pause 4: 36.3)
 #pragma unroll
                 for (int j = 0; j < V; ++j) {
-                    f0[j] = load16<false>(pf + e0 + j * ROW);
+                    f0[j] = load16_any<false>(fg + (j ? g0 + j * ROW : g_first));
                     __builtin_amdgcn_sched_barrier(0); __builtin_amdgcn_s_sleep(kLoadPace / 2); __builtin_amdgcn_sched_barrier(0);
-                    f1[j] = load16<false>(pf + e0 + j * ROW + 4);
+                    f1[j] = load16_any<false>(fg + (j ? g0 + j * ROW : g_first) + 4);
                     __builtin_amdgcn_sched_barrier(0); __builtin_amdgcn_s_sleep(kLoadPace / 2); __builtin_amdgcn_sched_barrier(0);
                 }
 #pragma unroll
                 for (int j = 0; j < V; ++j) {
-                    xo[j] = load16<H>(po + e0 + j * ROW);
+                    xo[j] = load16<H>(og + (j ? g0 + j * ROW : g_first));
                     __builtin_amdgcn_sched_barrier(0); __builtin_amdgcn_s_sleep(kLoadPace / 2); __builtin_amdgcn_sched_barrier(0);
                 }
 #pragma unroll
@@ -467,34 +508,53 @@ __global__ __launch_bounds__(kThreads) void extract_kernel(const ExtractArgs a) 
                 // nothing into weights gains nothing from it (18.87 / 18.83) and stays as it was.
 #pragma unroll
                 for (int j = 0; j < V; ++j) {
-                    xn[j] = load16<H>(pn + e0 + j * ROW);
+                    xn[j] = load16_any<H>(ng + (j ? g0 + j * ROW : g_first));
                     __builtin_amdgcn_sched_barrier(0); __builtin_amdgcn_s_sleep(kLoadPace); __builtin_amdgcn_sched_barrier(0);
                 }
 #pragma unroll
                 for (int j = 0; j < V; ++j) {
-                    xo[j] = load16<H>(po + e0 + j * ROW);
+                    xo[j] = load16<H>(og + (j ? g0 + j * ROW : g_first));
                     __builtin_amdgcn_sched_barrier(0); __builtin_amdgcn_s_sleep(kLoadPace); __builtin_amdgcn_sched_barrier(0);
                 }
             } else {
 #pragma unroll
-                for (int j = 0; j < V; ++j) xn[j] = load16<H>(pn + e0 + j * ROW);
+                for (int j = 0; j < V; ++j) xn[j] = load16_any<H>(ng + (j ? g0 + j * ROW : g_first));
 #pragma unroll
-                for (int j = 0; j < V; ++j) xo[j] = load16<H>(po + e0 + j * ROW);
+                for (int j = 0; j < V; ++j) xo[j] = load16<H>(og + (j ? g0 + j * ROW : g_first));
             }
         };
         // one flavour of loads per instantiation: choosing between two at run time cost 2 ms of the 3 ms the hints gain
         stream_tile(std::integral_constant<bool, NT || LINES>{});
     } else {
+        constexpr bool H = NT || LINES;
+        const u32x4 none = {0u, 0u, 0u, 0u};
 #pragma unroll
         for (int j = 0; j < V; ++j) {
-            const uint32_t e = e0 + j * ROW;
-            if (aligned && e + VE <= len) {
-                xo[j] = load16<false>(po + e);
-                if (CAST) xn[j] = round8_bf16(load16<false>(pf + e), load16<false>(pf + e + 4));
-                else xn[j] = load16<false>(pn + e);
-            } else {
-                xo[j] = EL::load_guarded(po, e, len);
-                xn[j] = CAST ? load8_guarded_cast(pf, e, len) : EL::load_guarded(pn, e, len);
+            const uint32_t g = g0 + j * ROW;
+            const bool whole = g < nbody && (j > 0 || !in_head);
+            xo[j] = whole ? load16<H>(og + g) : none;
+            if (CAST) xn[j] = whole ? round8_bf16(load16_any<false>(fg + g), load16_any<false>(fg + g + 4)) : none;
+            else xn[j] = whole ? load16_any<H>(ng + g) : none;
+        }
+    }
+    const bool has_tail = glen > nbody;                                 // uniform
+    if (h != 0 || has_tail) {
+        const bool front = in_head && nbody != 0;
+        if (front || (has_tail && tid == kThreads - 1)) {
+            const uint32_t at = front ? 0u : nbody;
+            const uint32_t lo = (h > at) ? h - at : 0u, hi = front ? VE : glen - nbody;
+            const u32x4 vo = EL::load_window(og + at, lo, hi);
+            u32x4 vn;
+            if constexpr (CAST) vn = load8_window_cast(fg + at, lo, hi);
+            else vn = EL::load_window(ng + at, lo, hi);
+            if (front) { xo[0] = vo; xn[0] = vn; }
+            const uint32_t md = EL::diff_mask(vo, vn);
+            if (!front) { s_tail = vn; s_tail_mask = md; }
+            if (LINES) {                                                // these two are refreshed element by element
+                for (uint32_t mm = md; mm; mm &= mm - 1u) {
+                    const uint32_t e = (uint32_t)__builtin_ctz(mm);
+                    og[at + e] = (T)EL::pattern(vn, e);
+                }
             }
         }
     }
@@ -520,12 +580,29 @@ __global__ __launch_bounds__(kThreads) void extract_kernel(const ExtractArgs a) 
         ex[2 * q + 1] = wave_total + (exc >> 16);
         wave_total += tot >> 16;
     }
-    // ---- snapshot refresh by whole lines: lane groups of 8 hold one aligned 128-byte line per vector
-    if (by_lines) {
+    // ---- snapshot refresh by whole lines: 8 consecutive grid vectors from a 128-byte boundary on, which begins q lanes
+    // before lane 0's vector; the line across the end of a row has its other vectors in the next row
+    if (LINES) {
+        const uint32_t q = ((uint32_t)(uintptr_t)og >> 4) & 7u;         // uniform
+        if (q == 0) {
 #pragma unroll
-        for (int j = 0; j < V; ++j) {
-            const unsigned long long changed = __ballot(m[j] != 0);
-            if ((uint32_t)(changed >> (lane & ~7)) & 0xFFu) store16_nt(po + e0 + j * ROW, xn[j]);
+            for (int j = 0; j < V; ++j) {
+                const unsigned long long changed = __ballot(m[j] != 0);
+                const uint32_t g = g0 + j * ROW;
+                if (((uint32_t)(changed >> (lane & ~7)) & 0xFFu) && g < nbody && (j > 0 || !in_head)) store16_nt(og + g, xn[j]);
+            }
+        } else {
+            const int first = (int)(((uint32_t)lane + q) & ~7u) - (int)q;                        // -7 .. 63
+            unsigned long long prev = 0, cur = __ballot(m[0] != 0);
+#pragma unroll
+            for (int j = 0; j < V; ++j) {
+                const unsigned long long next = (j + 1 < V) ? __ballot(m[(j + 1) % V] != 0) : 0ull;
+                uint32_t line = (first < 0) ? (uint32_t)((cur << -first) | (prev >> (64 + first))) : (uint32_t)(cur >> first);
+                if (first > 56) line |= (uint32_t)(next << (64 - first));
+                const uint32_t g = g0 + j * ROW;
+                if ((line & 0xFFu) && g < nbody && (j > 0 || !in_head)) store16_nt(og + g, xn[j]);
+                prev = cur; cur = next;
+            }
         }
     }
     if (lane == 0) s_wave_total[wave] = wave_total;
@@ -537,7 +614,9 @@ __global__ __launch_bounds__(kThreads) void extract_kernel(const ExtractArgs a) 
         wave_base += (w < wave) ? t : 0u;
         tile_total += t;
     }
-    tile_total = uniform(tile_total);
+    const uint32_t tail_rank = tile_total;                // the tail's changed elements rank last
+    const uint32_t tail_mask = has_tail ? s_tail_mask : 0u;
+    tile_total = uniform(tile_total + (uint32_t)__popc(tail_mask));
 #pragma unroll
     for (int j = 0; j < V; ++j) ex[j] += wave_base;       // from here on: rank inside the tile
 
@@ -574,23 +653,23 @@ __global__ __launch_bounds__(kThreads) void extract_kernel(const ExtractArgs a) 
         // 22.3 / 39.9 ms staged; smaller tiles do better staged).
         __syncthreads();                            // s_excl
         const uint32_t excl = s_excl;
-        const bool elementwise = RG == 0 || (LINES && !by_lines);
-#pragma unroll
-        for (int j = 0; j < V; ++j) {
-            uint32_t mm = m[j];
-            uint32_t r = excl + ex[j];              // below 2^32: a bucket holds fewer than 2^31 elements
-            const uint32_t local = e0 + j * ROW;
+        auto write_out = [&](uint32_t mm, uint32_t r, uint32_t g, u32x4 x) {
+            // r is below 2^32: a bucket holds fewer than 2^31 elements
             while (mm) {
                 const uint32_t e = (uint32_t)__builtin_ctz(mm);
                 mm &= mm - 1u;
-                const T val = (T)EL::pattern(xn[j], e);
-                if (local + e < len) {              // masks are zero beyond len; keeps stores in bounds regardless
-                    if ((uint64_t)r < a.cap) { Ib[r] = (int32_t)(idx_base + local + e); Vb[r] = val; }
-                    if (elementwise) po[local + e] = val;
+                const T val = (T)EL::pattern(x, e);
+                const uint32_t local = g + e - h;
+                if (local < len) {                  // masks are zero outside the tile; keeps stores in bounds regardless
+                    if ((uint64_t)r < a.cap) { Ib[r] = (int32_t)(idx_base + local); Vb[r] = val; }
+                    if (RG == 0) po[local] = val;
                 }
                 ++r;
             }
-        }
+        };
+#pragma unroll
+        for (int j = 0; j < V; ++j) write_out(m[j], excl + ex[j], g0 + j * ROW, xn[j]);
+        if (has_tail && tid == kThreads - 1) write_out(tail_mask, excl + tail_rank, nbody, s_tail);
         return;
     }
     for (uint32_t r0 = 0; r0 < tile_total; r0 += kStage) {
@@ -601,13 +680,20 @@ __global__ __launch_bounds__(kThreads) void extract_kernel(const ExtractArgs a) 
             // that lies wholly before or after them (this keeps dense tiles linear in the number of rounds)
             if (mm && ex[j] < r0 + kStage && ex[j] + __popc(mm) > r0) {
                 uint32_t rank = ex[j] - r0;                  // wraps for elements of earlier rounds: skipped below
-                const uint32_t local = e0 + j * ROW;
+                const uint32_t local = g0 + j * ROW - h;
                 while (mm) {
                     const uint32_t e = (uint32_t)__builtin_ctz(mm);
                     mm &= mm - 1u;
                     if (rank < kStage) s_stage[rank] = ((local + e) << 16) | EL::pattern(xn[j], e);
                     ++rank;
                 }
+            }
+        }
+        if (has_tail && tid == kThreads - 1) {
+            uint32_t rank = tail_rank - r0;
+            for (uint32_t mm = tail_mask; mm; mm &= mm - 1u, ++rank) {
+                const uint32_t e = (uint32_t)__builtin_ctz(mm);
+                if (rank < kStage) s_stage[rank] = ((nbody - h + e) << 16) | EL::pattern(s_tail, e);
             }
         }
         lds_barrier();
@@ -620,8 +706,7 @@ __global__ __launch_bounds__(kThreads) void extract_kernel(const ExtractArgs a) 
             const uint64_t r = (uint64_t)excl + r0 + k;
             if (local < len) {                      // always true for a correct scan; keeps stores in bounds
                 if (r < a.cap) { Ib[r] = (int32_t)(idx_base + local); Vb[r] = val; }
-                // snapshot refresh: W_prev <- W at changed positions, unless the tile went by whole lines
-                if (RG == 0 || (LINES && !by_lines)) po[local] = val;
+                if (RG == 0) po[local] = val;           // snapshot refresh: W_prev <- W at changed positions
             }
         }
         lds_barrier();
