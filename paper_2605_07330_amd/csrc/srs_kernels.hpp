@@ -1498,93 +1498,193 @@ __global__ __launch_bounds__(kThreads) void vc_hist_kernel(const ValueCodecArgs 
 
 // One workgroup per bucket builds the Huffman lengths exactly as the header specifies (merge the two smallest
 // live nodes, ties to the smaller id; weights halved until no length exceeds 12), then all threads derive the
-// canonical codes.  The merge runs in wave 0: node ids 0..255 are the symbols, 256.. the merged nodes in order
-// of creation; lane l keeps the keys (weight << 9 | id) of the nodes l, l + 64, ... l + 448 in registers (all
-// ones = not live), so "the smallest live node by (weight, id)" is a wave-wide minimum of one 64-bit key per
-// lane and a merge step is two of those.  The leaf depths are then read off the parent array by all threads.
-__device__ __forceinline__ unsigned long long wave_min_u64(unsigned long long x) {
+// canonical codes.  Node ids 0..255 are the symbols, 256.. the merged nodes in order of creation.  The symbols are sorted
+// once by (weight, id); merged nodes come into being in ascending (weight, id) order by themselves, so the two
+// smallest live nodes are always at the heads of these two queues, and a tie between them goes to the symbol.  One wave
+// runs the merge with both queues in registers and the queue heads in scalar registers: a step is a few readlanes.  Up
+// to kVcWave symbols (the high bytes of weights are 20 to 30) a wave also sorts and measures the depths by itself, and the
+// waves try successive halvings side by side; more symbols take R = 4 registers per lane and queue (entry i in lane i & 63
+// of register i >> 6) and the whole workgroup around the merge.  Bound by the serial chain.  240 buckets of 335 k
+// values: 147 us when every step searched all nodes for its two minima with 64-bit wave reductions, 49 us by the general
+// path, and 15 us now.
+__device__ __forceinline__ uint32_t lane_value(uint32_t x, uint32_t lane) { return (uint32_t)__builtin_amdgcn_readlane((int)x, (int)lane); }
+
+template <int R>
+__device__ __forceinline__ void vc_merge(uint32_t used, const uint32_t *sorted_w, const uint8_t *sorted_s, int16_t *parent, int lane) {
+    uint32_t leaf[R], node[R], leaf_up[R], node_up[R];       // weights; ids of the parents
 #pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const unsigned long long y = __shfl_xor(x, d, 64);
-        x = y < x ? y : x;
+    for (int r = 0; r < R; ++r) {
+        const uint32_t i = (uint32_t)lane + 64u * r;
+        leaf[r] = i < used ? sorted_w[i] : 0u;
+        node[r] = leaf_up[r] = node_up[r] = 0u;
     }
-    return x;
+    uint32_t nl = 0, nn = 0;                                 // heads of the two queues
+    for (uint32_t made = 0; made + 1 < used; ++made) {       // `made` is also the end of the queue of merged nodes
+        uint32_t sum = 0;
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            uint32_t wl = 0, wn = 0;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                if ((nl >> 6) == (uint32_t)r) wl = lane_value(leaf[r], nl & 63u);
+                if ((nn >> 6) == (uint32_t)r) wn = lane_value(node[r], nn & 63u);
+            }
+            const bool take_leaf = nl < used && (nn >= made || wl <= wn);      // one of the two queues has an entry
+            const uint32_t at = take_leaf ? nl : nn;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const bool here = (at >> 6) == (uint32_t)r && (at & 63u) == (uint32_t)lane;
+                if (here && take_leaf) leaf_up[r] = 256u + made;
+                if (here && !take_leaf) node_up[r] = 256u + made;
+            }
+            sum += take_leaf ? wl : wn;
+            nl += take_leaf ? 1u : 0u;
+            nn += take_leaf ? 0u : 1u;
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            if ((made >> 6) == (uint32_t)r && (made & 63u) == (uint32_t)lane) node[r] = sum;
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {                            // the root has no parent: -1 stands
+        const uint32_t i = (uint32_t)lane + 64u * r;
+        if (i < used && leaf_up[r]) parent[sorted_s[i]] = (int16_t)leaf_up[r];
+        if (i + 2 < used) parent[256 + i] = (int16_t)node_up[r];               // used - 1 merged nodes, the last is the root
+    }
+}
+
+// Code length of symbol number `lane` of `used` = 2 .. kVcWave (weight w, 0 for lanes past the last; lanes in symbol order).
+// perm: 64 words of LDS of this wave's own.  No branches inside a step: a queue that is empty shows the largest word.
+constexpr uint32_t kVcWave = 63;
+
+__device__ __forceinline__ uint32_t vc_wave_lengths(uint32_t w, uint32_t used, uint32_t *perm, int lane) {
+    constexpr uint32_t kEmpty = 0xFFFFFFFFu;
+    const uint32_t me = (uint32_t)lane;
+    uint32_t rank = 0;                                       // by (weight, symbol)
+    for (uint32_t i = 0; i < used; ++i) {
+        const uint32_t x = lane_value(w, i);
+        rank += (x < w || (x == w && i < me)) ? 1u : 0u;
+    }
+    if (me < used) perm[rank] = w;
+    __builtin_amdgcn_wave_barrier();                         // one wave: its LDS operations stay in order
+    const uint32_t leaf = me < used ? *(volatile uint32_t *)(perm + lane) : kEmpty;
+    uint32_t node = kEmpty, up = 0, leaf_up = 0;             // merged weights, their parents, the sorted symbols' parents
+    uint32_t nl = 0, nn = 0;                                 // at most 63 each
+    for (uint32_t made = 0; made + 1 < used; ++made) {
+        uint32_t sum = 0;
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const uint32_t wl = lane_value(leaf, nl), wn = lane_value(node, nn);
+            const bool take_leaf = wl <= wn;
+            leaf_up = me == (take_leaf ? nl : 64u) ? made : leaf_up;
+            up = me == (take_leaf ? 64u : nn) ? made : up;
+            sum += take_leaf ? wl : wn;
+            nl += take_leaf ? 1u : 0u;
+            nn += take_leaf ? 0u : 1u;
+        }
+        node = (me == made) ? sum : node;
+    }
+    uint32_t depth = 0;                                      // of the merged nodes, from the root down
+    for (int k = (int)used - 3; k >= 0; --k) {
+        const uint32_t d = lane_value(depth, lane_value(up, (uint32_t)k)) + 1u;
+        depth = (lane == k) ? d : depth;
+    }
+    const uint32_t sorted_len = (uint32_t)__shfl((int)depth, (int)leaf_up, 64) + 1u;
+    const uint32_t l = (uint32_t)__shfl((int)sorted_len, (int)(rank & 63u), 64);
+    return me < used ? l : 0u;
 }
 
 __global__ __launch_bounds__(kThreads) void vc_build_kernel(const ValueCodecArgs a) {
-    constexpr unsigned long long kDead = ~0ull;
     __shared__ int16_t parent[512];
-    __shared__ uint32_t w0[256];
-    __shared__ uint8_t len[256];
-    __shared__ uint32_t count_l[kVcMaxLen + 2];
-    __shared__ uint32_t s_used, s_maxlen;
+    __shared__ __align__(16) uint32_t packed_w[256];         // weights of the symbols that occur, in symbol order, then 0
+    __shared__ uint32_t sorted_w[256];
+    __shared__ uint8_t sorted_s[256];
+    __shared__ uint32_t count_l[kVcMaxLen + 1][kWaves];
+    __shared__ uint32_t s_used[kWaves], s_maxlen, s_fits[kWaves];
+    __shared__ uint8_t s_len[256];
     const uint32_t b = blockIdx.x, s = threadIdx.x;
-    const int lane = s & 63;
-    w0[s] = a.hist[(uint64_t)b * 256 + s];
-    len[s] = 0;
-    if (s < kVcMaxLen + 2) count_l[s] = 0;
-    if (s == 0) s_used = 0;
+    const int lane = s & 63, wave = s >> 6;
+    uint32_t w = a.hist[(uint64_t)b * 256 + s];
+    packed_w[s] = 0;
+    const unsigned long long there = __ballot(w != 0);
+    if (lane == 0) s_used[wave] = (uint32_t)__builtin_popcountll(there);
     __syncthreads();
-    if (w0[s]) atomicAdd(&s_used, 1u);
-    __syncthreads();
-    const uint32_t used = s_used;
-    while (used > 0) {                                       // uniform: every thread takes every barrier
+    uint32_t used = 0, place = (uint32_t)__builtin_popcountll(there & ((1ull << lane) - 1ull));
+#pragma unroll
+    for (int v = 0; v < kWaves; ++v) { place += (v < wave) ? s_used[v] : 0u; used += s_used[v]; }
+    used = uniform(used);
+    uint32_t l = 0;
+    if (used == 1) {
+        l = w ? 1u : 0u;
+    } else if (used > 1 && used <= kVcWave) {                // uniform
+        if (w) packed_w[place] = w;
+        __syncthreads();
+        // r halvings make ceil(w / 2^r): the four waves try four numbers of halvings at a time (335 k values take 6)
+        for (uint32_t r0 = 0;; r0 += kWaves) {               // 31 halvings leave weights of 1 and lengths of 6 at most
+            const uint32_t r = r0 + (uint32_t)wave;
+            const uint32_t wr = (uint32_t)(((uint64_t)packed_w[lane] + (1ull << r) - 1ull) >> r);
+            const uint32_t len = vc_wave_lengths(wr, used, sorted_w + 64 * wave, lane);
+            s_len[64 * wave + lane] = (uint8_t)len;
+            const bool fits = !__any(len > kVcMaxLen);
+            if (lane == 0) s_fits[wave] = fits ? 1u : 0u;
+            __syncthreads();
+            uint32_t hit = kWaves;
+#pragma unroll
+            for (int v = kWaves - 1; v >= 0; --v) hit = s_fits[v] ? (uint32_t)v : hit;
+            hit = uniform(hit);
+            if (hit < kWaves) { l = w ? (uint32_t)s_len[64 * hit + place] : 0u; break; }
+            __syncthreads();                                 // everybody has read s_fits
+        }
+    }
+    while (used > kVcWave) {                                 // uniform: every thread takes every barrier
+        if (w) packed_w[place] = w;
         parent[s] = -1; parent[s + 256] = -1;
         if (s == 0) s_maxlen = 0;
         __syncthreads();
-        if (s < 64) {
-            unsigned long long key[8];
+        if (w) {                                             // rank by (weight, symbol): every weight is non-zero
+            uint32_t rank = 0;
+            for (uint32_t i = 0; i < used; i += 4) {         // entries past the last are 0 ...
+                const u32x4 x = *reinterpret_cast<const u32x4 *>(packed_w + i);
+                const uint32_t xi[4] = {x.x, x.y, x.z, x.w};
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const uint32_t id = (uint32_t)lane + 64u * r, w = w0[id];
-                key[r] = w ? (((unsigned long long)w << 9) | id) : kDead;
-                key[r + 4] = kDead;                           // merged nodes 256 + lane + 64 r: none yet
+                for (uint32_t c = 0; c < 4; ++c) rank += (xi[c] < w || (xi[c] == w && i + c < place)) ? 1u : 0u;
             }
-            uint32_t nnodes = 256;
-            for (uint32_t nlive = used; nlive > 1; --nlive, ++nnodes) {
-                unsigned long long pick[2];
-#pragma unroll
-                for (int t = 0; t < 2; ++t) {                 // the smallest, then the smallest of what is left
-                    unsigned long long m = key[0];
-#pragma unroll
-                    for (int r = 1; r < 8; ++r) m = key[r] < m ? key[r] : m;
-                    m = wave_min_u64(m);
-                    pick[t] = m;
-#pragma unroll
-                    for (int r = 0; r < 8; ++r) if (key[r] == m) key[r] = kDead;      // ids are unique: one lane, one slot
-                }
-                const uint32_t x = (uint32_t)(pick[0] & 511u), y = (uint32_t)(pick[1] & 511u);
-                const unsigned long long wsum = (pick[0] >> 9) + (pick[1] >> 9);
-                if (lane == 0) { parent[x] = (int16_t)nnodes; parent[y] = (int16_t)nnodes; }
-                const uint32_t slot = nnodes - 256u;          // owner: lane slot & 63, register 4 + slot / 64
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    if ((slot >> 6) == (uint32_t)r && (slot & 63u) == (uint32_t)lane) key[r + 4] = (wsum << 9) | nnodes;
-            }
+            rank -= ((used + 3u) & ~3u) - used;              // ... and counted as smaller
+            sorted_w[rank] = w;
+            sorted_s[rank] = (uint8_t)s;
         }
         __syncthreads();
-        uint32_t d = 0;
-        if (w0[s]) {
-            for (int jn = (int)s; parent[jn] >= 0; jn = parent[jn]) ++d;
-            if (used == 1) d = 1;
-            atomicMax(&s_maxlen, d);
+        if (wave == 0) {
+            vc_merge<4>(used, sorted_w, sorted_s, parent, lane);
         }
-        len[s] = (uint8_t)d;
+        __syncthreads();
+        l = 0;
+        if (w) {
+            for (int jn = (int)s; parent[jn] >= 0; jn = parent[jn]) ++l;
+            atomicMax(&s_maxlen, l);
+        }
         __syncthreads();
         if (s_maxlen <= kVcMaxLen) break;
-        if (w0[s]) w0[s] = (w0[s] + 1) / 2;
-        __syncthreads();
+        w = w ? (w + 1) / 2 : 0u;
+        __syncthreads();                                     // everybody has read s_maxlen
+    }
+    a.lens[(uint64_t)b * 256 + s] = (uint8_t)l;
+    // canonical code = first code of its length + number of smaller symbols of the same length
+    uint32_t rank = 0;
+    for (uint32_t j = 1; j <= kVcMaxLen; ++j) {
+        const unsigned long long m = __ballot(l == j);
+        if (l == j) rank = (uint32_t)__builtin_popcountll(m & ((1ull << lane) - 1ull));
+        if (lane == 0) count_l[j][wave] = (uint32_t)__builtin_popcountll(m);
     }
     __syncthreads();
-    const uint32_t l = len[s];
-    a.lens[(uint64_t)b * 256 + s] = (uint8_t)l;
-    if (l) atomicAdd(&count_l[l], 1u);
-    __syncthreads();
-    // canonical code = first code of its length + number of smaller symbols of the same length
     uint32_t first = 0, code = 0;
-    for (uint32_t j = 1; j <= kVcMaxLen; ++j) { if (j == l) first = code; code = (code + count_l[j]) << 1; }
-    uint32_t rank = 0;
-    for (uint32_t i = 0; i < s; ++i) rank += (len[i] == l) ? 1u : 0u;
+    for (uint32_t j = 1; j <= kVcMaxLen; ++j) {
+        uint32_t cj = 0;
+#pragma unroll
+        for (int v = 0; v < kWaves; ++v) { cj += count_l[j][v]; if (j == l && v < wave) rank += count_l[j][v]; }
+        if (j == l) first = code;
+        code = (code + cj) << 1;
+    }
     const uint32_t c = first + rank;
     a.rcode[(uint64_t)b * 256 + s] = l ? (__brev(c) >> (32 - l)) : 0u;
 }

@@ -126,3 +126,27 @@ def test_corrupt_stream_is_flagged(srs, ctx):
     V_out = torch.full((1, cap), -1, dtype=torch.int16, device=DEV)
     ctx.decode_values(enc, d_counts, 1, cap, V_out)
     assert ctx.status() == srs.FLAG_BAD_INDEX
+
+
+@pytest.mark.parametrize("used", [1, 2, 3, 63, 64, 65, 128, 129, 255, 256])
+def test_code_lengths_over_symbol_counts(srs, ctx, used):
+    """Equal, rising and geometric weights (ties among symbols, between symbols and merged nodes, and codes that have to
+    be shortened) for the numbers of symbols around one and four registers of the merge; one bucket of counts each."""
+    print(f"case used={used}", flush=True)
+    rng = np.random.default_rng(used)
+    weights = [np.full(used, 3), np.arange(used) + 1, np.minimum(2 ** np.minimum(np.arange(used), 14), 9000) if used < 20
+               else rng.permutation(np.minimum((1.3 ** np.minimum(np.arange(used), 34)).astype(np.int64), 9000) + (np.arange(used) % 2))]
+    rows = []
+    for wgt in weights:
+        hi = np.repeat(rng.permutation(256)[:used].astype(np.uint16), np.maximum(wgt, 1))
+        rng.shuffle(hi)
+        rows.append((hi << 8) | rng.integers(0, 256, size=hi.size, dtype=np.uint16))
+    cap = max(r.size for r in rows)
+    counts = np.array([r.size for r in rows], np.uint32)
+    V = np.stack([np.pad(r, (0, cap - r.size)) for r in rows])
+    want = oracle.encode_values(V, counts)
+    d_V = to_dev(V, np.int16); d_counts = to_dev(counts, np.int32)
+    enc = srs.alloc_value_stream(len(rows), cap, DEV)
+    ctx.encode_values(d_V, d_counts, len(rows), cap, enc)
+    assert ctx.status() == 0
+    check_stream(enc, want, counts, cap)
