@@ -1447,20 +1447,27 @@ struct ValueCodecArgs {
 constexpr uint32_t kVcHistChunks = 8;        // chunks of one bucket counted by one workgroup
 
 __global__ __launch_bounds__(kThreads) void vc_hist_kernel(const ValueCodecArgs a) {
-    // The high bytes of a payload crowd into a handful of bins, and LDS atomics of one wave on one address take
-    // turns: 32 partial histograms, one per 8 lanes, 257 words apart so that the same bin of different partials
-    // lies in different banks.
-    constexpr uint32_t kParts = kThreads / 8, kPitch = 257;
-    __shared__ uint32_t h[kParts * kPitch];
+    // The high bytes of a payload crowd into a handful of bins, and LDS atomics of one wave on one word take turns: every
+    // two lanes count in a histogram of their own, with four bins to a word (two threads count 128 values, so a
+    // byte holds any count), 65 words apart so that the same word of different histograms lies in different banks.
+    // 240 buckets of 335 k values: 86 us with a 32-bit histogram per 8 lanes, 44 us now.
+    constexpr uint32_t kParts = kThreads / 2, kPitch = 65;
+    static_assert(kVcHistChunks * kVcChunk / kParts < 256u, "a byte holds every count of two threads");
+    static_assert(kParts * kPitch % (4 * kThreads) / 4 <= kThreads && kParts * kPitch % 4 == 0, "cleared in 16-byte stores");
+    __shared__ __align__(16) uint32_t h[kParts * kPitch];
+    __shared__ uint32_t s_sum[256];
     const uint32_t groups = (a.nchunk + kVcHistChunks - 1) / kVcHistChunks;
     const uint32_t b = blockIdx.x / groups, g = blockIdx.x - b * groups;
     const uint64_t cnt = ((uint64_t)a.counts[b] < a.cap) ? a.counts[b] : a.cap;
     const uint64_t g0 = (uint64_t)g * kVcHistChunks * kVcChunk;
     if (g0 >= cnt) return;
     const uint32_t s = threadIdx.x;
-    uint32_t *const mine = h + (s >> 3) * kPitch;
+    uint32_t *const mine = h + (s >> 1) * kPitch;
+    auto count = [&](uint32_t bin) { atomicAdd(&mine[bin >> 2], 1u << (8u * (bin & 3u))); };
     const uint32_t gn = (uint32_t)((cnt - g0 < (uint64_t)kVcHistChunks * kVcChunk) ? (cnt - g0) : kVcHistChunks * kVcChunk);
-    for (uint32_t i = s; i < kParts * kPitch; i += kThreads) h[i] = 0;
+    const u32x4 zero = {0, 0, 0, 0};
+    for (uint32_t i = s; i < kParts * kPitch / 4; i += kThreads) reinterpret_cast<u32x4 *>(h)[i] = zero;
+    s_sum[s] = 0;
     __syncthreads();
     const uint16_t *v = a.V + (uint64_t)b * a.cap + g0;
     if ((((uintptr_t)v) & 15u) == 0) {
@@ -1479,21 +1486,32 @@ __global__ __launch_bounds__(kThreads) void vc_hist_kernel(const ValueCodecArgs 
                 const uint32_t d[4] = {x[q].x, x[q].y, x[q].z, x[q].w};
 #pragma unroll
                 for (int c = 0; c < 4; ++c) {
-                    atomicAdd(&mine[(d[c] >> 8) & 0xFFu], 1u);
-                    atomicAdd(&mine[d[c] >> 24], 1u);
+                    count((d[c] >> 8) & 0xFFu);
+                    count(d[c] >> 24);
                 }
             } else {
-                for (uint32_t i = i0; i < gn; ++i) atomicAdd(&mine[v[i] >> 8], 1u);
+                for (uint32_t i = i0; i < gn; ++i) count(v[i] >> 8);
             }
         }
     } else {
-        for (uint32_t i = s; i < gn; i += kThreads) atomicAdd(&mine[v[i] >> 8], 1u);
+        for (uint32_t i = s; i < gn; i += kThreads) count(v[i] >> 8);
     }
     __syncthreads();
-    uint32_t t = 0;
+    // every wave adds up a quarter of the histograms, a lane one word of them, two bins to a 16-bit field each
+    const uint32_t word = s & 63u, p0 = (s >> 6) * (kParts / kWaves);
+    uint32_t even = 0, odd = 0;
 #pragma unroll 8
-    for (uint32_t p = 0; p < kParts; ++p) t += h[p * kPitch + s];
-    if (t) atomicAdd(a.hist + (uint64_t)b * 256 + s, t);
+    for (uint32_t p = 0; p < kParts / kWaves; ++p) {
+        const uint32_t x = h[(p0 + p) * kPitch + word];
+        even += x & 0x00FF00FFu;
+        odd += (x >> 8) & 0x00FF00FFu;
+    }
+    const uint32_t n[4] = {even & 0xFFFFu, odd & 0xFFFFu, even >> 16, odd >> 16};
+#pragma unroll
+    for (uint32_t c = 0; c < 4; ++c)
+        if (n[c]) atomicAdd(&s_sum[4u * word + c], n[c]);
+    __syncthreads();
+    if (s_sum[s]) atomicAdd(a.hist + (uint64_t)b * 256 + s, s_sum[s]);
 }
 
 // One workgroup per bucket builds the Huffman lengths exactly as the header specifies (merge the two smallest
