@@ -168,18 +168,6 @@ __device__ __forceinline__ u32x4 load16_any(gptr<const void> p) {
 }
 __device__ __forceinline__ void store16_nt(gptr<void> p, u32x4 v) { __builtin_nontemporal_store(v, (gptr<u32x4>)p); }
 
-// 8 patterns starting at element e of a run of len elements, as 4 dwords; elements at or beyond
-// len read as 0 (for both inputs, hence "unchanged").  Any alignment.
-__device__ __forceinline__ u32x4 load8_guarded(gptr<const uint16_t> p, uint32_t e, uint32_t len) {
-    uint32_t h[8];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) h[k] = (e + k < len) ? (uint32_t)p[e + k] : 0u;
-    u32x4 r;
-    r.x = h[0] | (h[1] << 16); r.y = h[2] | (h[3] << 16);
-    r.z = h[4] | (h[5] << 16); r.w = h[6] | (h[7] << 16);
-    return r;
-}
-
 // binary32 pattern -> BF16 pattern, round to nearest even; NaN -> 0x7FC0
 __device__ __forceinline__ uint32_t round_bf16(uint32_t x) {
     const uint32_t r = (x + 0x7FFFu + ((x >> 16) & 1u)) >> 16;
@@ -211,17 +199,6 @@ __device__ __forceinline__ u32x4 load8_window_cast(gptr<const uint32_t> p, uint3
     uint32_t h[8];
 #pragma unroll
     for (uint32_t k = 0; k < 8; ++k) h[k] = (k >= lo && k < hi) ? round_bf16(p[k]) : 0u;
-    u32x4 r;
-    r.x = h[0] | (h[1] << 16); r.y = h[2] | (h[3] << 16);
-    r.z = h[4] | (h[5] << 16); r.w = h[6] | (h[7] << 16);
-    return r;
-}
-
-// guarded, any alignment (4-byte elements): elements at or beyond len read as BF16 pattern 0
-__device__ __forceinline__ u32x4 load8_guarded_cast(gptr<const uint32_t> p, uint32_t e, uint32_t len) {
-    uint32_t h[8];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) h[k] = (e + k < len) ? round_bf16(p[e + k]) : 0u;
     u32x4 r;
     r.x = h[0] | (h[1] << 16); r.y = h[2] | (h[3] << 16);
     r.z = h[4] | (h[5] << 16); r.w = h[6] | (h[7] << 16);
@@ -355,6 +332,36 @@ __device__ __forceinline__ uint32_t look_back(const ExtractArgs &a, uint32_t til
         pos -= 64;
     }
     return excl;
+}
+
+// Refresh by whole lines of a tile read on extract_kernel's grid (og: grid position 0, g0: this lane's first, m: change
+// masks, x: what to write): 8 consecutive grid vectors from a 128-byte boundary on, which begins q lanes before lane 0's
+// vector; the line across the end of a row has its other vectors in the next row.
+template <int V, class T>
+__device__ __forceinline__ void refresh_lines(gptr<T> og, uint32_t g0, uint32_t nbody, bool in_head, const uint32_t (&m)[V],
+                                              const u32x4 (&x)[V], int lane) {
+    constexpr uint32_t ROW = 64u * 16u / sizeof(T);
+    const uint32_t q = ((uint32_t)(uintptr_t)og >> 4) & 7u;             // uniform
+    if (q == 0) {
+#pragma unroll
+        for (int j = 0; j < V; ++j) {
+            const unsigned long long changed = __ballot(m[j] != 0);
+            const uint32_t g = g0 + j * ROW;
+            if (((uint32_t)(changed >> (lane & ~7)) & 0xFFu) && g < nbody && (j > 0 || !in_head)) store16_nt(og + g, x[j]);
+        }
+    } else {
+        const int first = (int)(((uint32_t)lane + q) & ~7u) - (int)q;                            // -7 .. 63
+        unsigned long long prev = 0, cur = __ballot(m[0] != 0);
+#pragma unroll
+        for (int j = 0; j < V; ++j) {
+            const unsigned long long next = (j + 1 < V) ? __ballot(m[(j + 1) % V] != 0) : 0ull;
+            uint32_t line = (first < 0) ? (uint32_t)((cur << -first) | (prev >> (64 + first))) : (uint32_t)(cur >> first);
+            if (first > 56) line |= (uint32_t)(next << (64 - first));
+            const uint32_t g = g0 + j * ROW;
+            if ((line & 0xFFu) && g < nbody && (j > 0 || !in_head)) store16_nt(og + g, x[j]);
+            prev = cur; cur = next;
+        }
+    }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -580,31 +587,7 @@ __global__ __launch_bounds__(kThreads, (V >= 16 && SRC == kSrcBf16) ? 3 : 1) voi
         ex[2 * q + 1] = wave_total + (exc >> 16);
         wave_total += tot >> 16;
     }
-    // ---- snapshot refresh by whole lines: 8 consecutive grid vectors from a 128-byte boundary on, which begins q lanes
-    // before lane 0's vector; the line across the end of a row has its other vectors in the next row
-    if (LINES) {
-        const uint32_t q = ((uint32_t)(uintptr_t)og >> 4) & 7u;         // uniform
-        if (q == 0) {
-#pragma unroll
-            for (int j = 0; j < V; ++j) {
-                const unsigned long long changed = __ballot(m[j] != 0);
-                const uint32_t g = g0 + j * ROW;
-                if (((uint32_t)(changed >> (lane & ~7)) & 0xFFu) && g < nbody && (j > 0 || !in_head)) store16_nt(og + g, xn[j]);
-            }
-        } else {
-            const int first = (int)(((uint32_t)lane + q) & ~7u) - (int)q;                        // -7 .. 63
-            unsigned long long prev = 0, cur = __ballot(m[0] != 0);
-#pragma unroll
-            for (int j = 0; j < V; ++j) {
-                const unsigned long long next = (j + 1 < V) ? __ballot(m[(j + 1) % V] != 0) : 0ull;
-                uint32_t line = (first < 0) ? (uint32_t)((cur << -first) | (prev >> (64 + first))) : (uint32_t)(cur >> first);
-                if (first > 56) line |= (uint32_t)(next << (64 - first));
-                const uint32_t g = g0 + j * ROW;
-                if ((line & 0xFFu) && g < nbody && (j > 0 || !in_head)) store16_nt(og + g, xn[j]);
-                prev = cur; cur = next;
-            }
-        }
-    }
+    if (LINES) refresh_lines<V, T>(og, g0, nbody, in_head, m, xn, lane);
     if (lane == 0) s_wave_total[wave] = wave_total;
     __syncthreads();
     uint32_t wave_base = 0, tile_total = 0;
@@ -855,63 +838,85 @@ __global__ __launch_bounds__(kThreads) void extract_marked_kernel(const ExtractA
 // are marked.  One workgroup per tile of the plan, in tile order; no chain, no ticket: tiles are independent here.
 // (Extract's bucket-interleaved order measured 3 % faster for two BF16 versions and 5 % slower with CAST.)
 // ---------------------------------------------------------------------------------------------
+// Tiles are read on extract_kernel's grid of 16-byte vectors, so that any alignment and length takes whole vectors but for
+// the incomplete ones in front and behind, which are read (and with CAST written back) element by element.  300 odd-sized
+// tensors end to end, the buffers two bytes off (108 M elements, 1 % changed, two steps marked and extracted): 605 us when
+// every vector of such a tile was read element by element, 208 us now.
 template <int V, bool CAST>
 __global__ __launch_bounds__(kThreads) void mark_kernel(const ExtractArgs a) {
     constexpr uint32_t TILE = (uint32_t)V * kUnit;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     if (blockIdx.x >= a.ntiles) return;
     const TileDesc d = a.tiles[blockIdx.x];
     const PtrPair p = a.ptrs[d.tensor];
     const gptr<uint16_t> po = as_global(p.old_w) + d.tensor_off;
-    const gptr<const uint32_t> pf = (gptr<const uint32_t>)p.new_w + d.tensor_off;
-    const gptr<const uint16_t> pn = (gptr<const uint16_t>)p.new_w + d.tensor_off;
     const uint32_t len = d.len;
-    const uint64_t g0 = a.tensor_base[d.tensor] + d.tensor_off;
-    const uint32_t e0 = (uint32_t)wave * (V * 512u) + (uint32_t)lane * 8u;
-    const bool aligned = CAST ? (((((uintptr_t)po) | ((uintptr_t)pf)) & 15u) == 0)
-                              : (((((uintptr_t)po) | ((uintptr_t)pn)) & 15u) == 0);
-    const bool full = aligned && len == TILE;
+    const uint32_t h = (uint32_t)((uintptr_t)po & 15u) / 2;
+    const uint32_t glen = len + h;                                      // grid positions h .. glen-1 exist
+    const uint32_t nbody = (glen < TILE ? glen : TILE) / 8 * 8;         // positions below it form whole vectors (but for h)
+    const uint32_t g0 = (uint32_t)wave * (V * 512u) + (uint32_t)lane * 8u;
+    const gptr<uint16_t> og = po - h;
+    const gptr<const uint32_t> fg = (gptr<const uint32_t>)p.new_w + d.tensor_off - h;
+    const gptr<const uint16_t> ng = (gptr<const uint16_t>)p.new_w + d.tensor_off - h;
+    // packed position of grid position 0: below zero where the list begins off a 16-byte boundary, and then only for
+    // elements that do not exist
+    const int64_t p0 = (int64_t)(a.tensor_base[d.tensor] + d.tensor_off) - (int64_t)h;
+    const bool in_head = h != 0 && tid == 0;
     u32x4 xo[V], xn[V];
+    // two versions that are only compared are read once each: non-temporal (2 % faster); with CAST the parameters are
+    // rewritten below by whole lines, hinted like extract's snapshot, and the master weights stay on ordinary loads
+    auto load = [&](int j, uint32_t g) {
+        xo[j] = load16<true>(og + g);
+        if (CAST) xn[j] = round8_bf16(load16_any<false>(fg + g), load16_any<false>(fg + g + 4));
+        else xn[j] = load16_any<true>(ng + g);
+    };
+    if (glen >= TILE) {                                                 // uniform over the workgroup
+        // the thread of the incomplete vector reads its neighbour's instead (and its own below)
 #pragma unroll
-    for (int j = 0; j < V; ++j) {
-        const uint32_t e = e0 + j * 512;
-        if (full || (aligned && e + 8 <= len)) {
-            // two versions that are only compared are read once each: non-temporal (2 % faster); with CAST the
-            // parameters are rewritten below by whole lines, hinted like extract's snapshot, and the master weights
-            // stay on ordinary loads
-            xo[j] = load16<true>(po + e);
-            if (CAST) xn[j] = round8_bf16(load16<false>(pf + e), load16<false>(pf + e + 4));
-            else xn[j] = load16<true>(pn + e);
-        } else {
-            xo[j] = load8_guarded(po, e, len);
-            xn[j] = CAST ? load8_guarded_cast(pf, e, len) : load8_guarded(pn, e, len);
+        for (int j = 0; j < V; ++j) load(j, (j == 0 && in_head) ? 8u : g0 + j * 512);
+    } else {
+        const u32x4 none = {0u, 0u, 0u, 0u};
+#pragma unroll
+        for (int j = 0; j < V; ++j) {
+            const uint32_t g = g0 + j * 512;
+            xo[j] = none; xn[j] = none;
+            if (g < nbody && (j > 0 || !in_head)) load(j, g);
         }
     }
-#pragma unroll
-    for (int j = 0; j < V; ++j) {
-        const uint32_t e = e0 + j * 512;
-        const uint32_t m = diff_mask8(xo[j], xn[j]);
-        if (CAST) {                                           // write the cast back where it changed something
-            if (full) {
-                const unsigned long long changed = __ballot(m != 0);
-                if ((uint32_t)(changed >> (lane & ~7)) & 0xFFu) store16_nt(po + e, xn[j]);
-            } else if (m) {
-                uint32_t mm = m;
-                while (mm) {
-                    const uint32_t k = (uint32_t)__builtin_ctz(mm);
-                    mm &= mm - 1u;
-                    po[e + k] = (uint16_t)pattern_at(xn[j], k);       // k < len - e: guarded loads read 0 == 0 beyond len
+    auto mark = [&](uint32_t g, uint32_t m) {                           // bit k of m: grid position g + k changed
+        const int64_t at = p0 + g;
+        const uint32_t sh = (uint32_t)at & 31u;
+        uint32_t *const w = a.bitmap + (at >> 5);
+        if (m << sh) atomicOr(w, m << sh);
+        const uint32_t spill = (sh > 24u) ? (m >> (32u - sh)) : 0u;     // bits that belong to the next word
+        if (spill) atomicOr(w + 1, spill);
+    };
+    const bool has_tail = glen > nbody;                                 // uniform
+    if (h != 0 || has_tail) {
+        const bool front = in_head && nbody != 0;
+        if (front || (has_tail && tid == kThreads - 1)) {
+            const uint32_t at = front ? 0u : nbody;
+            const uint32_t lo = (h > at) ? h - at : 0u, hi = front ? 8u : glen - nbody;
+            const u32x4 vo = load8_window(og + at, lo, hi);
+            const u32x4 vn = CAST ? load8_window_cast(fg + at, lo, hi) : load8_window(ng + at, lo, hi);
+            const uint32_t md = diff_mask8(vo, vn);
+            if (front) { xo[0] = vo; xn[0] = vn; }
+            else if (md) mark(at, md);
+            if (CAST) {
+                for (uint32_t mm = md; mm; mm &= mm - 1u) {
+                    const uint32_t e = (uint32_t)__builtin_ctz(mm);
+                    og[at + e] = (uint16_t)pattern_at(vn, e);
                 }
             }
         }
-        if (m) {
-            const uint64_t g = g0 + e;
-            const uint32_t sh = (uint32_t)(g & 31u);
-            atomicOr(a.bitmap + (g >> 5), m << sh);
-            const uint32_t spill = (sh > 24u) ? (m >> (32u - sh)) : 0u;       // bits that belong to the next word
-            if (spill) atomicOr(a.bitmap + (g >> 5) + 1, spill);
-        }
     }
+    uint32_t m[V];
+#pragma unroll
+    for (int j = 0; j < V; ++j) m[j] = diff_mask8(xo[j], xn[j]);
+    if (CAST) refresh_lines<V, uint16_t>(og, g0, nbody, in_head, m, xn, lane);   // write the cast back where it changed something
+#pragma unroll
+    for (int j = 0; j < V; ++j)
+        if (m[j]) mark(g0 + j * 512, m[j]);
 }
 
 // ---------------------------------------------------------------------------------------------

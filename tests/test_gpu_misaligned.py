@@ -75,3 +75,44 @@ def test_extract_any_alignment(oo, no, mode, tile, kind):
                 assert np.array_equal(host(tb, dt), buf), n
     finally:
         ctx.close()
+
+
+@pytest.mark.parametrize("cast", [False, True])
+@pytest.mark.parametrize("tile", [32768, 4096])
+@pytest.mark.parametrize("oo,no", [(0, 0), (1, 3), (7, 2), (61, 60)])
+def test_mark_any_alignment(oo, no, tile, cast):
+    """Tensors end to end in one buffer, so that each starts at its own offset, in tiles that the buckets cut anywhere."""
+    from paper_2605_07330_amd import srs
+    print(f"case mark old+{oo} new+{no} tile={tile} cast={cast}", flush=True)
+    total, be = sum(SIZES), 20011
+    for density in (0.02, 0.7):
+        rng = np.random.default_rng(100 * oo + no)
+        old = rng.integers(0, 1 << 16, total).astype(np.uint16)
+        change = rng.random(total) < density
+        change[[0, -1]] = True
+        if cast:
+            new = (rng.standard_normal(total) * 0.02).astype(np.float32)
+            old = np.where(change, old, oracle.round_bf16(new)).astype(np.uint16)
+        else:
+            new = np.where(change, ~old, old).astype(np.uint16)
+        cuts = np.cumsum([0] + SIZES)
+        views = lambda t: [t[a:b] for a, b in zip(cuts[:-1], cuts[1:])]  # noqa: E731
+        want, bits = old.copy(), np.zeros(oracle.bitmap_words(total), np.uint32)
+        (oracle.cast_mark_multi if cast else oracle.mark_multi)(views(want), views(new), SIZES, bits)
+        tb, t, buf = device_copy(old, oo)
+        _, u, _ = device_copy(new, no)
+        ctx = srs.Context(0)
+        try:
+            ctx.set_option(srs.OPT_TILE_ELEMS, tile)
+            plan = ctx.plan(SIZES, be)
+            guard = 5                                      # words on both sides of the bitmap stay clear
+            words = torch.zeros(bits.size + 2 * guard, dtype=torch.int32, device=DEV)
+            bitmap = words[guard:guard + bits.size]
+            (ctx.cast_mark_multi if cast else ctx.mark_multi)(plan, views(t), views(u), bitmap)
+            assert ctx.status() == 0
+            assert np.array_equal(host(bitmap, np.uint32), bits)
+            assert (words[:guard] == 0).all() and (words[guard + bits.size:] == 0).all()
+            buf[oo:oo + total] = want
+            assert np.array_equal(host(tb, np.uint16), buf)
+        finally:
+            ctx.close()
