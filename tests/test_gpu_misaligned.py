@@ -116,3 +116,37 @@ def test_mark_any_alignment(oo, no, tile, cast):
             assert np.array_equal(host(tb, np.uint16), buf)
         finally:
             ctx.close()
+
+
+@pytest.mark.parametrize("oo,no", [(0, 0), (1, 3), (7, 2), (61, 60)])
+def test_dense_copy_any_alignment(oo, no):
+    """Every bucket packed whole and unpacked into other weights; slots of an odd size, so that they too start anywhere."""
+    from paper_2605_07330_amd import srs
+    print(f"case dense new+{no} weights+{oo}", flush=True)
+    total, be = sum(SIZES), 20011
+    rng = np.random.default_rng(100 * oo + no)
+    new = rng.integers(0, 1 << 16, total).astype(np.uint16)
+    cuts = np.cumsum([0] + SIZES)
+    views = lambda t: [t[a:b] for a, b in zip(cuts[:-1], cuts[1:])]  # noqa: E731
+    ctx = srs.Context(0)
+    try:
+        plan = ctx.plan(SIZES, be)
+        nb = plan.nbuckets
+        _, u, _ = device_copy(new, no)
+        tb, t, buf = device_copy(np.zeros(total, np.uint16), oo)
+        order = rng.permutation(nb).astype(np.int32)
+        bucket_of = torch.from_numpy(order).to(DEV)
+        n_dense = torch.full((1,), nb, dtype=torch.int32, device=DEV)
+        dense = torch.zeros(nb * be + PAD, dtype=torch.int16, device=DEV)
+        ctx.pack_dense_multi(plan, views(u), views(u), bucket_of, n_dense, nb, dense)
+        want = np.zeros(nb * be + PAD, np.uint16)
+        for s, b in enumerate(order):
+            run = new[b * be:(b + 1) * be]
+            want[s * be:s * be + run.size] = run
+        assert np.array_equal(host(dense, np.uint16), want)
+        ctx.unpack_dense_multi(plan, views(t), bucket_of, n_dense, nb, dense)
+        assert ctx.status() == 0
+        buf[oo:oo + total] = new
+        assert np.array_equal(host(tb, np.uint16), buf)
+    finally:
+        ctx.close()
