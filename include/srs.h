@@ -69,8 +69,9 @@ typedef enum {
 
 /* options for srs_set_option() */
 #define SRS_OPT_SPIN_LIMIT 1   /* max polls of a predecessor tile before SRS_FLAG_TIMEOUT (default 1<<24) */
-#define SRS_OPT_TILE_ELEMS 2   /* elements per extract tile: 4096, 8192, 16384 or 32768 (default; tuning; affects
-                                  plans created afterwards) */
+#define SRS_OPT_TILE_ELEMS 2   /* elements per extract tile: 4096, 8192, 16384 or 32768 (default for plans; tuning;
+                                  affects plans created afterwards).  Until it is set, the calls on a single tensor
+                                  take smaller tiles for small tensors. */
 #define SRS_OPT_REFRESH_GROUP 3 /* snapshot refresh: 8 (default) = every aligned 128-byte line of the snapshot that
                                   holds a change is rewritten from the new weights (unchanged elements get the value
                                   they have; only elements of the tensor are stored); 0 = a store per changed

@@ -61,6 +61,7 @@ struct srs_ctx {
     uint64_t vc_cap = 0;                    // in words
     uint32_t spin_limit = 1u << 24;
     uint32_t tile_elems = 32768;
+    bool tile_set = false;                  // tile_elems was chosen by the caller: single tensors use it too, whatever their size
     uint32_t group = 64;                    // buckets whose tiles are interleaved over consecutive workgroups
     uint32_t refresh_group = 8;             // 8: snapshot refreshed by whole 128-byte lines; 0: element by element
     uint32_t snapshot_mode = 0;             // 0: refreshed inside the scan; 1: left alone, the caller swaps buffers;
@@ -92,8 +93,21 @@ namespace {
 // many buckets, which only happens with bucket sizes far below a tile
 uint32_t ticket_stride_for(uint64_t nb) { return nb <= 65536 ? 64u : 1u; }
 
+// Clears the ticket counters and status words on the stream; nothing to do where no bucket has a second tile, as neither is
+// used then.
+int clear_extract_scratch(uint32_t *tickets, uint64_t nb, uint32_t stride, unsigned long long *status, uint64_t ntiles,
+                          bool one_tile_buckets, hipStream_t st) {
+    if (one_tile_buckets) return SRS_OK;
+    const uint64_t n = ntiles > nb ? ntiles : nb;
+    const uint32_t threads = 256;
+    hipLaunchKernelGGL(prepare_extract_kernel, dim3((uint32_t)((n + threads - 1) / threads)), dim3(threads), 0, st,
+                       tickets, nb, stride, status, ntiles);
+    SRS_HIP(hipGetLastError());
+    return SRS_OK;
+}
+
 // make room for ntiles status words and nb ticket counters, then clear both on the stream
-int prepare_extract(srs_ctx *ctx, uint64_t ntiles, uint64_t nb, hipStream_t st, uint32_t *stride) {
+int prepare_extract(srs_ctx *ctx, uint64_t ntiles, uint64_t nb, bool one_tile_buckets, hipStream_t st, uint32_t *stride) {
     *stride = ticket_stride_for(nb);
     const uint64_t words = nb * (*stride);
     if (words > ctx->tickets_cap) {
@@ -112,29 +126,19 @@ int prepare_extract(srs_ctx *ctx, uint64_t ntiles, uint64_t nb, hipStream_t st, 
         SRS_HIP(hipMalloc((void **)&ctx->status, cap * sizeof(unsigned long long)));
         ctx->status_cap = cap;
     }
-    const uint64_t n = ntiles > nb ? ntiles : nb;
-    const uint32_t threads = 256;
-    hipLaunchKernelGGL(prepare_extract_kernel, dim3((uint32_t)((n + threads - 1) / threads)), dim3(threads), 0, st,
-                       ctx->tickets, nb, *stride, ctx->status, ntiles);
-    SRS_HIP(hipGetLastError());
-    return SRS_OK;
+    return clear_extract_scratch(ctx->tickets, nb, *stride, ctx->status, ntiles, one_tile_buckets, st);
 }
 
 // The same on the static scratch: nothing is allocated, sizes beyond the array are refused.  Ticket counters sit
 // 256 bytes apart while they fit, 4 bytes apart above that.
-int prepare_extract_static(srs_ctx *ctx, uint64_t ntiles, uint64_t nb, hipStream_t st, uint32_t *stride,
+int prepare_extract_static(srs_ctx *ctx, uint64_t ntiles, uint64_t nb, bool one_tile_buckets, hipStream_t st, uint32_t *stride,
                            unsigned long long **status, uint32_t **tickets) {
     if (!ctx->static_scratch) return SRS_ERR_HIP;
     if (ntiles > kStaticTiles || nb > kStaticTicketWords) return SRS_ERR_TOO_LARGE;
     *stride = (nb * 64u <= kStaticTicketWords) ? 64u : 1u;
     *status = reinterpret_cast<unsigned long long *>(ctx->static_scratch);
     *tickets = reinterpret_cast<uint32_t *>(ctx->static_scratch + kStaticTiles * sizeof(unsigned long long));
-    const uint64_t n = ntiles > nb ? ntiles : nb;
-    const uint32_t threads = 256;
-    hipLaunchKernelGGL(prepare_extract_kernel, dim3((uint32_t)((n + threads - 1) / threads)), dim3(threads), 0, st,
-                       *tickets, nb, *stride, *status, ntiles);
-    SRS_HIP(hipGetLastError());
-    return SRS_OK;
+    return clear_extract_scratch(*tickets, nb, *stride, *status, ntiles, one_tile_buckets, st);
 }
 
 // One-byte elements: a tile of tile_elems elements is V = tile_elems / 4096 vectors per lane (16 elements each), so
@@ -405,6 +409,31 @@ int launch_second_pass(const srs_ctx *ctx, const srs_plan *plan, const ExtractAr
     return SRS_OK;
 }
 
+uint64_t single_tiles(uint64_t n, uint64_t be, uint64_t tile) {
+    const uint64_t full = (n - 1) / be;                   // buckets before the last
+    return full * ((be + tile - 1) / tile) + (n - full * be + tile - 1) / tile;
+}
+
+// Elements per tile of a single tensor for which the caller chose none.  The largest tile streams best, but leaves CUs
+// idle where there are fewer tiles than CUs, and its serial part (16 vectors ranked per lane) is what small calls
+// consist of: the smallest tile that makes no more than one per CU is taken.  A tile that holds whole buckets goes before
+// it up to half the largest, as it saves the launch that clears tickets and status words.
+// Extract at 1 % changed with its clearing launch, refreshed in place, tiles of 4096 / 8192 / 16384 / 32768, us:
+// 4 K elements 5.5 / 5.8 / 7.0 / 8.3, 64 K in one bucket 7.0 / 7.7 / 9.6 / 13.5, 1 M in four 8.4 / 8.5 / 10.3 / 14.6,
+// 4 M in four 15.4 / 12.5 / 11.4 / 15.1, 16 M in four 43.9 / 34.9 / 28.6 / 25.6, 256 M in one 794 / 440 / 317 / 273.
+constexpr uint64_t kFewTiles = 256;
+
+uint32_t single_tile_elems(const srs_ctx *ctx, uint64_t n, uint64_t be, int eb) {
+    if (ctx->tile_set) return ctx->tile_elems;
+    uint32_t best = 0;
+    for (uint32_t tile = (eb == 1) ? 8192u : 4096u; tile < ctx->tile_elems; tile *= 2) {
+        if (single_tiles(n, be, tile) > kFewTiles) continue;
+        if (be <= tile || n <= tile) return tile;
+        if (!best) best = tile;
+    }
+    return best ? best : ctx->tile_elems;
+}
+
 int extract_single(srs_ctx *ctx, void *old_snapshot, const void *new_w, uint64_t n, uint64_t bucket_elems,
                    int32_t *I, void *V, uint32_t *counts, uint64_t cap, void *stream, bool cast, int eb = 2,
                    bool static_scratch = false) {
@@ -419,11 +448,11 @@ int extract_single(srs_ctx *ctx, void *old_snapshot, const void *new_w, uint64_t
     hipStream_t st = (hipStream_t)stream;
     SRS_ON_DEVICE(ctx->device);
 
-    const uint64_t T = ctx->tile_elems;
+    const uint64_t T = single_tile_elems(ctx, n, bucket_elems, eb);
     const uint64_t nb = (n + bucket_elems - 1) / bucket_elems;
     const uint64_t tpb = (bucket_elems + T - 1) / T;
     const uint64_t last_len = n - (nb - 1) * bucket_elems;
-    const uint64_t ntiles = (nb - 1) * tpb + (last_len + T - 1) / T;
+    const uint64_t ntiles = single_tiles(n, bucket_elems, T);
     if (ntiles > 0x7fffffffull) return SRS_ERR_INVALID;
 
     if (nb > 0x7fffffffull) return SRS_ERR_INVALID;
@@ -433,8 +462,8 @@ int extract_single(srs_ctx *ctx, void *old_snapshot, const void *new_w, uint64_t
 
     ExtractArgs a;
     std::memset(&a, 0, sizeof(a));
-    int rc = static_scratch ? prepare_extract_static(ctx, ntiles, nb, st, &a.ticket_stride, &a.status, &a.tickets)
-                            : prepare_extract(ctx, ntiles, nb, st, &a.ticket_stride);
+    int rc = static_scratch ? prepare_extract_static(ctx, ntiles, nb, ntiles == nb, st, &a.ticket_stride, &a.status, &a.tickets)
+                            : prepare_extract(ctx, ntiles, nb, ntiles == nb, st, &a.ticket_stride);
     if (rc != SRS_OK) return rc;
     if (!static_scratch) { a.status = ctx->status; a.tickets = ctx->tickets; }
     a.old_w = (uint16_t *)old_snapshot; a.new_w = new_w; a.n = n;
@@ -444,9 +473,9 @@ int extract_single(srs_ctx *ctx, void *old_snapshot, const void *new_w, uint64_t
     a.I = I; a.V = (uint16_t *)V; a.counts = counts; a.cap = cap;
     a.flags = ctx->flags;
     a.spin_limit = ctx->spin_limit;
-    rc = launch_extract<false>(ctx, ctx->tile_elems, a, st, cast ? kSrcFp32 : kSrcBf16, eb);
+    rc = launch_extract<false>(ctx, (uint32_t)T, a, st, cast ? kSrcFp32 : kSrcBf16, eb);
     if (rc != SRS_OK || !second_pass) return rc;
-    return launch_second_pass<false>(ctx, nullptr, a, bucket_elems, ctx->tile_elems, eb, st);
+    return launch_second_pass<false>(ctx, nullptr, a, bucket_elems, (uint32_t)T, eb, st);
 }
 }  // namespace
 
@@ -473,7 +502,7 @@ int extract_multi(srs_ctx *ctx, srs_plan *plan, const srs_tensor_pair *t,
 
     ExtractArgs a;
     std::memset(&a, 0, sizeof(a));
-    int rc = prepare_extract(ctx, plan->ntiles, plan->nbuckets, st, &a.ticket_stride);
+    int rc = prepare_extract(ctx, plan->ntiles, plan->nbuckets, plan->max_bucket_tiles == 1, st, &a.ticket_stride);
     if (rc != SRS_OK) return rc;
     a.tiles = plan->d_tiles; a.ptrs = plan->d_pairs; a.ntiles = plan->ntiles;
     a.wg_info = plan->d_wg_info; a.bucket_first = plan->d_bucket_first; a.nb = plan->nbuckets;
@@ -549,7 +578,7 @@ int srs_set_option(srs_ctx *ctx, int option, uint64_t value) {
             ctx->spin_limit = (uint32_t)value; return SRS_OK;
         case SRS_OPT_TILE_ELEMS:
             if (!valid_tile_elems(value)) return SRS_ERR_INVALID;
-            ctx->tile_elems = (uint32_t)value; return SRS_OK;
+            ctx->tile_elems = (uint32_t)value; ctx->tile_set = true; return SRS_OK;
         case SRS_OPT_REFRESH_GROUP:
             if (value != 0 && value != 8) return SRS_ERR_INVALID;
             ctx->refresh_group = (uint32_t)value; return SRS_OK;

@@ -434,12 +434,16 @@ __global__ __launch_bounds__(kThreads, (V >= 16 && SRC == kSrcBf16) ? 3 : 1) voi
         first_tile = bucket * a.tiles_per_bucket;
         bucket_tiles = (bucket == a.nb - 1) ? a.last_tiles : a.tiles_per_bucket;
     }
-    if (tid == 0)
-        s_ticket = __hip_atomic_fetch_add(a.tickets + (uint64_t)bucket * a.ticket_stride, 1u, __ATOMIC_RELAXED,
-                                          __HIP_MEMORY_SCOPE_AGENT);
-    __syncthreads();
-    const uint32_t k = uniform(s_ticket);
-    if (k >= bucket_tiles) return;         // cannot happen: each bucket is served by exactly bucket_tiles workgroups
+    // a bucket of one tile needs neither ticket nor status word (where all are, the host does not clear them either)
+    uint32_t k = 0;
+    if (bucket_tiles > 1) {                // uniform
+        if (tid == 0)
+            s_ticket = __hip_atomic_fetch_add(a.tickets + (uint64_t)bucket * a.ticket_stride, 1u, __ATOMIC_RELAXED,
+                                              __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        k = uniform(s_ticket);
+        if (k >= bucket_tiles) return;     // cannot happen: each bucket is served by exactly bucket_tiles workgroups
+    }
     const uint32_t tile = first_tile + k;
     const bool last = (k == bucket_tiles - 1);
 
@@ -607,7 +611,7 @@ __global__ __launch_bounds__(kThreads, (V >= 16 && SRC == kSrcBf16) ? 3 : 1) voi
     if (wave == 0) {
         uint32_t excl = 0;
         if (tile == first_tile) {
-            if (lane == 0) status_store(a.status + tile, status_word(kStPrefix, tile_total));
+            if (lane == 0 && !last) status_store(a.status + tile, status_word(kStPrefix, tile_total));
         } else {
             if (lane == 0) status_store(a.status + tile, status_word(kStAgg, tile_total));
             excl = look_back(a, tile, first_tile, lane);
@@ -733,12 +737,15 @@ __global__ __launch_bounds__(kThreads) void extract_marked_kernel(const ExtractA
     // ---- bucket, ticket, tile: as in extract_kernel (tensor lists only)
     const WgInfo wi = a.wg_info[blockIdx.x];
     const uint32_t bucket = wi.bucket, first_tile = wi.first_tile, bucket_tiles = wi.ntiles;
-    if (tid == 0)
-        s_ticket = __hip_atomic_fetch_add(a.tickets + (uint64_t)bucket * a.ticket_stride, 1u, __ATOMIC_RELAXED,
-                                          __HIP_MEMORY_SCOPE_AGENT);
-    __syncthreads();
-    const uint32_t k = uniform(s_ticket);
-    if (k >= bucket_tiles) return;
+    uint32_t k = 0;
+    if (bucket_tiles > 1) {
+        if (tid == 0)
+            s_ticket = __hip_atomic_fetch_add(a.tickets + (uint64_t)bucket * a.ticket_stride, 1u, __ATOMIC_RELAXED,
+                                              __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        k = uniform(s_ticket);
+        if (k >= bucket_tiles) return;
+    }
     const uint32_t tile = first_tile + k;
     const bool last = (k == bucket_tiles - 1);
     const TileDesc d = a.tiles[tile];
@@ -775,7 +782,7 @@ __global__ __launch_bounds__(kThreads) void extract_marked_kernel(const ExtractA
     if (wave == 0) {
         uint32_t excl = 0;
         if (tile == first_tile) {
-            if (lane == 0) status_store(a.status + tile, status_word(kStPrefix, tile_total));
+            if (lane == 0 && !last) status_store(a.status + tile, status_word(kStPrefix, tile_total));
         } else {
             if (lane == 0) status_store(a.status + tile, status_word(kStAgg, tile_total));
             excl = look_back(a, tile, first_tile, lane);
