@@ -849,9 +849,14 @@ __global__ __launch_bounds__(kThreads) void extract_marked_kernel(const ExtractA
 // the incomplete ones in front and behind, which are read (and with CAST written back) element by element.  300 odd-sized
 // tensors end to end, the buffers two bytes off (108 M elements, 1 % changed, two steps marked and extracted): 605 us when
 // every vector of such a tile was read element by element, 208 us now.
+// The bits are gathered in LDS first, so that the bitmap sees one coalesced atomic per 256 bytes of it and wave instead of one
+// per vector that holds a change: two steps of 1.2 G elements marked and extracted, 0.6 % changed 2.06 -> 2.01 ms, 5 %
+// 3.58 -> 2.36 ms, 0.1 % 1.82 ms as before.
 template <int V, bool CAST>
 __global__ __launch_bounds__(kThreads) void mark_kernel(const ExtractArgs a) {
     constexpr uint32_t TILE = (uint32_t)V * kUnit;
+    constexpr uint32_t kWords = TILE / 32 + 4;           // 32 + 31 + TILE + 7 bits and the word that a last vector may spill into
+    __shared__ uint32_t s_bits[kWords];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     if (blockIdx.x >= a.ntiles) return;
     const TileDesc d = a.tiles[blockIdx.x];
@@ -865,9 +870,11 @@ __global__ __launch_bounds__(kThreads) void mark_kernel(const ExtractArgs a) {
     const gptr<uint16_t> og = po - h;
     const gptr<const uint32_t> fg = (gptr<const uint32_t>)p.new_w + d.tensor_off - h;
     const gptr<const uint16_t> ng = (gptr<const uint16_t>)p.new_w + d.tensor_off - h;
-    // packed position of grid position 0: below zero where the list begins off a 16-byte boundary, and then only for
-    // elements that do not exist
-    const int64_t p0 = (int64_t)(a.tensor_base[d.tensor] + d.tensor_off) - (int64_t)h;
+    // word 0 of s_bits is the one before the word of the tile's first element: grid positions below h are in front of it
+    const uint64_t pos = a.tensor_base[d.tensor] + d.tensor_off;        // packed position of the tile's first element
+    const uint32_t bit0 = 32u + (uint32_t)(pos & 31u) - h;              // bit of grid position 0 in s_bits
+    for (uint32_t i = tid; i < kWords; i += kThreads) s_bits[i] = 0;
+    __syncthreads();
     const bool in_head = h != 0 && tid == 0;
     u32x4 xo[V], xn[V];
     // two versions that are only compared are read once each: non-temporal (2 % faster); with CAST the parameters are
@@ -891,12 +898,9 @@ __global__ __launch_bounds__(kThreads) void mark_kernel(const ExtractArgs a) {
         }
     }
     auto mark = [&](uint32_t g, uint32_t m) {                           // bit k of m: grid position g + k changed
-        const int64_t at = p0 + g;
-        const uint32_t sh = (uint32_t)at & 31u;
-        uint32_t *const w = a.bitmap + (at >> 5);
-        if (m << sh) atomicOr(w, m << sh);
-        const uint32_t spill = (sh > 24u) ? (m >> (32u - sh)) : 0u;     // bits that belong to the next word
-        if (spill) atomicOr(w + 1, spill);
+        const uint32_t at = bit0 + g, sh = at & 31u;
+        atomicOr(&s_bits[at >> 5], m << sh);
+        if (sh > 24u) atomicOr(&s_bits[(at >> 5) + 1], m >> (32u - sh));
     };
     const bool has_tail = glen > nbody;                                 // uniform
     if (h != 0 || has_tail) {
@@ -924,6 +928,12 @@ __global__ __launch_bounds__(kThreads) void mark_kernel(const ExtractArgs a) {
 #pragma unroll
     for (int j = 0; j < V; ++j)
         if (m[j]) mark(g0 + j * 512, m[j]);
+    __syncthreads();
+    uint32_t *const w = a.bitmap + (pos >> 5);
+    for (uint32_t i = tid; i + 1 < kWords; i += kThreads) {
+        const uint32_t x = s_bits[i + 1];
+        if (x) atomicOr(w + i, x);                                      // bits are set for elements that exist only
+    }
 }
 
 // ---------------------------------------------------------------------------------------------
