@@ -118,8 +118,10 @@ def version() -> int:
 
 
 def _stream_ptr(stream: Optional[torch.cuda.Stream]) -> int:
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return int(s.cuda_stream)
+    if stream is not None:
+        return int(stream.cuda_stream)
+    # the handle of torch.cuda.current_stream() without the Stream object around it, whose making took 2.9 us of each call's 8
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _dev16(t: torch.Tensor, what: str, width: int = 2) -> None:
