@@ -968,8 +968,6 @@ int srs_apply_encoded(srs_ctx *ctx, void *weights, uint64_t n, uint64_t bucket_e
     const dim3 grid((uint32_t)(nb * cpb));
     hipLaunchKernelGGL((apply_encoded_kernel<false>), grid, dim3(kThreads), 0, st, a);
     SRS_HIP(hipGetLastError());
-    hipLaunchKernelGGL((apply_kernel<false>), grid, dim3(kThreads), 0, st, a);      // buckets that kept 32-bit indices
-    SRS_HIP(hipGetLastError());
     return SRS_OK;
 }
 
@@ -994,8 +992,6 @@ int srs_apply_multi_encoded(srs_ctx *ctx, srs_plan *plan, const srs_tensor *t, c
     a.D = D; a.max_gap = max_gap; a.anchors = anchors; a.base_stride = 0;
     const dim3 grid((uint32_t)((uint64_t)plan->nbuckets * cpb));
     hipLaunchKernelGGL((apply_encoded_kernel<true>), grid, dim3(kThreads), 0, st, a);
-    SRS_HIP(hipGetLastError());
-    hipLaunchKernelGGL((apply_kernel<true>), grid, dim3(kThreads), 0, st, a);
     SRS_HIP(hipGetLastError());
     return SRS_OK;
 }

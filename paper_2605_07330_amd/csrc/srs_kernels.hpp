@@ -109,7 +109,7 @@ struct ApplyArgs {
     // pointers to skip between two entries of wptrs: 0 for the apply-side table, 1 when wptrs is the extract-side
     // table of PtrPair read through its old_w members (the second-pass snapshot refresh)
     uint32_t wptr_skip;
-    // 16-bit index coding (null / 0 when the payload carries 32-bit indices only)
+    // 16-bit index coding (null / 0 for apply_kernel, whose payload carries 32-bit indices only)
     const uint16_t *D; const uint32_t *max_gap; const int32_t *anchors; uint64_t base_stride;
 };
 
@@ -1111,8 +1111,7 @@ __device__ __forceinline__ void scatter_pairs(const ApplyArgs &a, ApplyShared &s
     if (bad) atomicOr(a.flags, kFlagBadIndex);
 }
 
-// 32-bit indices.  When a.max_gap is given, buckets whose indices travel as 16-bit differences are
-// left to apply_encoded_kernel.
+// 32-bit indices
 template <bool MULTI, int EB>
 __device__ __forceinline__ void apply_pairs(const ApplyArgs &a, ApplyShared &sh, uint32_t b, uint64_t start, uint32_t nvalid) {
     typedef typename Elem<EB>::type T;
@@ -1138,7 +1137,6 @@ __global__ __launch_bounds__(kThreads) void apply_kernel(const ApplyArgs a) {
     uint32_t b; uint64_t start;
     const uint32_t nvalid = apply_chunk(a, b, start);
     if (nvalid == 0) return;
-    if (a.max_gap && a.max_gap[b] < kWideGap) return;
     apply_pairs<MULTI, EB>(a, sh, b, start, nvalid);
 }
 
@@ -1194,7 +1192,9 @@ __global__ __launch_bounds__(kThreads) void tensor_view_kernel(const ApplyArgs a
 // the running sums into positions inside the bucket.  The positions then change hands through LDS so that
 // thread t scatters pairs t, t+256, ...: one store instruction of a wave covers 64 consecutive pairs (about 13 KB
 // of weights at 1 % density) as in apply_kernel, not every eighth pair of 512 (100 KB), which takes the memory
-// side half as long again (12.4 against 8.2 ms on the 910-bucket benchmark set).
+// side half as long again (12.4 against 8.2 ms on the 910-bucket benchmark set).  Buckets with differences that do not fit
+// are scattered from their 32-bit indices by the same launch (by a second one before: values of 64 buckets of 335 k pairs
+// decoded and applied 777 us, 770 now; of one bucket of 2.6 k pairs 28.6 / 27.2)
 template <bool MULTI>
 __global__ __launch_bounds__(kThreads) void apply_encoded_kernel(const ApplyArgs a) {
     __shared__ ApplyShared sh;
@@ -1202,7 +1202,10 @@ __global__ __launch_bounds__(kThreads) void apply_encoded_kernel(const ApplyArgs
     uint32_t b; uint64_t start;
     const uint32_t nvalid = apply_chunk(a, b, start);
     if (nvalid == 0) return;
-    if (a.max_gap[b] >= kWideGap) return;           // this bucket travels with 32-bit indices
+    if (a.max_gap[b] >= kWideGap) {                 // uniform: this bucket travels with 32-bit indices
+        apply_pairs<MULTI, 2>(a, sh, b, start, nvalid);
+        return;
+    }
     const uint16_t *const Db = a.D + (uint64_t)b * a.cap + start;
     const uint16_t *const Vb = a.V + (uint64_t)b * a.cap + start;
     const uint32_t k0 = threadIdx.x * kApplyPer;
