@@ -1,0 +1,43 @@
+"""What the compiler makes of kernels whose speed hangs on it: the listing of the library's own sources (CPU only)."""
+import re
+import subprocess
+
+import pytest
+
+from paper_2605_07330_amd import build
+
+
+@pytest.fixture(scope="module")
+def kernels(tmp_path_factory):
+    """Demangled name -> listing of each kernel."""
+    out = str(tmp_path_factory.mktemp("listing") / "srs.s")
+    cmd = [a for a in build.hipcc_command(out) if a not in ("-shared", "-fPIC") and not a.startswith("-Wl,")]
+    subprocess.run([*cmd, "--cuda-device-only", "-S"], check=True, stderr=subprocess.DEVNULL)
+    parts = re.split(r"^(_Z\w+):[^\n]*; @", open(out).read(), flags=re.M)
+    names = subprocess.run(["c++filt"], input="\n".join(parts[1::2]), capture_output=True, text=True, check=True).stdout.split("\n")
+    return {n.removeprefix("void srs::").split("(")[0]: body for n, body in zip(names, parts[2::2])}
+
+
+def load_runs(body, least):
+    """Base operands of each run of at least `least` 16-byte loads that no branch, label or barrier interrupts."""
+    runs, run = [], []
+    for line in body.split("\n"):
+        line = line.strip()
+        m = re.match(r"global_load_dwordx4 v\[\d+:\d+\], \S+, (s\[\d+:\d+\]|off)", line)
+        if m:
+            run.append(m.group(1))
+        elif re.match(r"(s_cbranch|s_branch|s_barrier|\.LBB|s_endpgm)", line):
+            if len(run) >= least:
+                runs.append(run)
+            run = []
+    return runs
+
+
+@pytest.mark.parametrize("name,vectors", [("extract_kernel<16, true, -1, 0, 2>", 16), ("extract_kernel<16, false, -1, 0, 2>", 16),
+                                          ("extract_kernel<8, true, -1, 0, 1>", 8), ("extract_kernel<8, false, -1, 0, 1>", 8)])
+def test_one_stream_after_the_other(kernels, name, vectors):
+    """A whole tile whose snapshot is left alone: all loads of one stream go out before the first of the other."""
+    runs = load_runs(kernels[name], vectors)
+    assert sum(map(len, runs)) >= 2 * vectors, runs
+    for run in runs:
+        assert sum(a != b for a, b in zip(run, run[1:])) <= 1, f"{name}: the streams alternate: {run}"
