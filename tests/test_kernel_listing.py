@@ -41,3 +41,10 @@ def test_one_stream_after_the_other(kernels, name, vectors):
     assert sum(map(len, runs)) >= 2 * vectors, runs
     for run in runs:
         assert sum(a != b for a, b in zip(run, run[1:])) <= 1, f"{name}: the streams alternate: {run}"
+
+
+@pytest.mark.parametrize("name,waves", [("extract_kernel<8, false, 0, 1, 2>", 4), ("extract_kernel<8, false, 8, 1, 2>", 4),
+                                        ("extract_kernel<16, true, 8, 1, 2>", 2), ("extract_kernel<16, false, 0, 1, 2>", 2)])
+def test_resident_waves_of_the_cast(kernels, name, waves):
+    """The path of incomplete tiles must not take registers from the path of whole ones."""
+    assert int(re.search(r"; Occupancy: (\d+)", kernels[name]).group(1)) >= waves
