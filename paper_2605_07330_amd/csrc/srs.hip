@@ -364,19 +364,34 @@ uint64_t apply_chunks_per_bucket(uint64_t cap, uint64_t be) {
     return (slots + kApplyChunk - 1) / kApplyChunk;
 }
 
-// The scatter.  Every workgroup looks at its own chunk slot, live or not, unless there are more than kWalkGrid slots and
-// they are so large that most of them cannot be live (a capacity from an eighth of the bucket on; a third changed already
-// travels better whole): then a fixed grid walks the live chunks (the walk's bucket table holds kWalkBuckets buckets;
-// longer lists of buckets keep the slots).  Slots / walk, us, capacities of 1.25 times the density: six 30B-A3B-shaped
-// layers at 0.5 % 745 / 747, 2 % 2058 / 2101, 5 % 3070 / 3181, two skewed layers (capacity 1/16) 75.9 / 78.5; capacities of
-// the whole bucket: 67 M elements at 0.1 % 16.9 / 8.3, 419 M in one bucket 89 / 22.6.
+// The scatter: a workgroup per chunk slot, live or not, unless the slots hold whole buckets and there are many of them; then
+// kDirectSlots of them keep a workgroup each and the rest are grouped (apply_grouped_kernel).  Where the lines lie:
+// - A capacity below the bucket was sized by a density, most slots are live, and looping over chunks only loses: grouped from
+//   half a bucket on, slots of half the bucket take 2-14 % longer from 20 to 30 % changed, from a quarter on up to 6 % at 20 %.
+// - Up to 8192 slots, the empty ones hide behind the live ones' stores.  In buckets of fewer than 16 chunks one round of
+//   direct slots is a large part of them, and the order of the live ones suffers: buckets of 8 chunks at 1 % 7 % slower.
+// - The groups grow with the slots left for them, so that a well-filled payload still makes several rounds of workgroups.
+// A workgroup per slot / grouped, whole-bucket slots, us: 400 M elements in one bucket at 0.05 % 84.6 / 13.5, 0.5 % 91 / 82,
+// 2 % 277 / 217, 10 % 417 / 350; 67 M in 64 buckets at 0.05 % 16.0 / 7.2, 2 % 36.7 / 36.7, 10 % 64.7 / 60.5; four
+// 30B-A3B-shaped layers at 0.1 % 531 / 145, 1 % 1250 / 755, 5 % 2554 / 2094; 300 odd-sized tensors at 0.1 % 25.2 / 9.1,
+// 1 % 39.7 / 39.3, 5 % 98 / 84.  Slower only where so much of a large single tensor has changed that it travels better whole:
+// by up to 5 % at 30 %, up to 20 % from about half on.
+constexpr uint64_t kGroupedSlots = 8192, kGroupedChunks = 16, kDirectSlots = 4096;
+
 template <bool MULTI, int EB>
-int launch_apply(const ApplyArgs &a, hipStream_t st) {
+int launch_apply(ApplyArgs a, hipStream_t st) {
     const uint64_t slots = (uint64_t)a.nb * a.chunks_per_bucket;
-    if (slots > kWalkGrid && a.nb <= kWalkBuckets && a.cap >= a.be / 8)
-        hipLaunchKernelGGL((apply_walk_kernel<MULTI, EB>), dim3(kWalkGrid), dim3(kThreads), 0, st, a);
-    else
+    if (slots > kGroupedSlots && a.chunks_per_bucket >= kGroupedChunks && a.cap >= a.be) {
+        const uint64_t spread = (kDirectSlots + a.nb - 1) / a.nb, half = ((uint64_t)a.chunks_per_bucket + 1) / 2;
+        a.direct = (uint32_t)(spread < half ? spread : half);
+        const uint32_t rest = a.chunks_per_bucket - a.direct;
+        const uint64_t left = (uint64_t)rest * a.nb;
+        a.group = left < 24576 ? 2 : left < 49152 ? 4 : 8;
+        const uint32_t grid = a.nb * (a.direct + (rest + a.group - 1) / a.group);          // at most the number of slots
+        hipLaunchKernelGGL((apply_grouped_kernel<MULTI, EB>), dim3(grid), dim3(kThreads), 0, st, a);
+    } else {
         hipLaunchKernelGGL((apply_kernel<MULTI, EB>), dim3((uint32_t)slots), dim3(kThreads), 0, st, a);
+    }
     SRS_HIP(hipGetLastError());
     return SRS_OK;
 }

@@ -109,6 +109,8 @@ struct ApplyArgs {
     // pointers to skip between two entries of wptrs: 0 for the apply-side table, 1 when wptrs is the extract-side
     // table of PtrPair read through its old_w members (the second-pass snapshot refresh)
     uint32_t wptr_skip;
+    // apply_grouped_kernel: chunks of each bucket that have a workgroup of their own, chunks per workgroup behind them
+    uint32_t direct, group;
     // 16-bit index coding (null / 0 for apply_kernel, whose payload carries 32-bit indices only)
     const uint16_t *D; const uint32_t *max_gap; const int32_t *anchors; uint64_t base_stride;
 };
@@ -990,8 +992,8 @@ struct ApplyShared {
 // nothing lost on the 244-bucket sets, 0.16 ms lost on the skewed set.
 constexpr uint32_t kApplyInterleave = 1024;
 
-__device__ __forceinline__ uint32_t apply_chunk(const ApplyArgs &a, uint32_t &b, uint64_t &start) {
-    const uint32_t per_group = kApplyInterleave * a.chunks_per_bucket;
+__device__ __forceinline__ uint32_t apply_chunk(const ApplyArgs &a, uint32_t per_bucket, uint32_t &b, uint64_t &start) {
+    const uint32_t per_group = kApplyInterleave * per_bucket;
     const uint32_t g = blockIdx.x / per_group, j = blockIdx.x - g * per_group;
     const uint32_t g0 = g * kApplyInterleave;
     if (g0 >= a.nb) return 0;
@@ -1006,78 +1008,15 @@ __device__ __forceinline__ uint32_t apply_chunk(const ApplyArgs &a, uint32_t &b,
     return (uint32_t)((cnt - start < kApplyChunk) ? (cnt - start) : kApplyChunk);
 }
 
-// Walk over the LIVE chunks only, for payloads whose slots are much larger than what they hold (a caller that does not
-// know the density makes cap = bucket_elems; skewed updates leave most buckets nearly empty).  A workgroup of the
-// direct mapping above that finds nothing costs 0.4-0.5 ns of the launch, which then bounds it: 89 us for 419 k pairs in
-// one bucket of 419 M slots.  Here a fixed grid of workgroups each scans the bucket counts once (nb <= kWalkBuckets: 16
-// bytes per thread, two barriers) and then takes every gridDim.x-th live chunk.  Chunk numbers run over kWalkRows
-// distant places of the payload in turn, which keeps the scatter of the moment spread over the weight set whatever the
-// distribution over the buckets.  Apply, direct mapping / walk, us: that bucket 89 / 22.6; two layers of the 8B-shaped set
-// at 0.1 % in full slots 85 / 21; 67 M elements at 0.1 % in 64 full buckets 16.9 / 8.3.  Where most slots are
-// live the direct mapping is up to 4 % faster and stays.
-constexpr uint32_t kWalkBuckets = 1024;
-constexpr uint32_t kWalkRows = 1024;
-constexpr uint32_t kWalkGrid = 2048;       // 8 workgroups of 4 waves on each of 256 CUs
-
-struct ChunkWalk {
-    uint32_t first[kWalkBuckets + 1];      // live chunks before each bucket
-    uint32_t wave_total[kWaves];
-};
-
-// fills w.first and returns the number of live chunks; all threads of the workgroup call it
-__device__ __forceinline__ uint32_t walk_begin(const ApplyArgs &a, ChunkWalk &w) {
-    constexpr uint32_t kPer = kWalkBuckets / kThreads;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const uint32_t b0 = threadIdx.x * kPer;
-    uint32_t n[kPer], mine = 0;
-#pragma unroll
-    for (uint32_t q = 0; q < kPer; ++q) {
-        const uint32_t cnt_true = (b0 + q < a.nb) ? a.counts[b0 + q] : 0u;
-        const uint64_t cnt = ((uint64_t)cnt_true < a.cap) ? cnt_true : a.cap;
-        n[q] = (uint32_t)((cnt + kApplyChunk - 1) / kApplyChunk);
-    }
-#pragma unroll
-    for (uint32_t q = 0; q < kPer; ++q) mine += n[q];
-    const uint32_t inc = wave_inclusive_scan(mine);
-    if (lane == 63) w.wave_total[wave] = inc;
-    __syncthreads();
-    uint32_t at = inc - mine, total = 0;
-#pragma unroll
-    for (int v = 0; v < kWaves; ++v) { at += (v < wave) ? w.wave_total[v] : 0u; total += w.wave_total[v]; }
-#pragma unroll
-    for (uint32_t q = 0; q < kPer; ++q) { w.first[b0 + q] = at; at += n[q]; }
-    if (threadIdx.x == kThreads - 1) w.first[kWalkBuckets] = at;
-    __syncthreads();
-    return total;
-}
-
-// the i-th chunk of the walk (i < kWalkRows * ceil(total / kWalkRows)); 0 pairs where the grid of rows has no chunk
-__device__ __forceinline__ uint32_t walk_chunk(const ApplyArgs &a, const ChunkWalk &w, uint32_t total, uint32_t i,
-                                               uint32_t &b, uint64_t &start) {
-    const uint32_t per_row = (total + kWalkRows - 1) / kWalkRows;
-    const uint32_t id = (i % kWalkRows) * per_row + i / kWalkRows;
-    if (id >= total) return 0;
-    uint32_t lo = 0, hi = kWalkBuckets;                // first[lo] <= id < first[hi]
-    while (hi - lo > 1) {
-        const uint32_t mid = (lo + hi) >> 1;
-        if (w.first[mid] <= id) lo = mid; else hi = mid;
-    }
-    b = uniform(lo);
-    const uint32_t cnt_true = a.counts[b];
-    const uint64_t cnt = ((uint64_t)cnt_true < a.cap) ? cnt_true : a.cap;
-    start = (uint64_t)(id - w.first[lo]) * kApplyChunk;
-    if (start >= cnt) return 0;
-    return (uint32_t)((cnt - start < kApplyChunk) ? (cnt - start) : kApplyChunk);
-}
-
 // Scatter of one thread's kApplyPer pairs of bucket b; pair j is live when bit j of `live` is set.  The stores carry
 // the non-temporal hint: each lands in a line nothing else will touch soon, and measures 10 % faster that way.
 // idx holds tensor-flat indices (single tensor) or positions inside the bucket (lists).  For lists the
-// bucket's segment table is cached in LDS (start inside the bucket -> byte address of that element).
+// bucket's segment table is cached in LDS (start inside the bucket -> byte address of that element), and stays there for the
+// workgroup's next chunk of the same bucket (fill = false).
 template <bool MULTI, int EB = 2>
 __device__ __forceinline__ void scatter_pairs(const ApplyArgs &a, ApplyShared &sh, uint32_t b,
                                               const int32_t (&idx)[kApplyPer], const uint16_t (&val)[kApplyPer],
-                                              uint32_t live) {
+                                              uint32_t live, bool fill = true) {
     typedef typename Elem<EB>::type T;       // width of a stored value; val[] holds it zero-extended
     bool bad = false;
     if (MULTI) {
@@ -1086,7 +1025,7 @@ __device__ __forceinline__ void scatter_pairs(const ApplyArgs &a, ApplyShared &s
         const uint32_t s_lo = a.seg_begin[b], s_hi = a.seg_begin[b + 1];
         const uint32_t nseg = s_hi - s_lo;
         const bool cached = nseg <= kSegCache;                 // uniform
-        if (cached) {
+        if (cached && fill) {
             for (uint32_t s = threadIdx.x; s < nseg; s += kThreads) {
                 const SegDesc d = a.segs[s_lo + s];
                 sh.off[s] = d.bucket_off;
@@ -1144,7 +1083,8 @@ __device__ __forceinline__ void scatter_pairs(const ApplyArgs &a, ApplyShared &s
 
 // 32-bit indices
 template <bool MULTI, int EB>
-__device__ __forceinline__ void apply_pairs(const ApplyArgs &a, ApplyShared &sh, uint32_t b, uint64_t start, uint32_t nvalid) {
+__device__ __forceinline__ void apply_pairs(const ApplyArgs &a, ApplyShared &sh, uint32_t b, uint64_t start, uint32_t nvalid,
+                                            bool fill = true) {
     typedef typename Elem<EB>::type T;
     const int32_t *const Ib = a.I + (uint64_t)b * a.cap + start;
     const T *const Vb = reinterpret_cast<const T *>(a.V) + (uint64_t)b * a.cap + start;
@@ -1159,31 +1099,44 @@ __device__ __forceinline__ void apply_pairs(const ApplyArgs &a, ApplyShared &sh,
         val[j] = ok ? Vb[k] : (uint16_t)0;
         live |= ok ? (1u << j) : 0u;
     }
-    scatter_pairs<MULTI, EB>(a, sh, b, idx, val, live);
+    scatter_pairs<MULTI, EB>(a, sh, b, idx, val, live, fill);
 }
 
 template <bool MULTI, int EB = 2>
 __global__ __launch_bounds__(kThreads) void apply_kernel(const ApplyArgs a) {
     __shared__ ApplyShared sh;
     uint32_t b; uint64_t start;
-    const uint32_t nvalid = apply_chunk(a, b, start);
+    const uint32_t nvalid = apply_chunk(a, a.chunks_per_bucket, b, start);
     if (nvalid == 0) return;
     apply_pairs<MULTI, EB>(a, sh, b, start, nvalid);
 }
 
-// the same over the walk of live chunks
+// The same for payloads whose slots are as large as their buckets (a caller that does not know the density): nearly all
+// slots are empty then, and the workgroups that find nothing, 0.43 ns each, bound the launch (400 M slots in one bucket, 0.05 %
+// changed: 85 us, 13.5 here).  The first `direct` chunks of each bucket keep a workgroup of their own, in
+// apply_kernel's order; behind them a workgroup takes `group` chunks of one bucket in a row and fills the segment cache once.
 template <bool MULTI, int EB = 2>
-__global__ __launch_bounds__(kThreads) void apply_walk_kernel(const ApplyArgs a) {
+__global__ __launch_bounds__(kThreads) void apply_grouped_kernel(const ApplyArgs a) {
     __shared__ ApplyShared sh;
-    __shared__ ChunkWalk walk;
-    const uint32_t total = walk_begin(a, walk);
-    const uint32_t end = (total + kWalkRows - 1) / kWalkRows * kWalkRows;
-    for (uint32_t i = blockIdx.x; i < end; i += gridDim.x) {
-        uint32_t b; uint64_t start;
-        const uint32_t nvalid = walk_chunk(a, walk, total, i, b, start);
-        if (nvalid == 0) continue;
-        apply_pairs<MULTI, EB>(a, sh, b, start, nvalid);
-        if (MULTI) __syncthreads();                 // the segment cache is refilled for the next chunk
+    uint32_t b; uint64_t start;
+    const uint32_t singles = a.direct * a.nb;
+    if (blockIdx.x < singles) {
+        const uint32_t nvalid = apply_chunk(a, a.direct, b, start);
+        if (nvalid) apply_pairs<MULTI, EB>(a, sh, b, start, nvalid);
+        return;
+    }
+    const uint32_t t = blockIdx.x - singles, g = t / a.nb;
+    b = t - g * a.nb;
+    const uint32_t first = a.direct + g * a.group;
+    const uint32_t end = (first + a.group < a.chunks_per_bucket) ? first + a.group : a.chunks_per_bucket;
+    const uint32_t cnt_true = a.counts[b];
+    uint64_t stop = (uint64_t)end * kApplyChunk;
+    if ((uint64_t)cnt_true < stop) stop = cnt_true;
+    if (a.cap < stop) stop = a.cap;
+    start = (uint64_t)first * kApplyChunk;
+    for (bool fill = true; start < stop; start += kApplyChunk, fill = false) {
+        const uint64_t left = stop - start;
+        apply_pairs<MULTI, EB>(a, sh, b, start, (uint32_t)(left < kApplyChunk ? left : kApplyChunk), fill);
     }
 }
 
@@ -1192,7 +1145,7 @@ __global__ __launch_bounds__(kThreads) void apply_walk_kernel(const ApplyArgs a)
 // bucket.  tensor_id / tensor_idx are laid out like I.  Same workgroup-to-chunk mapping and segment search as apply.
 __global__ __launch_bounds__(kThreads) void tensor_view_kernel(const ApplyArgs a, uint32_t *tensor_id, int32_t *tensor_idx) {
     uint32_t b; uint64_t start;
-    const uint32_t nvalid = apply_chunk(a, b, start);
+    const uint32_t nvalid = apply_chunk(a, a.chunks_per_bucket, b, start);
     if (nvalid == 0) return;
     const uint64_t b0 = (uint64_t)b * a.be;
     const uint32_t blen = (uint32_t)((a.total - b0 < a.be) ? (a.total - b0) : a.be);
@@ -1231,7 +1184,7 @@ __global__ __launch_bounds__(kThreads) void apply_encoded_kernel(const ApplyArgs
     __shared__ ApplyShared sh;
     __shared__ int32_t s_pos[kApplyChunk + kApplyChunk / 8];    // pair k at k + k/8: both access patterns spread over the banks
     uint32_t b; uint64_t start;
-    const uint32_t nvalid = apply_chunk(a, b, start);
+    const uint32_t nvalid = apply_chunk(a, a.chunks_per_bucket, b, start);
     if (nvalid == 0) return;
     if (a.max_gap[b] >= kWideGap) {                 // uniform: this bucket travels with 32-bit indices
         apply_pairs<MULTI, 2>(a, sh, b, start, nvalid);
@@ -1292,7 +1245,7 @@ __global__ __launch_bounds__(kThreads) void encode_indices_kernel(const ApplyArg
                                                                   int32_t *anchors) {
     __shared__ uint32_t s_gap[kWaves];
     uint32_t b; uint64_t start;
-    const uint32_t nvalid = apply_chunk(a, b, start);
+    const uint32_t nvalid = apply_chunk(a, a.chunks_per_bucket, b, start);
     if (nvalid == 0) return;
     const int32_t *const Ib = a.I + (uint64_t)b * a.cap;
     const int64_t base = (int64_t)((uint64_t)b * a.base_stride);

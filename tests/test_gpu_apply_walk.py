@@ -1,6 +1,5 @@
-"""Apply over the walk of live chunks (payload slots well above 2048 chunks in all) against the oracle, tolerance 0: chunk
-counts around a row of the walk, empty and full buckets next to each other, the largest bucket table and one bucket more
-(which keeps the direct mapping), counts above cap, both element widths, single tensors and lists."""
+"""Apply of payloads with well above 2048 chunk slots, most of them empty, against the oracle, tolerance 0: few pairs, full
+buckets next to empty ones, 1024 buckets and one more, counts above cap, both element widths, single tensors and lists."""
 import numpy as np
 import pytest
 import torch
@@ -11,7 +10,7 @@ from util import from_u16, u16
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
-# (buckets, bucket_elems, cap, kind): slots = buckets * ceil(min(cap, bucket_elems) / 2048) decides the mapping
+# (buckets, bucket_elems, cap, kind): slots = buckets * ceil(min(cap, bucket_elems) / 2048)
 CASES = [(1, 4_300_000, 4_300_000, "few"), (3, 1_500_000, 1_500_000, "few"), (33, 140_000, 140_000, "ends"),
          (700, 6_000, 6_000, "skew"), (1024, 4_097, 4_097, "ends"), (1025, 4_097, 4_097, "ends"), (1024, 4_200, 5_000, "none"),
          (64, 70_000, 66_000, "over"), (2, 2_200_000, 2_200_000, "rows")]
@@ -29,7 +28,7 @@ def make_counts(nb, be, cap, kind, rng):
     elif kind == "over":
         c[:] = rng.integers(0, 4000, nb)
         c[5], c[-1] = be, 0
-    elif kind == "rows":                       # one chunk more than a whole number of rows
+    elif kind == "rows":                       # 1024 chunks and one more
         c[:] = [1024 * 2048, 1]
     return np.minimum(c, be)
 
