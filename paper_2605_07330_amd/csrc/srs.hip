@@ -440,7 +440,10 @@ uint64_t single_tiles(uint64_t n, uint64_t be, uint64_t tile) {
 // Extract at 1 % changed with its clearing launch, refreshed in place, tiles of 4096 / 8192 / 16384 / 32768, us:
 // 4 K elements 5.5 / 5.8 / 7.0 / 8.3, 64 K in one bucket 7.0 / 7.7 / 9.6 / 13.5, 1 M in four 8.4 / 8.5 / 10.3 / 14.6,
 // 4 M in four 15.4 / 12.5 / 11.4 / 15.1, 16 M in four 43.9 / 34.9 / 28.6 / 25.6, 256 M in one 794 / 440 / 317 / 273.
-constexpr uint64_t kFewTiles = 256;
+// One-byte elements: a tile takes half as long to read, and the chain of the tiles of one bucket shows from 192 on.  16384 /
+// 32768 for 4 M elements in one bucket (256 / 128 tiles), snapshot rotated, us: 0.03 % 10.5 / 10.0, 3 % 11.5 / 11.8; 8192 /
+// 16384 for 2 M (256 / 128): 9.8 / 8.4, 10.1 / 9.2; 16384 / 32768 for 3 M (192 / 96), refreshed in place: 9.9 / 10.3, 11.3 / 12.4.
+constexpr uint64_t kFewTiles = 256, kFewTilesU8 = 192;
 
 uint32_t single_tile_elems(const srs_ctx *ctx, uint64_t n, uint64_t be, int eb) {
     if (ctx->tile_set) return ctx->tile_elems;
@@ -448,7 +451,7 @@ uint32_t single_tile_elems(const srs_ctx *ctx, uint64_t n, uint64_t be, int eb) 
     for (uint32_t tile = (eb == 1) ? 8192u : 4096u; tile < ctx->tile_elems; tile *= 2) {
         if (single_tiles(n, be, tile) > kFewTiles) continue;
         if (be <= tile || n <= tile) return tile;
-        if (!best) best = tile;
+        if (!best && (eb == 2 || single_tiles(be < n ? be : n, be, tile) <= kFewTilesU8)) best = tile;
     }
     return best ? best : ctx->tile_elems;
 }
