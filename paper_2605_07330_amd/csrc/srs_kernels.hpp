@@ -1474,7 +1474,8 @@ __global__ __launch_bounds__(kThreads) void vc_hist_kernel(const ValueCodecArgs 
     // 240 buckets of 335 k values: 86 us with a 32-bit histogram per 8 lanes, 44 us now.
     constexpr uint32_t kParts = kThreads / 2, kPitch = 65;
     static_assert(kVcHistChunks * kVcChunk / kParts < 256u, "a byte holds every count of two threads");
-    static_assert(kParts * kPitch % (4 * kThreads) / 4 <= kThreads && kParts * kPitch % 4 == 0, "cleared in 16-byte stores");
+    static_assert(kParts * kPitch % 4 == 0, "cleared in 16-byte stores");
+    static_assert(kVcHistChunks * kVcChunk / kWaves < 65536u, "16 bits hold what a wave adds up");
     __shared__ __align__(16) uint32_t h[kParts * kPitch];
     __shared__ uint32_t s_sum[256];
     const uint32_t groups = (a.nchunk + kVcHistChunks - 1) / kVcHistChunks;
@@ -1548,8 +1549,8 @@ __global__ __launch_bounds__(kThreads) void vc_hist_kernel(const ValueCodecArgs 
 // path, and 15 us now.
 __device__ __forceinline__ uint32_t lane_value(uint32_t x, uint32_t lane) { return (uint32_t)__builtin_amdgcn_readlane((int)x, (int)lane); }
 
-template <int R>
 __device__ __forceinline__ void vc_merge(uint32_t used, const uint32_t *sorted_w, const uint8_t *sorted_s, int16_t *parent, int lane) {
+    constexpr int R = 4;                                     // 256 symbols, 64 lanes
     uint32_t leaf[R], node[R], leaf_up[R], node_up[R];       // weights; ids of the parents
 #pragma unroll
     for (int r = 0; r < R; ++r) {
@@ -1694,7 +1695,7 @@ __global__ __launch_bounds__(kThreads) void vc_build_kernel(const ValueCodecArgs
         }
         __syncthreads();
         if (wave == 0) {
-            vc_merge<4>(used, sorted_w, sorted_s, parent, lane);
+            vc_merge(used, sorted_w, sorted_s, parent, lane);
         }
         __syncthreads();
         l = 0;
