@@ -117,11 +117,17 @@ def version() -> int:
     return _lib.srs_version()
 
 
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream_ptr(stream: Optional[torch.cuda.Stream]) -> int:
     if stream is not None:
         return int(stream.cuda_stream)
-    # the handle of torch.cuda.current_stream() without the Stream object around it, whose making took 2.9 us of each call's 8
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    # the handle of torch.cuda.current_stream() without the Stream object around it, whose making took 2.9 us of each call's 8;
+    # torch does not promise this function
+    if _raw_stream is not None:
+        return _raw_stream(torch.cuda.current_device())
+    return int(torch.cuda.current_stream().cuda_stream)
 
 
 def _dev16(t: torch.Tensor, what: str, width: int = 2) -> None:
