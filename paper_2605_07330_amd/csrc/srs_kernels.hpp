@@ -685,6 +685,11 @@ __global__ __launch_bounds__(kThreads, (V >= 16 && SRC == kSrcBf16) ? 3 : 1) voi
                     if (RG == 0) po[local] = val;
                 }
                 ++r;
+                // 8 clocks between the pairs of the kernel that also rewrites lines: its stores then leave more evenly, as its
+                // loads do.  Refreshed by lines, without / with, us: two 32B-shaped layers at 10 % 1261 / 1272, 30 % 1746 /
+                // 1670, 50 % 2338 / 2261, 100 % 4278 / 4388; three 30B-A3B-shaped at 30 % 3005 / 2944.  (16 and 32 clocks
+                // gain more at 50 % and lose 1 to 2 % at 20 %.)
+                if (LINES) asm volatile("s_nop 7");
             }
         };
 #pragma unroll
