@@ -529,14 +529,15 @@ __global__ __launch_bounds__(kThreads, (V >= 16 && SRC == kSrcBf16) ? 3 : 1) voi
                     xo[j] = load16<H>(og + (j ? g0 + j * ROW : g_first));
                     __builtin_amdgcn_sched_barrier(0); __builtin_amdgcn_s_sleep(kLoadPace); __builtin_amdgcn_sched_barrier(0);
                 }
-            } else if (h == 0) {
+            } else if (EB == 2 && h == 0) {
                 // The kernel that writes nothing into weights reads one stream after the other.  The fence holds the
                 // scheduler to it: without it the two streams' loads alternate, which costs 1 to 6 %.  Tiles that start on
                 // a 16-byte boundary (uniform; all of an aligned list) get loads of their own without the choice of a
                 // first vector, worth up to 3 % more.  Rotated snapshot, one process, us: alternating / fence / fence
                 // and own loads: eight 32B-shaped layers at 0.2 % 2569 / 2462 / 2388, at 1 % 2756 / 2641 / 2560, four
                 // at 5 % with the second pass 3343 / 3278 / 3257; 8B-shaped set at 1 % 5954 / 5933 / 5923; single tensor
-                // of 300 M elements in odd buckets 259 / 251 / 244; one-byte elements the same within 1 %.
+                // of 300 M elements in odd buckets 259 / 251 / 244.  One-byte elements do without: there the same two
+                // changes gain up to 1 % on 30B-A3B-shaped sets and lose up to 2 % on 32B-shaped and 8B-shaped ones.
 #pragma unroll
                 for (int j = 0; j < V; ++j) xn[j] = load16_any<H>(ng + g0 + j * ROW);
                 __builtin_amdgcn_sched_barrier(0);
@@ -545,7 +546,7 @@ __global__ __launch_bounds__(kThreads, (V >= 16 && SRC == kSrcBf16) ? 3 : 1) voi
             } else {
 #pragma unroll
                 for (int j = 0; j < V; ++j) xn[j] = load16_any<H>(ng + (j ? g0 + j * ROW : g_first));
-                __builtin_amdgcn_sched_barrier(0);
+                if constexpr (EB == 2) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int j = 0; j < V; ++j) xo[j] = load16<H>(og + (j ? g0 + j * ROW : g_first));
             }

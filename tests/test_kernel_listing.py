@@ -33,8 +33,7 @@ def load_runs(body, least):
     return runs
 
 
-@pytest.mark.parametrize("name,vectors", [("extract_kernel<16, true, -1, 0, 2>", 16), ("extract_kernel<16, false, -1, 0, 2>", 16),
-                                          ("extract_kernel<8, true, -1, 0, 1>", 8), ("extract_kernel<8, false, -1, 0, 1>", 8)])
+@pytest.mark.parametrize("name,vectors", [("extract_kernel<16, true, -1, 0, 2>", 16), ("extract_kernel<16, false, -1, 0, 2>", 16)])
 def test_one_stream_after_the_other(kernels, name, vectors):
     """A whole tile whose snapshot is left alone: all loads of one stream go out before the first of the other."""
     runs = load_runs(kernels[name], vectors)
