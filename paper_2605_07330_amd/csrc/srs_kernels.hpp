@@ -387,8 +387,16 @@ __device__ __forceinline__ void refresh_lines(gptr<T> og, uint32_t g0, uint32_t 
 // source for the host code.)
 constexpr int kSrcBf16 = 0, kSrcFp32 = 1, kSrcBitmap = 2;
 
+// Waves per SIMD are demanded where the incomplete vectors' registers would cost the whole tiles one.  Lists of one-byte
+// elements in tiles of 16384, 6 or 7 waves / 8, us: five 32B-shaped layers in place at 0.5 % 1500 / 1448, rotated 1195 /
+// 1168, four 8B-shaped 508 / 499, three 30B-A3B-shaped 1151 / 1174.  (Single tensors, which take that tile by default, have
+// few workgroups and are 1 to 3 % faster without.)
+constexpr int waves_per_simd(int v, bool multi, int src, int eb) {
+    return (v >= 16 && src == kSrcBf16) ? 3 : (v == 4 && eb == 1 && multi) ? 8 : 1;
+}
+
 template <int V, bool MULTI, int RG, int SRC = kSrcBf16, int EB = 2>
-__global__ __launch_bounds__(kThreads, (V >= 16 && SRC == kSrcBf16) ? 3 : 1) void extract_kernel(const ExtractArgs a) {
+__global__ __launch_bounds__(kThreads, waves_per_simd(V, MULTI, SRC, EB)) void extract_kernel(const ExtractArgs a) {
     // A snapshot that is not written is read exactly once, like the new weights: both streams then carry the
     // non-temporal hint (measured 4 % faster).  With element-wise refresh the hint on either stream measures slower,
     // on the snapshot by 5 ms: 2-byte refresh stores must find their line still cached, hinted or not.

@@ -43,7 +43,8 @@ def test_one_stream_after_the_other(kernels, name, vectors):
 
 
 @pytest.mark.parametrize("name,waves", [("extract_kernel<8, false, 0, 1, 2>", 4), ("extract_kernel<8, false, 8, 1, 2>", 4),
-                                        ("extract_kernel<16, true, 8, 1, 2>", 2), ("extract_kernel<16, false, 0, 1, 2>", 2)])
-def test_resident_waves_of_the_cast(kernels, name, waves):
+                                        ("extract_kernel<16, true, 8, 1, 2>", 2), ("extract_kernel<16, false, 0, 1, 2>", 2),
+                                        ("extract_kernel<4, true, 8, 0, 1>", 8), ("extract_kernel<4, true, -1, 0, 1>", 8)])
+def test_resident_waves(kernels, name, waves):
     """The path of incomplete tiles must not take registers from the path of whole ones."""
     assert int(re.search(r"; Occupancy: (\d+)", kernels[name]).group(1)) >= waves
