@@ -18,7 +18,8 @@
  *     it past the call's completion on the stream).  Arrays of descriptors (srs_tensor_pair[],
  *     srs_tensor[], numel[]) are HOST arrays, read before the call returns.
  *   - Weights are 16-bit patterns (BF16; FP16 works unchanged).  No arithmetic is done on them.
- *     Base pointers need 2-byte alignment only; 16-byte alignment takes the fast path.
+ *     Base pointers need 2-byte alignment only: tensors of any alignment and length are read in 16-byte vectors, but for
+ *     one incomplete vector at either end of a tile.
  *   - `stream` is a hipStream_t passed as void* (NULL = the default stream).  Every call is
  *     asynchronous on it and does no host synchronisation, except where stated.
  *   - Payload layout: bucket b owns the slots I[b*cap .. b*cap+cap) and V[b*cap .. b*cap+cap).
@@ -29,8 +30,8 @@
  *     counts[b] are left untouched.
  *   - Return value: SRS_OK (0) or a negative srs_error.  Argument errors (SRS_ERR_INVALID,
  *     SRS_ERR_TOO_LARGE) are found before anything is launched or copied.  SRS_ERR_HIP reports a
- *     failed runtime call (allocation, copy, launch); calls that issue several kernels (the encoded
- *     applies, the value coder, every extract with its clearing kernel) may then have launched the
+ *     failed runtime call (allocation, copy, launch); calls that issue several kernels (the value coder,
+ *     an extract with its clearing kernel or its second pass) may then have launched the
  *     earlier ones, so the outputs of such a call are undefined.  Device-side conditions (overflow,
  *     bad index, look-back time-out) are reported through srs_status().
  *   - A context serialises its own scratch memory: use one context per stream, and do not run
@@ -71,11 +72,13 @@ typedef enum {
 #define SRS_OPT_SPIN_LIMIT 1   /* max polls of a predecessor tile before SRS_FLAG_TIMEOUT (default 1<<24) */
 #define SRS_OPT_TILE_ELEMS 2   /* elements per extract tile: 4096, 8192, 16384 or 32768 (default for plans; tuning;
                                   affects plans created afterwards).  Until it is set, the calls on a single tensor
-                                  take smaller tiles for small tensors. */
-#define SRS_OPT_REFRESH_GROUP 3 /* snapshot refresh: 8 (default) = every aligned 128-byte line of the snapshot that
-                                  holds a change is rewritten from the new weights (unchanged elements get the value
-                                  they have; only elements of the tensor are stored); 0 = a store per changed
-                                  element everywhere.  Same result; tuning.
+                                  take smaller tiles for small tensors, never more than 256 because of it. */
+#define SRS_OPT_REFRESH_GROUP 3 /* snapshot refresh: 8 (default) = aligned 128-byte lines of the snapshot that hold a
+                                  change are rewritten from the new weights (unchanged elements get the value they
+                                  have).  Only elements of the tensor are stored; of a line that two waves or tiles
+                                  share, each rewrites its own part if that part holds a change, and the incomplete
+                                  16-byte vectors at the two ends of a tile are stored element by element.  0 = a
+                                  store per changed element everywhere.  Same result; tuning.
                                   Applies to the extract calls of every element width and to the fused cast. */
 #define SRS_OPT_INTERLEAVE 4   /* buckets whose tiles are interleaved over consecutive workgroups, 1..4096
                                   (default 64; tuning; affects plans created afterwards) */
@@ -126,10 +129,12 @@ int srs_extract(srs_ctx *ctx, void *old_snapshot, const void *new_w, uint64_t n,
  * tile status words and ticket counters live in a static device array of the library (9 MiB per GPU, held until
  * the process ends) instead of the context's growable scratch, so the call never allocates, frees or
  * synchronises, whatever its size.  Limits: at most 2^20 tiles (a bucket has ceil(bucket_elems / SRS_OPT_TILE_ELEMS)
- * tiles: with buckets of at least one default tile of 32768 elements every n below 2^31 fits) and at most 2^18 buckets; beyond either the call returns
+ * tiles; where the option is not set and a small tensor takes smaller ones, there are at most 256 in all: with buckets of
+ * at least one default tile of 32768 elements every n below 2^31 fits) and at most 2^18 buckets; beyond either the call returns
  * SRS_ERR_TOO_LARGE and launches nothing.  Every context on one GPU shares that GPU's array: two such calls that
  * overlap in time on one GPU (different streams or different contexts) race; order them on one stream.  The
- * array keeps the previous call's contents; a small kernel at the head of each call clears what the call uses.
+ * array keeps the previous call's contents; where a bucket has more than one tile, a small kernel at the head of the call
+ * clears what the call uses, and where none has, neither array is used.
  */
 int srs_extract_noalloc(srs_ctx *ctx, void *old_snapshot, const void *new_w, uint64_t n, uint64_t bucket_elems,
                         int32_t *I, uint16_t *V, uint32_t *counts, uint64_t cap, void *stream);
@@ -198,8 +203,7 @@ int srs_tensor_indices(srs_ctx *ctx, srs_plan *plan, const int32_t *I, const uin
  * through the 16-bit calls above unchanged.  These four calls are the same operations on 8-bit patterns (FP8 in
  * either of its formats, or any other one-byte type): old_snapshot / new_w / weights hold n (or numel[k]) bytes,
  * V is uint8_t[nb*cap]; indices, counts, capacity rule, flags, snapshot semantics (SRS_OPT_SNAPSHOT included) and
- * error behaviour are those of the 16-bit calls.  No alignment is required (16-byte aligned tensors take the
- * vector path).  A plan serves both widths.  Restrictions: SRS_OPT_TILE_ELEMS 4096 is rejected with
+ * error behaviour are those of the 16-bit calls.  No alignment is required.  A plan serves both widths.  Restrictions: SRS_OPT_TILE_ELEMS 4096 is rejected with
  * SRS_ERR_INVALID (a one-byte tile is at least 8192 elements).  The fused cast, the cumulative set, the index coding of an
  * existing payload (srs_encode_indices reads I only) and the routing work as they stand or do not apply; an
  * encoded apply and a value coder for one-byte values are not provided.
@@ -221,8 +225,7 @@ int srs_apply_multi_u8(srs_ctx *ctx, srs_plan *plan, const srs_tensor *t,
  * model parameters on entry and the new ones on completion; the payload is exactly what srs_extract(old =
  * weights before, new = round_BF16(master)) would give, with the same layout, capacity rule and flags.
  * round_BF16 rounds the binary32 value to the nearest BF16, ties to even; a NaN becomes 0x7FC0.
- * master: device pointer(s) to FP32 data, 4-byte aligned (16-byte alignment of both buffers takes the vector
- * path).  In the list form t[k].old_snapshot is tensor k's BF16 model parameters and t[k].new_w its FP32
+ * master: device pointer(s) to FP32 data, 4-byte aligned.  In the list form t[k].old_snapshot is tensor k's BF16 model parameters and t[k].new_w its FP32
  * master weights.
  */
 int srs_extract_cast(srs_ctx *ctx, void *weights, const float *master, uint64_t n, uint64_t bucket_elems,

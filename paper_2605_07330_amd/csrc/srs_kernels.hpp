@@ -12,14 +12,15 @@
 //   scan + an LDS combine across the four waves, chains tiles of the same bucket with a
 //   decoupled look-back on one 64-bit {flag, value} status word per tile, stages the
 //   (index, value) pairs of the tile in LDS in rank order and writes them out coalesced
-//   (Alg. 2: V = W[I], I int32 ascending).  The snapshot is refreshed in the same pass: every 128-byte line of
-//   it that holds a change is rewritten whole from the new weights the lanes hold (RG = 8), or each changed
+//   (Alg. 2: V = W[I], I int32 ascending).  The snapshot is refreshed in the same pass: 128-byte lines of
+//   it that hold a change are rewritten from the new weights the lanes hold (RG = 8), or each changed
 //   element is stored by itself (RG = 0), or nothing is written for callers that rotate buffers (RG = -1).
 //   Template flavours of the same kernel: SRC = FP32 master weights rounded to BF16 on the fly (the
 //   cast-and-copy of Alg. 1 fused with its diff); EB = 1 for one-byte (FP8) patterns.
 // mark_kernel: one optimizer step of Alg. 1's index accumulation, OR-ed into a bitmap.
 // extract_marked_kernel: the payload of the accumulated index set, gathered through the bitmap.
-// apply_kernel: the scatter of Alg. 3, W[I] <- V, one workgroup per (bucket, payload chunk).
+// apply_kernel: the scatter of Alg. 3, W[I] <- V, one workgroup per (bucket, payload chunk);
+//   apply_grouped_kernel: the same where the payload slots hold whole buckets, several chunks per workgroup.
 // refresh_overflow_kernel: whole-bucket copy for buckets whose payload overflowed, when the snapshot is refreshed
 // by scattering the payload into it after the scan (apply_kernel on the snapshot) instead of inside extract_kernel.
 // apply_encoded_kernel / encode_indices_kernel: the 16-bit index delta coding of Sec. 3.3.
@@ -336,7 +337,7 @@ __device__ __forceinline__ uint32_t look_back(const ExtractArgs &a, uint32_t til
     return excl;
 }
 
-// Refresh by whole lines of a tile read on extract_kernel's grid (og: grid position 0, g0: this lane's first, m: change
+// Refresh by lines of a tile read on extract_kernel's grid (og: grid position 0, g0: this lane's first, m: change
 // masks, x: what to write): 8 consecutive grid vectors from a 128-byte boundary on, which begins q lanes before lane 0's
 // vector; the line across the end of a row has its other vectors in the next row.
 template <int V, class T>
@@ -369,9 +370,10 @@ __device__ __forceinline__ void refresh_lines(gptr<T> og, uint32_t g0, uint32_t 
 // ---------------------------------------------------------------------------------------------
 // extract
 // ---------------------------------------------------------------------------------------------
-// RG = how the snapshot is refreshed.  8: by whole lines -- the tile rewrites every
-// aligned 128-byte line of the snapshot that holds a change (8 lanes x 16 bytes of one store instruction) from the
-// new weights it has in registers; unchanged elements get the value they already hold.  The snapshot's loads and
+// RG = how the snapshot is refreshed.  8: by whole lines -- the tile rewrites each
+// aligned 128-byte line of the snapshot that holds a change (8 lanes x 16 bytes) from the
+// new weights it has in registers; unchanged elements get the value they already hold.  (A wave rewrites its part of a line
+// that reaches beyond its part of the tile if that part holds a change; the incomplete vectors go element by element.)  The snapshot's loads and
 // these stores carry the non-temporal hint: a line written in full needs no read-modify-write behind the L2, and
 // nothing of the snapshot is needed again.  Measured on the 910-bucket benchmark set against element-wise refresh,
 // in one process, ms: 21.8 / 22.4 at 0.1 % changed, 25.8 / 28.7 at 1 %, 30.1 / 36.2 at 3 %, 33.6 / 40.4 at 10 %.
