@@ -11,7 +11,7 @@
 //   (Alg. 1: I = { i : W[i] != W_prev[i] }), ranks the changed elements with a packed DPP wave
 //   scan + an LDS combine across the four waves, chains tiles of the same bucket with a
 //   decoupled look-back on one 64-bit {flag, value} status word per tile, stages the
-//   (index, value) pairs of the tile in LDS in rank order and writes them out coalesced
+//   (index, value) pairs of the tile in LDS in rank order and writes them out coalesced, by one wave once the others are done
 //   (Alg. 2: V = W[I], I int32 ascending).  The snapshot is refreshed in the same pass: 128-byte lines of
 //   it that hold a change are rewritten from the new weights the lanes hold (RG = 8), or each changed
 //   element is stored by itself (RG = 0), or nothing is written for callers that rotate buffers (RG = -1).
@@ -56,6 +56,14 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 #define SRS_GLOBAL __attribute__((address_space(1)))
 template <class T> using gptr = T SRS_GLOBAL *;
 template <class T> __device__ __forceinline__ gptr<T> as_global(T *p) { return (gptr<T>)p; }
+// a uniform pointer that stays in scalar registers: the accesses of a lane then share one offset register, instead of each having
+// a 64-bit address of its own
+template <class T> __device__ __forceinline__ gptr<T> scalar_base(gptr<T> p) {
+    uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(unsigned long long)p);
+    uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)((unsigned long long)p >> 32));
+    asm("" : "+s"(lo), "+s"(hi));
+    return (gptr<T>)(((unsigned long long)hi << 32) | lo);
+}
 
 struct TileDesc {          // one extract tile of a tensor list (16 bytes)
     uint32_t tensor;       // index into the pointer table
@@ -123,7 +131,7 @@ struct ApplyArgs {
 template <int CTRL, int ROW_MASK, int BANK_MASK>
 __device__ __forceinline__ uint32_t dpp_get(uint32_t x) {
     // lanes whose source is outside the row, or whose row is masked off, receive 0
-    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROW_MASK, BANK_MASK, false);
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROW_MASK, BANK_MASK, ROW_MASK == 0xF && BANK_MASK == 0xF);
 }
 
 // inclusive prefix sum over the 64 lanes of a wave (also valid on two packed 16-bit fields as long
@@ -141,8 +149,10 @@ __device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t x) {
 // workgroup barrier that orders LDS accesses only: waits for this wave's LDS operations (lgkmcnt), not for its
 // outstanding global loads and stores, before the barrier instruction
 __device__ __forceinline__ void lds_barrier() {
+    asm volatile("" ::: "memory");          // the compiler keeps LDS accesses on their side of it
     __builtin_amdgcn_s_waitcnt(0xC07F);     // vmcnt and expcnt at their maxima (= no wait), lgkmcnt(0)
     __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
 }
 
 __device__ __forceinline__ uint32_t lane63(uint32_t x) {
@@ -337,20 +347,21 @@ __device__ __forceinline__ uint32_t look_back(const ExtractArgs &a, uint32_t til
     return excl;
 }
 
-// Refresh by lines of a tile read on extract_kernel's grid (og: grid position 0, g0: this lane's first, m: change
+// Refresh by lines of a tile read on extract_kernel's grid (ow: first grid position of the wave, lv: this lane's first from there,
+// nw: grid positions of the wave below it form whole vectors, m: change
 // masks, x: what to write): 8 consecutive grid vectors from a 128-byte boundary on, which begins q lanes before lane 0's
 // vector; the line across the end of a row has its other vectors in the next row.
 template <int V, class T>
-__device__ __forceinline__ void refresh_lines(gptr<T> og, uint32_t g0, uint32_t nbody, bool in_head, const uint32_t (&m)[V],
+__device__ __forceinline__ void refresh_lines(gptr<T> ow, uint32_t lv, uint32_t nw, bool in_head, const uint32_t (&m)[V],
                                               const u32x4 (&x)[V], int lane) {
     constexpr uint32_t ROW = 64u * 16u / sizeof(T);
-    const uint32_t q = ((uint32_t)(uintptr_t)og >> 4) & 7u;             // uniform
+    const uint32_t q = ((uint32_t)(uintptr_t)ow >> 4) & 7u;             // uniform
     if (q == 0) {
 #pragma unroll
         for (int j = 0; j < V; ++j) {
             const unsigned long long changed = __ballot(m[j] != 0);
-            const uint32_t g = g0 + j * ROW;
-            if (((uint32_t)(changed >> (lane & ~7)) & 0xFFu) && g < nbody && (j > 0 || !in_head)) store16_nt(og + g, x[j]);
+            if (((uint32_t)(changed >> (lane & ~7)) & 0xFFu) && lv + j * ROW < nw && (j > 0 || !in_head))
+                store16_nt(scalar_base(ow + (j & ~3) * ROW) + lv + (j & 3) * ROW, x[j]);
         }
     } else {
         const int first = (int)(((uint32_t)lane + q) & ~7u) - (int)q;                            // -7 .. 63
@@ -360,8 +371,8 @@ __device__ __forceinline__ void refresh_lines(gptr<T> og, uint32_t g0, uint32_t 
             const unsigned long long next = (j + 1 < V) ? __ballot(m[(j + 1) % V] != 0) : 0ull;
             uint32_t line = (first < 0) ? (uint32_t)((cur << -first) | (prev >> (64 + first))) : (uint32_t)(cur >> first);
             if (first > 56) line |= (uint32_t)(next << (64 - first));
-            const uint32_t g = g0 + j * ROW;
-            if ((line & 0xFFu) && g < nbody && (j > 0 || !in_head)) store16_nt(og + g, x[j]);
+            if ((line & 0xFFu) && lv + j * ROW < nw && (j > 0 || !in_head))
+                store16_nt(scalar_base(ow + (j & ~3) * ROW) + lv + (j & 3) * ROW, x[j]);
             prev = cur; cur = next;
         }
     }
@@ -389,12 +400,38 @@ __device__ __forceinline__ void refresh_lines(gptr<T> og, uint32_t g0, uint32_t 
 // source for the host code.)
 constexpr int kSrcBf16 = 0, kSrcFp32 = 1, kSrcBitmap = 2;
 
-// Waves per SIMD are demanded where the incomplete vectors' registers would cost the whole tiles one.  Lists of one-byte
-// elements in tiles of 16384, 6 or 7 waves / 8, us: five 32B-shaped layers in place at 0.5 % 1500 / 1448, rotated 1195 /
-// 1168, four 8B-shaped 508 / 499, three 30B-A3B-shaped 1151 / 1174.  (Single tensors, which take that tile by default, have
-// few workgroups and are 1 to 3 % faster without.)
+// Waves per SIMD are demanded where a few registers more would cost one.  Lists of one-byte elements in tiles of 16384,
+// 6 waves / 8, us: five 32B-shaped layers in place at 0.3 % 1228 / 1174, rotated 1066 / 1025, four 8B-shaped 433 / 428.
 constexpr int waves_per_simd(int v, bool multi, int src, int eb) {
-    return (v >= 16 && src == kSrcBf16) ? 3 : (v == 4 && eb == 1 && multi) ? 8 : 1;
+    return (v >= 16 && src == kSrcBf16) ? 3 : (v == 8 && src == kSrcFp32) ? 4 : (v == 4 && eb == 1 && multi) ? 8 : 1;
+}
+
+// Tables that no kernel of the launch writes, read at uniform addresses: in the constant address space they come through the
+// scalar cache wherever they are read; behind an atomic or a barrier the compiler would take vector loads.
+template <class T> __device__ __forceinline__ const T __attribute__((address_space(4))) *as_table(const T *p) {
+    return (const T __attribute__((address_space(4))) *)p;
+}
+
+// 16 bytes moved up / down by `bytes` (0 .. 15), zeros coming in
+__device__ __forceinline__ u32x4 shift_up(u32x4 v, uint32_t bytes) {
+    unsigned long long lo = ((unsigned long long)v.y << 32) | v.x, hi = ((unsigned long long)v.w << 32) | v.z;
+    const uint32_t n = (bytes & 7u) * 8u;
+    if (bytes >= 8u) { hi = lo; lo = 0; }
+    hi = (hi << n) | (n ? lo >> (64u - n) : 0ull);
+    lo <<= n;
+    u32x4 r;
+    r.x = (uint32_t)lo; r.y = (uint32_t)(lo >> 32); r.z = (uint32_t)hi; r.w = (uint32_t)(hi >> 32);
+    return r;
+}
+__device__ __forceinline__ u32x4 shift_down(u32x4 v, uint32_t bytes) {
+    unsigned long long lo = ((unsigned long long)v.y << 32) | v.x, hi = ((unsigned long long)v.w << 32) | v.z;
+    const uint32_t n = (bytes & 7u) * 8u;
+    if (bytes >= 8u) { lo = hi; hi = 0; }
+    lo = (lo >> n) | (n ? hi << (64u - n) : 0ull);
+    hi >>= n;
+    u32x4 r;
+    r.x = (uint32_t)lo; r.y = (uint32_t)(lo >> 32); r.z = (uint32_t)hi; r.w = (uint32_t)(hi >> 32);
+    return r;
 }
 
 template <int V, bool MULTI, int RG, int SRC = kSrcBf16, int EB = 2>
@@ -422,13 +459,14 @@ __global__ __launch_bounds__(kThreads, waves_per_simd(V, MULTI, SRC, EB)) void e
     __shared__ u32x4 s_tail;               // the tile's last, incomplete vector (see below) and its change mask
     __shared__ uint32_t s_tail_mask;
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const uint32_t wave = uniform((uint32_t)tid >> 6), wbase = wave * (V * ROW);   // first grid position of the wave
 
     // ---- which bucket this workgroup serves, then claim that bucket's next tile
     uint32_t bucket, first_tile, bucket_tiles;
     if (MULTI) {
-        const WgInfo wi = a.wg_info[blockIdx.x];
-        bucket = wi.bucket; first_tile = wi.first_tile; bucket_tiles = wi.ntiles;
+        const auto *wi = as_table(a.wg_info + blockIdx.x);
+        bucket = wi->bucket; first_tile = wi->first_tile; bucket_tiles = wi->ntiles;
     } else {
         // groups of `group` buckets; inside a group consecutive workgroups rotate over its buckets.
         // Only the very last bucket may have fewer tiles: in its group the first last_tiles rounds
@@ -460,21 +498,24 @@ __global__ __launch_bounds__(kThreads, waves_per_simd(V, MULTI, SRC, EB)) void e
     const bool last = (k == bucket_tiles - 1);
 
     // ---- where this tile lives
-    uint32_t bucket_off, len, idx_base;
-    gptr<T> po; gptr<const void> pn_raw; uint64_t pn_off;      // new weights: base pointer and element offset
+    constexpr uint32_t NB = CAST ? 4u : (uint32_t)EB;                   // bytes per new weight
+    uint32_t len, idx_base;
+    gptr<T> po; gptr<const uint8_t> pn;
     if (MULTI) {
-        const TileDesc d = a.tiles[tile];
-        const PtrPair p = a.ptrs[d.tensor];
-        po = (gptr<T>)p.old_w + d.tensor_off; pn_raw = as_global(p.new_w); pn_off = d.tensor_off;
-        bucket_off = d.bucket_off; len = d.len;
-        idx_base = bucket_off;                          // index = position inside the bucket
+        const auto *d = as_table(a.tiles + tile);
+        const uint32_t tensor = d->tensor, off = d->tensor_off;
+        len = d->len;
+        idx_base = d->bucket_off;                       // index = position inside the bucket
+        const auto *t = as_table(a.ptrs + tensor);
+        po = (gptr<T>)t->old_w + off;
+        pn = (gptr<const uint8_t>)as_global(t->new_w) + (uint64_t)off * NB;
     } else {
         const uint64_t b0 = (uint64_t)bucket * a.be;
-        const uint32_t blen = (uint32_t)((a.n - b0 < a.be) ? (a.n - b0) : a.be);
-        bucket_off = k * TILE;
-        len = (blen - bucket_off < TILE) ? (blen - bucket_off) : TILE;
-        po = (gptr<T>)a.old_w + b0 + bucket_off; pn_raw = as_global(a.new_w); pn_off = b0 + bucket_off;
-        idx_base = (uint32_t)(b0 + bucket_off);         // index = tensor-flat position
+        const uint32_t blen = (uint32_t)((a.n - b0 < a.be) ? (a.n - b0) : a.be), off = k * TILE;
+        len = (blen - off < TILE) ? (blen - off) : TILE;
+        po = (gptr<T>)a.old_w + b0 + off;
+        pn = (gptr<const uint8_t>)as_global(a.new_w) + (b0 + off) * NB;
+        idx_base = (uint32_t)(b0 + off);                // index = tensor-flat position
     }
 
     // ---- stream the tile in 16-byte vectors on a grid that starts at the 16-byte boundary at or before its first
@@ -482,208 +523,228 @@ __global__ __launch_bounds__(kThreads, waves_per_simd(V, MULTI, SRC, EB)) void e
     // lane l holds positions (j*64 + l)*VE .. +VE, so ascending order is (wave, j, lane, element).  Vectors that lie
     // wholly in the tile are one load each whatever the alignment of the new weights.  What is left over is at most one
     // incomplete vector in front (thread 0's first) and one behind the last whole vector (thread kThreads-1 takes it, as
-    // a vector of its own that ranks after all others); those two are read element by element.
-    // The sizes of real parameter lists put most tiles off the 16-byte boundaries, or make them incomplete: 300 odd-sized
-    // tensors end to end (108 M elements, 1 % changed) took 283 us when each vector of such a tile was read element by
-    // element, and 116 us now.
-    u32x4 xo[V], xn[V];
+    // a vector of its own that ranks after all others).  Those two are read as the tile's first and last 16 bytes, at any
+    // address, and shifted to their place; a tile shorter than a vector is read element by element.
+    // Lanes that have no vector read the tile's first 16 bytes as well, and a tile shorter than a vector reads the flag word:
+    // one run of loads without a branch in it serves every tile, and all of them are in flight together.  Measured with what
+    // follows below, us, extract only: 300 odd-sized tensors end to end (108 M elements, 1 % changed) 119 -> 107, with the
+    // snapshot rotated and the new weights six bytes off 98 -> 80.
+    u32x4 xo[V], xn[V], f1[CAST ? V : 1], to, tn, tn1;
     const uint32_t h = (uint32_t)((uintptr_t)po & 15u) / EB;
     const uint32_t glen = len + h;                                      // grid positions h .. glen-1 exist
     const uint32_t nbody = (glen < TILE ? glen : TILE) / VE * VE;       // positions below it form whole vectors (but for h)
-    const uint32_t g0 = (uint32_t)wave * (V * ROW) + (uint32_t)lane * VE;
+    uint32_t lv = (uint32_t)lane * VE;                                  // this lane's first position, from its wave's first
+    auto fresh = [&]() { asm volatile("" : "+v"(lv)); };                // what follows derives its positions anew instead of keeping them in registers
+    const uint32_t nw = nbody > wbase ? nbody - wbase : 0u;             // the wave's positions below it form whole vectors
     // bases of the grid: only positions h .. glen-1 are ever accessed
     const gptr<T> og = po - h;
-    const gptr<const uint32_t> fg = (gptr<const uint32_t>)pn_raw + pn_off - h;     // with CAST: the master weights
-    const gptr<const T> ng = (gptr<const T>)pn_raw + pn_off - h;
+    const gptr<const uint32_t> fg = (gptr<const uint32_t>)pn - h;     // with CAST: the master weights
+    const gptr<const T> ng = (gptr<const T>)pn - h;
     const bool in_head = h != 0 && tid == 0;                            // this thread's first vector is the incomplete one in front
-    uint32_t m[V];
-    if (glen >= TILE) {                                                 // uniform over the workgroup
-        // the thread of the incomplete vector reads its neighbour's instead (and its own below): no branch between the loads
-        const uint32_t g_first = in_head ? VE : g0;
-        auto stream_tile = [&](auto hint) {                // all loads of the tile issued back to back
-            constexpr bool H = decltype(hint)::value;
-            if (CAST) {
-                u32x4 f0[V], f1[V];
-                // paced like the loads of the in-place refresh below (this flavour always writes the parameters
-                // back); half the pause, as there are half as many bytes per load of master weights.  Measured on
-                // the benchmark set at 1 %: 36.2 ms against 37.4 unpaced (pause 4: 36.3)
-#pragma unroll
-                for (int j = 0; j < V; ++j) {
-                    f0[j] = load16_any<false>(fg + (j ? g0 + j * ROW : g_first));
-                    __builtin_amdgcn_sched_barrier(0); __builtin_amdgcn_s_sleep(kLoadPace / 2); __builtin_amdgcn_sched_barrier(0);
-                    f1[j] = load16_any<false>(fg + (j ? g0 + j * ROW : g_first) + 4);
-                    __builtin_amdgcn_sched_barrier(0); __builtin_amdgcn_s_sleep(kLoadPace / 2); __builtin_amdgcn_sched_barrier(0);
-                }
-#pragma unroll
-                for (int j = 0; j < V; ++j) {
-                    xo[j] = load16<H>(og + (j ? g0 + j * ROW : g_first));
-                    __builtin_amdgcn_sched_barrier(0); __builtin_amdgcn_s_sleep(kLoadPace / 2); __builtin_amdgcn_sched_barrier(0);
-                }
-#pragma unroll
-                for (int j = 0; j < V; ++j) xn[j] = round8_bf16(f0[j], f1[j]);
-            } else if (RG >= 0) {
-                // A kernel that also writes the snapshot issues its loads in program order with a short sleep
-                // after each (kLoadPace x 64 clocks): the tile's 32 loads then leave the CU over about 3 us instead
-                // of in one burst, which the memory side, busy with the refresh stores of the other workgroups,
-                // serves faster.  Measured in one process on the benchmark sets, paced / unpaced, ms: 30B-A3B at
-                // 1 % 25.09 / 25.84, at 0.1 % 20.83 / 21.82, at 5 % 30.70 / 30.89, skewed 20.45 / 21.44; 8B at 1 %
-                // 6.80 / 7.24.  (Pace 1, 2, 4, 6, 8: 25.58, 25.31, 25.10, 25.04, 25.17.)  The kernel that writes
-                // nothing into weights gains nothing from it (18.87 / 18.83) and stays as it was.
-#pragma unroll
-                for (int j = 0; j < V; ++j) {
-                    xn[j] = load16_any<H>(ng + (j ? g0 + j * ROW : g_first));
-                    __builtin_amdgcn_sched_barrier(0); __builtin_amdgcn_s_sleep(kLoadPace); __builtin_amdgcn_sched_barrier(0);
-                }
-#pragma unroll
-                for (int j = 0; j < V; ++j) {
-                    xo[j] = load16<H>(og + (j ? g0 + j * ROW : g_first));
-                    __builtin_amdgcn_sched_barrier(0); __builtin_amdgcn_s_sleep(kLoadPace); __builtin_amdgcn_sched_barrier(0);
-                }
-            } else if (EB == 2 && h == 0) {
-                // The kernel that writes nothing into weights reads one stream after the other.  The fence holds the
-                // scheduler to it: without it the two streams' loads alternate, which costs 1 to 6 %.  Tiles that start on
-                // a 16-byte boundary (uniform; all of an aligned list) get loads of their own without the choice of a
-                // first vector, worth up to 3 % more.  Rotated snapshot, one process, us: alternating / fence / fence
-                // and own loads: eight 32B-shaped layers at 0.2 % 2569 / 2462 / 2388, at 1 % 2756 / 2641 / 2560, four
-                // at 5 % with the second pass 3343 / 3278 / 3257; 8B-shaped set at 1 % 5954 / 5933 / 5923; single tensor
-                // of 300 M elements in odd buckets 259 / 251 / 244.  One-byte elements do without: there the same two
-                // changes gain up to 1 % on 30B-A3B-shaped sets and lose up to 2 % on 32B-shaped and 8B-shaped ones.
-#pragma unroll
-                for (int j = 0; j < V; ++j) xn[j] = load16_any<H>(ng + g0 + j * ROW);
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int j = 0; j < V; ++j) xo[j] = load16<H>(og + g0 + j * ROW);
-            } else {
-#pragma unroll
-                for (int j = 0; j < V; ++j) xn[j] = load16_any<H>(ng + (j ? g0 + j * ROW : g_first));
-                if constexpr (EB == 2) __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int j = 0; j < V; ++j) xo[j] = load16<H>(og + (j ? g0 + j * ROW : g_first));
-            }
-        };
-        // one flavour of loads per instantiation: choosing between two at run time cost 2 ms of the 3 ms the hints gain
-        stream_tile(std::integral_constant<bool, NT || LINES>{});
-    } else {
-        constexpr bool H = NT || LINES;
-        const u32x4 none = {0u, 0u, 0u, 0u};
-        // Master weights are rounded in groups of four vectors, whose loads go out together: rounding each as it arrives
-        // makes a chain of up to V round trips, and loading all of them first takes registers from the whole tiles.  Cast of
-        // single tensors refreshed by lines, one at a time / fours, us: 7 M elements at 3 % 23.0 / 21.3, 4 M in buckets of
-        // 300,000 at 0.03 % 15.7 / 13.8 (twos and eights the same within 1 %); aligned lists the same within 1 %.
-        constexpr int G = (CAST && V > 4) ? 4 : V;
-#pragma unroll
-        for (int i = 0; i < V; i += G) {
-            u32x4 f1[CAST ? G : 1];
-#pragma unroll
-            for (int j = i; j < i + G; ++j) {
-                const uint32_t g = g0 + j * ROW;
-                const bool whole = g < nbody && (j > 0 || !in_head);
-                xo[j] = whole ? load16<H>(og + g) : none;
-                if constexpr (CAST) {
-                    xn[j] = whole ? load16_any<false>(fg + g) : none;
-                    f1[j - i] = whole ? load16_any<false>(fg + g + 4) : none;
-                } else {
-                    xn[j] = whole ? load16_any<H>(ng + g) : none;
-                }
-            }
-            if constexpr (CAST) {
-#pragma unroll
-                for (int j = i; j < i + G; ++j) xn[j] = round8_bf16(xn[j], f1[j - i]);
-            }
-        }
-    }
     const bool has_tail = glen > nbody;                                 // uniform
-    if (h != 0 || has_tail) {
-        const bool front = in_head && nbody != 0;
-        if (front || (has_tail && tid == kThreads - 1)) {
-            const uint32_t at = front ? 0u : nbody;
-            const uint32_t lo = (h > at) ? h - at : 0u, hi = front ? VE : glen - nbody;
-            const u32x4 vo = EL::load_window(og + at, lo, hi);
-            u32x4 vn;
-            if constexpr (CAST) vn = load8_window_cast(fg + at, lo, hi);
-            else vn = EL::load_window(ng + at, lo, hi);
-            if (front) { xo[0] = vo; xn[0] = vn; }
-            const uint32_t md = EL::diff_mask(vo, vn);
-            if (!front) { s_tail = vn; s_tail_mask = md; }
-            if (LINES) {                                                // these two are refreshed element by element
-                for (uint32_t mm = md; mm; mm &= mm - 1u) {
-                    const uint32_t e = (uint32_t)__builtin_ctz(mm);
-                    og[at + e] = (T)EL::pattern(vn, e);
-                }
-            }
+    const bool short_tile = len < VE;                                   // uniform
+    const u32x4 none = {0u, 0u, 0u, 0u};
+    constexpr bool H = NT || LINES;
+    const gptr<const uint8_t> ob = scalar_base(short_tile ? (gptr<const uint8_t>)as_global(a.flags) : (gptr<const uint8_t>)og);
+    const gptr<const uint8_t> nb = scalar_base(short_tile ? (gptr<const uint8_t>)as_global(a.flags)
+                                               : CAST ? (gptr<const uint8_t>)fg : (gptr<const uint8_t>)ng);
+    const uint32_t spare = short_tile ? 0u : h;
+    auto has_vector = [&](int j) -> bool { return lv + j * ROW < nw && !(j == 0 && in_head); };
+    auto position = [&](int j) -> uint32_t { return has_vector(j) ? wbase + lv + j * ROW : spare; };
+
+    __builtin_amdgcn_sched_barrier(0);
+    uint32_t t_pos = has_tail && !short_tile ? glen - VE : spare;
+    asm volatile("" : "+v"(t_pos));       // uniform: the compiler would wait for the loads to move them to scalar registers
+    tn = load16_any<false>(nb + t_pos * NB);
+    if (CAST) tn1 = load16_any<false>(nb + (t_pos * NB + 16u));
+    __builtin_amdgcn_sched_barrier(0);
+    auto pace = [&](auto clocks) {
+        constexpr int C = decltype(clocks)::value;
+        if constexpr (C > 0) {
+            __builtin_amdgcn_sched_barrier(0); __builtin_amdgcn_s_sleep(C); __builtin_amdgcn_sched_barrier(0);
         }
+    };
+    const std::integral_constant<int, CAST ? kLoadPace / 2 : (RG >= 0) ? kLoadPace : 0> p;
+#pragma unroll
+    for (int j = 0; j < V; ++j) {
+        xn[j] = load16_any<H && !CAST>(nb + position(j) * NB); pace(p);
+        if (CAST) { f1[j] = load16_any<false>(nb + (position(j) * NB + 16u)); pace(p); }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    fresh();
+    to = load16_any<false>(ob + t_pos * (uint32_t)EB);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int j = 0; j < V; ++j) { xo[j] = load16_any<H>(ob + position(j) * (uint32_t)EB); pace(p); }
+
+    // ---- change masks and their counts, the tail's first (its loads went out ahead of each stream)
+    fresh();
+    uint32_t m[V], ex[V];
+    auto refresh_incomplete = [&](uint32_t at, uint32_t mm, u32x4 x) {      // element by element
+        for (; mm; mm &= mm - 1u) {
+            const uint32_t e = (uint32_t)__builtin_ctz(mm);
+            og[at + e] = (T)EL::pattern(x, e);
+        }
+    };
+    if (has_tail && tid == kThreads - 1) {
+        uint32_t md;
+        u32x4 vn;
+        if (short_tile) {
+            const uint32_t lo = (h > nbody) ? h - nbody : 0u, hi = glen - nbody;
+            const u32x4 vo = EL::load_window(og + nbody, lo, hi);
+            if constexpr (CAST) vn = load8_window_cast(fg + nbody, lo, hi);
+            else vn = EL::load_window(ng + nbody, lo, hi);
+            md = EL::diff_mask(vo, vn);
+        } else {
+            const uint32_t down = (VE - (glen - nbody)) * EB;
+            if (CAST) tn = round8_bf16(tn, tn1);
+            vn = shift_down(tn, down);
+            md = EL::diff_mask(shift_down(to, down), vn);
+        }
+        s_tail = vn;
+        s_tail_mask = md;
+        if (LINES) refresh_incomplete(nbody, md, vn);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int j = 0; j < V; ++j) {
+        if (CAST) xn[j] = round8_bf16(xn[j], f1[j]);
+        m[j] = EL::diff_mask(xo[j], xn[j]);
+        if (!has_vector(j)) m[j] = 0;
+        if (j == 0 && in_head) {
+            // the front: elements 0 .. VE-h-1 of the tile, to positions h .. VE-1
+            u32x4 vo, vn;
+            if (short_tile) {
+                const uint32_t hi = glen < VE ? 0u : VE;                    // (a tile within one vector is all tail)
+                vo = EL::load_window(og, h, hi);
+                if constexpr (CAST) vn = load8_window_cast(fg, h, hi);
+                else vn = EL::load_window(ng, h, hi);
+            } else {
+                vo = shift_up(xo[0], h * EB);
+                vn = shift_up(xn[0], h * EB);
+            }
+            xn[0] = vn;
+            m[0] = EL::diff_mask(vo, vn);
+            if (LINES) refresh_incomplete(0, m[0], vn);
+        }
+        if (j % 4 == 3) __builtin_amdgcn_sched_barrier(0);
     }
 
-    // ---- change masks and their counts
-    uint32_t pk[V / 2];
-#pragma unroll
-    for (int j = 0; j < V; ++j) m[j] = EL::diff_mask(xo[j], xn[j]);
-
-#pragma unroll
-    for (int q = 0; q < V / 2; ++q) pk[q] = __popc(m[2 * q]) | (__popc(m[2 * q + 1]) << 16);
-
-    // ---- wave scan (two vectors per register), then offsets of each vector inside the wave
-    uint32_t ex[V];       // rank of this lane's first changed element of vector j inside the wave
+    // ---- wave scan (two vectors per register), then the rank of this lane's first changed element of each vector
     uint32_t wave_total = 0;
 #pragma unroll
     for (int q = 0; q < V / 2; ++q) {
-        const uint32_t inc = wave_inclusive_scan(pk[q]);
-        const uint32_t tot = lane63(inc);
-        const uint32_t exc = inc - pk[q];
+        const uint32_t both = __popc(m[2 * q]) | (__popc(m[2 * q + 1]) << 16);
+        uint32_t inc = wave_inclusive_scan(both);
+        asm("" : "+v"(inc));                 // inc - both stays a difference: as a sum of the scan's steps it would keep six registers
+        const uint32_t tot = lane63(inc), exc = inc - both;
         ex[2 * q] = wave_total + (exc & 0xFFFFu);
         wave_total += tot & 0xFFFFu;
         ex[2 * q + 1] = wave_total + (exc >> 16);
         wave_total += tot >> 16;
     }
-    if (LINES) refresh_lines<V, T>(og, g0, nbody, in_head, m, xn, lane);
+    if (LINES) refresh_lines<V, T>(og + wbase, lv, nw, in_head, m, xn, lane);
+    fresh();
     if (lane == 0) s_wave_total[wave] = wave_total;
     __syncthreads();
     uint32_t wave_base = 0, tile_total = 0;
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w) {
-        const uint32_t t = s_wave_total[w];
+    for (uint32_t w = 0; w < (uint32_t)kWaves; ++w) {
+        const uint32_t t = uniform(s_wave_total[w]);
         wave_base += (w < wave) ? t : 0u;
         tile_total += t;
     }
     const uint32_t tail_rank = tile_total;                // the tail's changed elements rank last
-    const uint32_t tail_mask = has_tail ? s_tail_mask : 0u;
-    tile_total = uniform(tile_total + (uint32_t)__popc(tail_mask));
+    const uint32_t tail_mask = has_tail ? uniform(s_tail_mask) : 0u;
+    tile_total += (uint32_t)__popc(tail_mask);
 #pragma unroll
     for (int j = 0; j < V; ++j) ex[j] += wave_base;       // from here on: rank inside the tile
 
-    // ---- chain with the earlier tiles of the bucket (wave 0), while the other waves start staging
-    if (wave == 0) {
+    // ---- the chain with the earlier tiles of the bucket: this tile's count is published now, and looked back from later
+    if (tid == 0 && !last) status_store(a.status + tile, status_word(tile == first_tile ? kStPrefix : kStAgg, tile_total));
+    // wave 0: changed elements of the bucket in front of the tile
+    auto settle = [&]() -> uint32_t {
         uint32_t excl = 0;
-        if (tile == first_tile) {
-            if (lane == 0 && !last) status_store(a.status + tile, status_word(kStPrefix, tile_total));
-        } else {
-            if (lane == 0) status_store(a.status + tile, status_word(kStAgg, tile_total));
+        if (tile != first_tile) {
             excl = look_back(a, tile, first_tile, lane);
-            if (lane == 0) status_store(a.status + tile, status_word(kStPrefix, excl + tile_total));
+            if (lane == 0 && !last) status_store(a.status + tile, status_word(kStPrefix, excl + tile_total));
         }
-        if (lane == 0) {
-            s_excl = excl;
-            if (last) {
-                const uint32_t c = excl + tile_total;
-                a.counts[bucket] = c;
-                if ((uint64_t)c > a.cap) atomicOr(a.flags, kFlagOverflow);
-            }
+        if (lane == 0 && last) {
+            const uint32_t c = excl + tile_total;
+            a.counts[bucket] = c;
+            if ((uint64_t)c > a.cap) atomicOr(a.flags, kFlagOverflow);
         }
-    }
+        return excl;
+    };
 
-    // ---- stage (index, value) pairs in LDS in rank order, write out coalesced; kStage per round.  The barriers of
-    // this loop order LDS accesses only (lds_barrier): a full __syncthreads would also wait for the round's global
-    // stores to complete, which on dense tiles (many rounds) costs more than the stores themselves.
     int32_t *const Ib = a.I + (uint64_t)bucket * a.cap;
     T *const Vb = reinterpret_cast<T *>(a.V) + (uint64_t)bucket * a.cap;
-    if (V >= 16 && tile_total > kStage) {
+    auto write_staged = [&](uint32_t from, uint32_t step, uint64_t rank0, uint32_t n) {
+        for (uint32_t q = from; q < n; q += step) {
+            const uint32_t ent = s_stage[q];
+            const uint32_t local = ent >> 16;
+            const T val = (T)(ent & 0xFFFFu);
+            const uint64_t r = rank0 + q;
+            if (local < len) {                      // always true for a correct scan; keeps stores in bounds
+                if (r < a.cap) { Ib[r] = (int32_t)(idx_base + local); Vb[r] = val; }
+                if (RG == 0) po[local] = val;           // snapshot refresh: W_prev <- W at changed positions
+            }
+        }
+    };
+    auto stage_round = [&](uint32_t r0) {
+#pragma unroll
+        for (int j = 0; j < V; ++j) {
+            uint32_t mm = m[j];
+            // the ranks of this vector's changed elements are ex[j] .. ex[j] + popc - 1: nothing to do in a round
+            // that lies wholly before or after them (this keeps dense tiles linear in the number of rounds)
+            if (mm && ex[j] < r0 + kStage && ex[j] + __popc(mm) > r0) {
+                uint32_t rank = ex[j] - r0;                  // wraps for elements of earlier rounds: skipped below
+                const uint32_t local = wbase + j * ROW - h + lv;
+                while (mm) {
+                    const uint32_t e = (uint32_t)__builtin_ctz(mm);
+                    mm &= mm - 1u;
+                    if (rank < kStage) s_stage[rank] = ((local + e) << 16) | EL::pattern(xn[j], e);
+                    ++rank;
+                }
+            }
+        }
+        if (has_tail && tid == kThreads - 1) {
+            uint32_t rank = tail_rank - r0;
+            for (uint32_t mm = tail_mask; mm; mm &= mm - 1u, ++rank) {
+                const uint32_t e = (uint32_t)__builtin_ctz(mm);
+                if (rank < kStage) s_stage[rank] = ((nbody - h + e) << 16) | EL::pattern(s_tail, e);
+            }
+        }
+    };
+
+    if (tile_total <= kStage) {
+        // One round of pairs, the usual case.  A tile's place in its bucket is known when all tiles before it have been
+        // counted, and where few buckets share the card hundreds of tiles wait for the slowest of them.  So the pairs are
+        // staged first, which gives the others time to publish and saves most polls of the status words; then three of
+        // the four waves end and give their registers back to workgroups that can load; wave 0 alone waits and writes out.
+        // Looking back at once / after staging / and with three waves gone, us: one 8B-shaped layer at 0.6 % refreshed in
+        // place 184 / 170 / 166 and rotated 159 / 147 / 143, 311 M elements in one bucket at 1 % 315 / 292 / 283 and
+        // 263 / 237 / 232, the same in 64 buckets 283 / 283 / 282.  (A workgroup that goes on to further tiles while the
+        // last ones wait in LDS gains as much on one bucket, but loses 3 to 7 % on many and a third on dense data.)
+        stage_round(0);
+        lds_barrier();
+        if (wave != 0) return;
+        const uint32_t excl = settle();
+        write_staged((uint32_t)lane, 64, excl, tile_total);
+        return;
+    }
+    if (wave == 0) {
+        const uint32_t e = settle();
+        if (lane == 0) s_excl = e;
+    }
+    __syncthreads();
+    const uint32_t excl = uniform(s_excl);
+    if (V >= 16) {
         // The largest tiles leave room for three workgroups per CU at most, and on dense data (several rounds of
         // staging) those spend most of their time writing out, with no loads in flight.  There every thread writes its
         // own pairs at their ranks instead: the lanes of a wave hold consecutive rank ranges, so these stores are
         // close together, and no round needs a barrier (measured at 25 % / 100 % density: 12.7 / 34.8 ms against
         // 22.3 / 39.9 ms staged; smaller tiles do better staged).
-        __syncthreads();                            // s_excl
-        const uint32_t excl = s_excl;
         auto write_out = [&](uint32_t mm, uint32_t r, uint32_t g, u32x4 x) {
             // r is below 2^32: a bucket holds fewer than 2^31 elements
             while (mm) {
@@ -704,47 +765,16 @@ __global__ __launch_bounds__(kThreads, waves_per_simd(V, MULTI, SRC, EB)) void e
             }
         };
 #pragma unroll
-        for (int j = 0; j < V; ++j) write_out(m[j], excl + ex[j], g0 + j * ROW, xn[j]);
+        for (int j = 0; j < V; ++j) write_out(m[j], excl + ex[j], wbase + j * ROW + lv, xn[j]);
         if (has_tail && tid == kThreads - 1) write_out(tail_mask, excl + tail_rank, nbody, s_tail);
         return;
     }
+    // The barriers of this loop order LDS accesses only (lds_barrier): a full __syncthreads would also wait for the round's
+    // global stores to complete, which on dense tiles (many rounds) costs more than the stores themselves.
     for (uint32_t r0 = 0; r0 < tile_total; r0 += kStage) {
-#pragma unroll
-        for (int j = 0; j < V; ++j) {
-            uint32_t mm = m[j];
-            // the ranks of this vector's changed elements are ex[j] .. ex[j] + popc - 1: nothing to do in a round
-            // that lies wholly before or after them (this keeps dense tiles linear in the number of rounds)
-            if (mm && ex[j] < r0 + kStage && ex[j] + __popc(mm) > r0) {
-                uint32_t rank = ex[j] - r0;                  // wraps for elements of earlier rounds: skipped below
-                const uint32_t local = g0 + j * ROW - h;
-                while (mm) {
-                    const uint32_t e = (uint32_t)__builtin_ctz(mm);
-                    mm &= mm - 1u;
-                    if (rank < kStage) s_stage[rank] = ((local + e) << 16) | EL::pattern(xn[j], e);
-                    ++rank;
-                }
-            }
-        }
-        if (has_tail && tid == kThreads - 1) {
-            uint32_t rank = tail_rank - r0;
-            for (uint32_t mm = tail_mask; mm; mm &= mm - 1u, ++rank) {
-                const uint32_t e = (uint32_t)__builtin_ctz(mm);
-                if (rank < kStage) s_stage[rank] = ((nbody - h + e) << 16) | EL::pattern(s_tail, e);
-            }
-        }
+        stage_round(r0);
         lds_barrier();
-        const uint32_t excl = s_excl;
-        const uint32_t nst = (tile_total - r0 < kStage) ? (tile_total - r0) : kStage;
-        for (uint32_t k = tid; k < nst; k += kThreads) {
-            const uint32_t ent = s_stage[k];
-            const uint32_t local = ent >> 16;
-            const T val = (T)(ent & 0xFFFFu);
-            const uint64_t r = (uint64_t)excl + r0 + k;
-            if (local < len) {                      // always true for a correct scan; keeps stores in bounds
-                if (r < a.cap) { Ib[r] = (int32_t)(idx_base + local); Vb[r] = val; }
-                if (RG == 0) po[local] = val;           // snapshot refresh: W_prev <- W at changed positions
-            }
-        }
+        write_staged((uint32_t)tid, kThreads, (uint64_t)excl + r0, (tile_total - r0 < kStage) ? (tile_total - r0) : kStage);
         lds_barrier();
     }
 }
@@ -973,7 +1003,8 @@ __global__ __launch_bounds__(kThreads) void mark_kernel(const ExtractArgs a) {
     uint32_t m[V];
 #pragma unroll
     for (int j = 0; j < V; ++j) m[j] = diff_mask8(xo[j], xn[j]);
-    if (CAST) refresh_lines<V, uint16_t>(og, g0, nbody, in_head, m, xn, lane);   // write the cast back where it changed something
+    const uint32_t wbase = uniform((uint32_t)wave) * (V * 512u);
+    if (CAST) refresh_lines<V, uint16_t>(og + wbase, (uint32_t)lane * 8u, nbody > wbase ? nbody - wbase : 0u, in_head, m, xn, lane);   // write the cast back where it changed something
 #pragma unroll
     for (int j = 0; j < V; ++j)
         if (m[j]) mark(g0 + j * 512, m[j]);
