@@ -31,7 +31,7 @@
  *   - Return value: SRS_OK (0) or a negative srs_error.  Argument errors (SRS_ERR_INVALID,
  *     SRS_ERR_TOO_LARGE) are found before anything is launched or copied.  SRS_ERR_HIP reports a
  *     failed runtime call (allocation, copy, launch); calls that issue several kernels (the value coder,
- *     an extract with its clearing kernel or its second pass) may then have launched the
+ *     an extract with its second pass) may then have launched the
  *     earlier ones, so the outputs of such a call are undefined.  Device-side conditions (overflow,
  *     bad index, look-back time-out) are reported through srs_status().
  *   - A context serialises its own scratch memory: use one context per stream, and do not run
@@ -100,7 +100,7 @@ typedef enum {
 typedef struct srs_ctx srs_ctx;    /* per-stream scratch: tile status words, per-bucket ticket counters, flag word */
 typedef struct srs_plan srs_plan;  /* immutable bucket / segment / tile tables of one tensor list */
 
-/* Context.  srs_create selects `device`, allocates a few KiB of device scratch and synchronises.
+/* Context.  srs_create selects `device`, allocates 160 KiB of device scratch and synchronises.
  * The tile-status and ticket arrays grow on demand inside srs_extract* (that one call then allocates
  * and synchronises the device; later calls of the same or smaller size do not). */
 int srs_create(srs_ctx **out, int device);
@@ -109,7 +109,8 @@ int srs_set_option(srs_ctx *ctx, int option, uint64_t value);
 const char *srs_strerror(int err);
 int srs_version(void);
 
-/* Waits for `stream`, copies the device flag word to *flags (host pointer) and clears it. */
+/* Waits for `stream`, copies the device flag word to *flags (host pointer) and clears it.  After SRS_FLAG_TIMEOUT it also
+ * queues kernels that put the context's scratch into its initial state. */
 int srs_status(srs_ctx *ctx, uint32_t *flags, void *stream);
 
 /*
@@ -132,9 +133,9 @@ int srs_extract(srs_ctx *ctx, void *old_snapshot, const void *new_w, uint64_t n,
  * tiles; where the option is not set and a small tensor takes smaller ones, there are at most 256 in all: with buckets of
  * at least one default tile of 32768 elements every n below 2^31 fits) and at most 2^18 buckets; beyond either the call returns
  * SRS_ERR_TOO_LARGE and launches nothing.  Every context on one GPU shares that GPU's array: two such calls that
- * overlap in time on one GPU (different streams or different contexts) race; order them on one stream.  The
- * array keeps the previous call's contents; where a bucket has more than one tile, a small kernel at the head of the call
- * clears what the call uses, and where none has, neither array is used.
+ * overlap in time on one GPU (different streams or different contexts) race; order them on one stream (srs_status
+ * puts the array in order again where it reports SRS_FLAG_TIMEOUT after such a race).  Nothing is cleared between calls:
+ * every call leaves the array as the next one needs it, and where no bucket has more than one tile it is not used.
  */
 int srs_extract_noalloc(srs_ctx *ctx, void *old_snapshot, const void *new_w, uint64_t n, uint64_t bucket_elems,
                         int32_t *I, uint16_t *V, uint32_t *counts, uint64_t cap, void *stream);

@@ -38,25 +38,28 @@ typedef srs::BasicDeviceGuard<HipDeviceApi> DeviceGuard;
 
 }  // namespace
 
-// Scratch of the entry point that may not allocate (srs_extract_noalloc): tile status words, then ticket counters.
+// Scratch of the entry point that may not allocate (srs_extract_noalloc): tile status words, ticket counters, then the epoch.
+// Like a context's own scratch it starts out as zeros and every launch leaves it ready for the next.
 // One copy per GPU, held until the process ends.  In host code `scratch` is only a handle for
 // hipGetSymbolAddress: srs_create resolves it once per context, with the context's device current, and everything
 // else (kernel arguments included) goes through the pointer kept in the context.
 namespace {
 constexpr uint64_t kStaticTiles = 1ull << 20;          // status words: 8 MiB
 constexpr uint64_t kStaticTicketWords = 1ull << 18;    // ticket counters: 1 MiB
-constexpr uint64_t kStaticScratchBytes = kStaticTiles * sizeof(unsigned long long) + kStaticTicketWords * sizeof(uint32_t);
+constexpr uint64_t kStaticScratchBytes = kStaticTiles * sizeof(unsigned long long) + kStaticTicketWords * sizeof(uint32_t) + 256;
 }  // namespace
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
 struct srs_ctx {
     int device = 0;
     unsigned char *static_scratch = nullptr;   // this device's address of `scratch`
+    bool used_static = false;               // a call of this context has used it
     unsigned long long *status = nullptr;   // tile status words
     uint64_t status_cap = 0;
     uint32_t *tickets = nullptr;            // per-bucket ticket counters
     uint64_t tickets_cap = 0;               // in words
-    uint32_t *flags = nullptr;              // device flag word (own 256-byte allocation)
+    uint32_t *flags = nullptr;              // device flag word, the epoch kEpochWord words behind it; behind these 256 bytes, in the
+                                            // same allocation, the first kFirst* ticket counters and status words
     uint32_t *vc_scratch = nullptr;         // value codec: per-bucket histograms and codes
     uint64_t vc_cap = 0;                    // in words
     uint32_t spin_limit = 1u << 24;
@@ -73,6 +76,7 @@ struct srs_plan {
     uint64_t total = 0, be = 0;
     uint32_t ntensors = 0, nbuckets = 0, nsegments = 0, ntiles = 0, tile_elems = 0;
     uint32_t max_bucket_tiles = 0;          // most tiles in any one bucket
+    uint32_t chained_buckets = 0;           // buckets of more than one tile
     TileDesc *d_tiles = nullptr;
     uint64_t *d_tensor_base = nullptr;      // [ntensors] packed position of each tensor's element 0
     WgInfo *d_wg_info = nullptr;            // [ntiles] bucket served by each workgroup of extract, and that bucket's tiles
@@ -89,56 +93,79 @@ struct srs_plan {
 
 namespace {
 
+constexpr uint32_t kEpochWord = 32;         // in the allocation of the flag word; srs_status clears the first two words only
+
 // ticket counters sit 256 bytes apart (atomics on one cache line serialise) unless there are very
 // many buckets, which only happens with bucket sizes far below a tile
 uint32_t ticket_stride_for(uint64_t nb) { return nb <= 65536 ? 64u : 1u; }
 
-// Clears the ticket counters and status words on the stream; nothing to do where no bucket has a second tile, as neither is
-// used then.
-int clear_extract_scratch(uint32_t *tickets, uint64_t nb, uint32_t stride, unsigned long long *status, uint64_t ntiles,
-                          bool one_tile_buckets, hipStream_t st) {
-    if (one_tile_buckets) return SRS_OK;
-    const uint64_t n = ntiles > nb ? ntiles : nb;
-    const uint32_t threads = 256;
-    hipLaunchKernelGGL(prepare_extract_kernel, dim3((uint32_t)((n + threads - 1) / threads)), dim3(threads), 0, st,
-                       tickets, nb, stride, status, ntiles);
-    SRS_HIP(hipGetLastError());
+// What a context starts out with, in one allocation: enough for half a billion elements in 128 buckets, so that a new context's
+// first calls need not allocate.
+constexpr uint64_t kFirstTickets = 128 * 64, kFirstStatus = 16384;
+constexpr uint64_t kFirstBytes = 256 + kFirstTickets * sizeof(uint32_t) + kFirstStatus * sizeof(unsigned long long);
+
+// A zeroed array of at least `need` elements in *p (capacity *cap; an array of more than `first` elements is an allocation of its
+// own), which may replace a smaller one: allocates and synchronises.
+template <class T>
+int grow_zeroed(T **p, uint64_t *cap, uint64_t need, uint64_t slack, uint64_t first) {
+    if (need <= *cap) return SRS_OK;
+    SRS_HIP(hipDeviceSynchronize());
+    if (*p && *cap > first) SRS_HIP(hipFree(*p));
+    *p = nullptr; *cap = 0;
+    const uint64_t n = (need + need / 4 + slack) / 2 * 2;
+    SRS_HIP(hipMalloc((void **)p, n * sizeof(T)));
+    if (hipMemset(*p, 0, n * sizeof(T)) != hipSuccess || hipDeviceSynchronize() != hipSuccess) {
+        (void)hipGetLastError(); (void)hipFree(*p); *p = nullptr;
+        return SRS_ERR_HIP;
+    }
+    *cap = n;
     return SRS_OK;
 }
 
-// make room for ntiles status words and nb ticket counters, then clear both on the stream
-int prepare_extract(srs_ctx *ctx, uint64_t ntiles, uint64_t nb, bool one_tile_buckets, hipStream_t st, uint32_t *stride) {
-    *stride = ticket_stride_for(nb);
-    const uint64_t words = nb * (*stride);
-    if (words > ctx->tickets_cap) {
-        SRS_HIP(hipDeviceSynchronize());
-        if (ctx->tickets) SRS_HIP(hipFree(ctx->tickets));
-        ctx->tickets = nullptr; ctx->tickets_cap = 0;
-        const uint64_t cap = words + words / 4 + 4096;
-        SRS_HIP(hipMalloc((void **)&ctx->tickets, cap * sizeof(uint32_t)));
-        ctx->tickets_cap = cap;
-    }
-    if (ntiles > ctx->status_cap) {
-        SRS_HIP(hipDeviceSynchronize());
-        if (ctx->status) SRS_HIP(hipFree(ctx->status));
-        ctx->status = nullptr; ctx->status_cap = 0;
-        const uint64_t cap = ntiles + ntiles / 4 + 1024;
-        SRS_HIP(hipMalloc((void **)&ctx->status, cap * sizeof(unsigned long long)));
-        ctx->status_cap = cap;
-    }
-    return clear_extract_scratch(ctx->tickets, nb, *stride, ctx->status, ntiles, one_tile_buckets, st);
+// The status words, ticket counters and epoch of an extract launch of ntiles tiles in nb buckets, `chained` of which have more
+// than one tile (none: nothing of it is used).  Nothing is cleared between launches.
+int extract_scratch(srs_ctx *ctx, uint64_t ntiles, uint64_t nb, uint32_t chained, ExtractArgs &a) {
+    a.chained = chained;
+    if (chained == 0) return SRS_OK;
+    a.ticket_stride = ticket_stride_for(nb);
+    int rc = grow_zeroed(&ctx->tickets, &ctx->tickets_cap, nb * a.ticket_stride, 4096, kFirstTickets);
+    if (rc == SRS_OK) rc = grow_zeroed(&ctx->status, &ctx->status_cap, ntiles, 1024, kFirstStatus);
+    a.tickets = ctx->tickets; a.status = ctx->status; a.status_cap = ctx->status_cap;
+    a.epoch = ctx->flags + kEpochWord;
+    return rc;
 }
 
 // The same on the static scratch: nothing is allocated, sizes beyond the array are refused.  Ticket counters sit
 // 256 bytes apart while they fit, 4 bytes apart above that.
-int prepare_extract_static(srs_ctx *ctx, uint64_t ntiles, uint64_t nb, bool one_tile_buckets, hipStream_t st, uint32_t *stride,
-                           unsigned long long **status, uint32_t **tickets) {
+int extract_scratch_static(srs_ctx *ctx, uint64_t ntiles, uint64_t nb, uint32_t chained, ExtractArgs &a) {
     if (!ctx->static_scratch) return SRS_ERR_HIP;
     if (ntiles > kStaticTiles || nb > kStaticTicketWords) return SRS_ERR_TOO_LARGE;
-    *stride = (nb * 64u <= kStaticTicketWords) ? 64u : 1u;
-    *status = reinterpret_cast<unsigned long long *>(ctx->static_scratch);
-    *tickets = reinterpret_cast<uint32_t *>(ctx->static_scratch + kStaticTiles * sizeof(unsigned long long));
-    return clear_extract_scratch(*tickets, nb, *stride, *status, ntiles, one_tile_buckets, st);
+    a.chained = chained;
+    ctx->used_static = true;
+    a.ticket_stride = (nb * 64u <= kStaticTicketWords) ? 64u : 1u;
+    a.status = reinterpret_cast<unsigned long long *>(ctx->static_scratch);
+    a.status_cap = kStaticTiles;
+    a.tickets = reinterpret_cast<uint32_t *>(ctx->static_scratch + kStaticTiles * sizeof(unsigned long long));
+    a.epoch = a.tickets + kStaticTicketWords;
+    return SRS_OK;
+}
+
+int fill_zero(void *p, uint64_t bytes, hipStream_t st) {
+    const uint64_t n = bytes / sizeof(unsigned long long);
+    if (n == 0) return SRS_OK;
+    hipLaunchKernelGGL(fill_u64_kernel, dim3((uint32_t)((n + 255) / 256)), dim3(256), 0, st, (unsigned long long *)p, n, 0ull);
+    SRS_HIP(hipGetLastError());
+    return SRS_OK;
+}
+
+// After a look-back that gave up: every launch leaves the counters as the next one needs them also then, but where it gave up
+// because calls overlapped that may not, they may have been left anywhere.
+int rewind_scratch(srs_ctx *ctx, hipStream_t st) {
+    int rc = fill_zero(ctx->tickets, ctx->tickets_cap * sizeof(uint32_t), st);
+    if (rc == SRS_OK) rc = fill_zero(ctx->status, ctx->status_cap * sizeof(unsigned long long), st);
+    if (rc == SRS_OK) rc = fill_zero(ctx->flags + kEpochWord + kEpochClaimed, 8, st);
+    if (rc == SRS_OK && ctx->used_static) rc = fill_zero(ctx->static_scratch, kStaticScratchBytes, st);
+    return rc;
 }
 
 // One-byte elements: a tile of tile_elems elements is V = tile_elems / 4096 vectors per lane (16 elements each), so
@@ -214,7 +241,7 @@ struct Layout {
     std::vector<SegDesc> segs;
     std::vector<uint32_t> seg_begin, bucket_first, wg_bucket;
     std::vector<TileDesc> tiles;
-    uint32_t nbuckets = 0, max_bucket_tiles = 0;
+    uint32_t nbuckets = 0, max_bucket_tiles = 0, chained_buckets = 0;
 };
 
 int build_layout(const uint64_t *numel, uint32_t ntensors, uint64_t bucket_elems, uint32_t tile_elems, uint32_t group,
@@ -260,6 +287,7 @@ int build_layout(const uint64_t *numel, uint32_t ntensors, uint64_t bucket_elems
         for (uint32_t b = 0; b < L.nbuckets; ++b) {
             const uint32_t nt = L.bucket_first[b + 1] - L.bucket_first[b];
             if (nt > L.max_bucket_tiles) L.max_bucket_tiles = nt;
+            if (nt > 1) ++L.chained_buckets;
         }
         L.wg_bucket.reserve(L.tiles.size());
         std::vector<uint32_t> left;
@@ -484,13 +512,13 @@ int extract_single(srs_ctx *ctx, void *old_snapshot, const void *new_w, uint64_t
 
     ExtractArgs a;
     std::memset(&a, 0, sizeof(a));
-    int rc = static_scratch ? prepare_extract_static(ctx, ntiles, nb, ntiles == nb, st, &a.ticket_stride, &a.status, &a.tickets)
-                            : prepare_extract(ctx, ntiles, nb, ntiles == nb, st, &a.ticket_stride);
+    const uint64_t last_tiles = (last_len + T - 1) / T;
+    const uint32_t chained = (uint32_t)((tpb > 1 ? nb - 1 : 0) + (last_tiles > 1 ? 1 : 0));
+    int rc = static_scratch ? extract_scratch_static(ctx, ntiles, nb, chained, a) : extract_scratch(ctx, ntiles, nb, chained, a);
     if (rc != SRS_OK) return rc;
-    if (!static_scratch) { a.status = ctx->status; a.tickets = ctx->tickets; }
     a.old_w = (uint16_t *)old_snapshot; a.new_w = new_w; a.n = n;
     a.be = (uint32_t)bucket_elems; a.tiles_per_bucket = (uint32_t)tpb;
-    a.nb = (uint32_t)nb; a.last_tiles = (uint32_t)((last_len + T - 1) / T); a.group = (uint32_t)group;
+    a.nb = (uint32_t)nb; a.last_tiles = (uint32_t)last_tiles; a.group = (uint32_t)group;
     a.ntiles = (uint32_t)ntiles;
     a.I = I; a.V = (uint16_t *)V; a.counts = counts; a.cap = cap;
     a.flags = ctx->flags;
@@ -524,12 +552,12 @@ int extract_multi(srs_ctx *ctx, srs_plan *plan, const srs_tensor_pair *t,
 
     ExtractArgs a;
     std::memset(&a, 0, sizeof(a));
-    int rc = prepare_extract(ctx, plan->ntiles, plan->nbuckets, plan->max_bucket_tiles == 1, st, &a.ticket_stride);
+    int rc = extract_scratch(ctx, plan->ntiles, plan->nbuckets, plan->chained_buckets, a);
     if (rc != SRS_OK) return rc;
     a.tiles = plan->d_tiles; a.ptrs = plan->d_pairs; a.ntiles = plan->ntiles;
     a.wg_info = plan->d_wg_info; a.bucket_first = plan->d_bucket_first; a.nb = plan->nbuckets;
     a.I = I; a.V = (uint16_t *)V; a.counts = counts; a.cap = cap;
-    a.status = ctx->status; a.tickets = ctx->tickets; a.flags = ctx->flags;
+    a.flags = ctx->flags;
     a.spin_limit = ctx->spin_limit;
     a.bitmap = const_cast<uint32_t *>(bitmap); a.bitmap_words = (plan->total + 31) / 32; a.tensor_base = plan->d_tensor_base;
     rc = launch_extract<true>(ctx, plan->tile_elems, a, st, src, eb);
@@ -564,12 +592,16 @@ int srs_create(srs_ctx **out, int device) {
     srs_ctx *ctx = new (std::nothrow) srs_ctx();
     if (!ctx) return SRS_ERR_NOMEM;
     ctx->device = device;
-    if (hipMalloc((void **)&ctx->flags, 256) != hipSuccess) {
+    if (hipMalloc((void **)&ctx->flags, kFirstBytes) != hipSuccess) {
         (void)hipGetLastError(); delete ctx; return SRS_ERR_HIP;
     }
-    if (hipMemset(ctx->flags, 0, 256) != hipSuccess || hipDeviceSynchronize() != hipSuccess) {
+    if (hipMemset(ctx->flags, 0, kFirstBytes) != hipSuccess || hipDeviceSynchronize() != hipSuccess) {
         (void)hipGetLastError(); (void)hipFree(ctx->flags); delete ctx; return SRS_ERR_HIP;
     }
+    ctx->tickets = ctx->flags + 64;
+    ctx->tickets_cap = kFirstTickets;
+    ctx->status = reinterpret_cast<unsigned long long *>(ctx->tickets + kFirstTickets);
+    ctx->status_cap = kFirstStatus;
     // this device's copy of the static scratch array (each GPU has its own, at its own address)
     void *sp = nullptr;
     if (hipGetSymbolAddress(&sp, HIP_SYMBOL(scratch)) != hipSuccess || !sp || ((uintptr_t)sp & 255u)) {
@@ -584,8 +616,8 @@ int srs_destroy(srs_ctx *ctx) {
     if (!ctx) return SRS_ERR_INVALID;
     DeviceGuard device_guard_(ctx->device);
     (void)hipDeviceSynchronize();
-    if (ctx->status) (void)hipFree(ctx->status);
-    if (ctx->tickets) (void)hipFree(ctx->tickets);
+    if (ctx->status && ctx->status_cap > kFirstStatus) (void)hipFree(ctx->status);
+    if (ctx->tickets && ctx->tickets_cap > kFirstTickets) (void)hipFree(ctx->tickets);
     if (ctx->vc_scratch) (void)hipFree(ctx->vc_scratch);
     if (ctx->flags) (void)hipFree(ctx->flags);
     delete ctx;
@@ -622,7 +654,7 @@ int srs_status(srs_ctx *ctx, uint32_t *flags, void *stream) {
     SRS_HIP(hipStreamSynchronize(st));
     hipLaunchKernelGGL(fill_u64_kernel, dim3(1), dim3(64), 0, st, (unsigned long long *)ctx->flags, (uint64_t)1, 0ull);
     SRS_HIP(hipGetLastError());
-    return SRS_OK;
+    return (*flags & kFlagTimeout) ? rewind_scratch(ctx, st) : SRS_OK;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -718,6 +750,7 @@ int srs_plan_create(srs_ctx *ctx, const uint64_t *numel, uint32_t ntensors, uint
         delete p; return SRS_ERR_NOMEM;
     }
     p->max_bucket_tiles = L.max_bucket_tiles;
+    p->chained_buckets = L.chained_buckets;
     std::vector<SegDesc> &segs = L.segs;
     std::vector<uint32_t> &seg_begin = L.seg_begin, &bucket_first = L.bucket_first, &wg_bucket = L.wg_bucket;
     std::vector<TileDesc> &tiles = L.tiles;
