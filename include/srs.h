@@ -72,7 +72,8 @@ typedef enum {
 #define SRS_OPT_SPIN_LIMIT 1   /* max polls of a predecessor tile before SRS_FLAG_TIMEOUT (default 1<<24) */
 #define SRS_OPT_TILE_ELEMS 2   /* elements per extract tile: 4096, 8192, 16384 or 32768 (default for plans; tuning;
                                   affects plans created afterwards).  Until it is set, the calls on a single tensor
-                                  take smaller tiles for small tensors, never more than 256 because of it. */
+                                  take smaller tiles for small tensors and small buckets: never more than 768 tiles
+                                  because of it, or one for each bucket. */
 #define SRS_OPT_REFRESH_GROUP 3 /* snapshot refresh: 8 (default) = aligned 128-byte lines of the snapshot that hold a
                                   change are rewritten from the new weights (unchanged elements get the value they
                                   have).  Only elements of the tensor are stored; of a line that two waves or tiles
@@ -130,7 +131,7 @@ int srs_extract(srs_ctx *ctx, void *old_snapshot, const void *new_w, uint64_t n,
  * tile status words and ticket counters live in a static device array of the library (9 MiB per GPU, held until
  * the process ends) instead of the context's growable scratch, so the call never allocates, frees or
  * synchronises, whatever its size.  Limits: at most 2^20 tiles (a bucket has ceil(bucket_elems / SRS_OPT_TILE_ELEMS)
- * tiles; where the option is not set and a small tensor takes smaller ones, there are at most 256 in all: with buckets of
+ * tiles; where the option is not set and a small tensor takes smaller ones, there are at most 768, or one for each bucket: with buckets of
  * at least one default tile of 32768 elements every n below 2^31 fits) and at most 2^18 buckets; beyond either the call returns
  * SRS_ERR_TOO_LARGE and launches nothing.  Every context on one GPU shares that GPU's array: two such calls that
  * overlap in time on one GPU (different streams or different contexts) race; order them on one stream (srs_status

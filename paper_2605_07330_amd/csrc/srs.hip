@@ -461,27 +461,29 @@ uint64_t single_tiles(uint64_t n, uint64_t be, uint64_t tile) {
     return full * ((be + tile - 1) / tile) + (n - full * be + tile - 1) / tile;
 }
 
-// Elements per tile of a single tensor for which the caller chose none.  The largest tile streams best, but leaves CUs
-// idle where there are fewer tiles than CUs, and its serial part (16 vectors ranked per lane) is what small calls
-// consist of: the smallest tile that makes no more than one per CU is taken.  A tile that holds whole buckets goes before
-// it up to half the largest, as it saves the launch that clears tickets and status words.
-// Extract at 1 % changed with its clearing launch, refreshed in place, tiles of 4096 / 8192 / 16384 / 32768, us:
-// 4 K elements 5.5 / 5.8 / 7.0 / 8.3, 64 K in one bucket 7.0 / 7.7 / 9.6 / 13.5, 1 M in four 8.4 / 8.5 / 10.3 / 14.6,
-// 4 M in four 15.4 / 12.5 / 11.4 / 15.1, 16 M in four 43.9 / 34.9 / 28.6 / 25.6, 256 M in one 794 / 440 / 317 / 273.
-// One-byte elements: a tile takes half as long to read, and the chain of the tiles of one bucket shows from 192 on.  16384 /
-// 32768 for 4 M elements in one bucket (256 / 128 tiles), snapshot rotated, us: 0.03 % 10.5 / 10.0, 3 % 11.5 / 11.8; 8192 /
-// 16384 for 2 M (256 / 128): 9.8 / 8.4, 10.1 / 9.2; 16384 / 32768 for 3 M (192 / 96), refreshed in place: 9.9 / 10.3, 11.3 / 12.4.
-constexpr uint64_t kFewTiles = 256, kFewTilesU8 = 192;
-
+// Elements per tile of a single tensor for which the caller chose none.  The largest tile streams best, but leaves CUs idle where
+// there are few of them, and its serial part (16 vectors ranked per lane) is what small calls consist of.  So the smallest tile
+// is taken that makes no more than three workgroups per CU, and in one bucket no more than its chain passes on without
+// showing: 128 tiles of 4096, 256 of the larger ones.  A tile never exceeds the bucket's own size rounded up, whatever the
+// number of buckets, and buckets of up to 8192 elements are one tile each, as that saves the ticket.
+// Extract at 1 % changed, refreshed in place, tiles of 4096 / 8192 / 16384 / 32768, us (replayed from a graph):
+// 8 K elements 4.5 / 3.7 / 5.2 / 8.1, 16 K 4.7 / 5.2 / 5.2 / 8.1, 64 K 5.1 / 6.1 / 8.2 / 12.8, 1 M in one bucket 8.6 / 7.7 /
+// 9.0 / 13.9, in four 6.5 / 6.5 / 8.3 / 13.7, 2 M in one 12.9 / 9.3 / 9.8 / 14.0, 4 M in one 21.7 / 14.3 / 11.7 / 14.6, in four
+// 12.0 / 9.0 / 9.9 / 13.5, in 1024 5.2 / 6.4 / 9.2 / 18.4, 6 M in twenty 11.8 / 9.5 / 10.9 / 13.7, 12 M in six 25.5 / 21.6 /
+// 16.3 / 18.5, 8 M in one 37.5 / 25.3 / 17.8 / 17.3, in eight 22.8 / 15.4 / 13.3 / 14.7, 16 M in four 39.8 / 31.6 / 24.5 / 22.8.
+// One-byte elements: a tile takes half as long to read; no more than one per CU, 192 in one bucket, and buckets of up to 16384
+// elements are one tile.  8192 / 16384 / 32768, us: 16 K 4.9 / 4.3 / 6.1, 1 M in one bucket 6.5 / 6.7 / 8.5, 2 M 8.6 / 7.4 / 8.7, 4 M 12.6 /
+// 9.2 / 9.4, in four 7.5 / 7.2 / 8.2, 8 M in one 21.9 / 14.1 / 11.4.
 uint32_t single_tile_elems(const srs_ctx *ctx, uint64_t n, uint64_t be, int eb) {
     if (ctx->tile_set) return ctx->tile_elems;
-    uint32_t best = 0;
+    const uint64_t bucket = be < n ? be : n, most = (eb == 1) ? 256 : 768, alone = (eb == 1) ? 16384 : 8192;
     for (uint32_t tile = (eb == 1) ? 8192u : 4096u; tile < ctx->tile_elems; tile *= 2) {
-        if (single_tiles(n, be, tile) > kFewTiles) continue;
-        if (be <= tile || n <= tile) return tile;
-        if (!best && (eb == 2 || single_tiles(be < n ? be : n, be, tile) <= kFewTilesU8)) best = tile;
+        if (bucket <= tile) return tile;
+        if (bucket <= alone) continue;                     // a larger one holds it whole
+        const uint64_t chain = (eb == 1) ? 192 : (tile == 4096) ? 128 : 256;
+        if (single_tiles(n, be, tile) <= most && single_tiles(bucket, bucket, tile) <= chain) return tile;
     }
-    return best ? best : ctx->tile_elems;
+    return ctx->tile_elems;
 }
 
 int extract_single(srs_ctx *ctx, void *old_snapshot, const void *new_w, uint64_t n, uint64_t bucket_elems,
