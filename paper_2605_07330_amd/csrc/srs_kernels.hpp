@@ -838,7 +838,8 @@ __global__ __launch_bounds__(kThreads, waves_per_simd(V, MULTI, SRC, EB)) void e
 // stages their tile-local positions in LDS in rank order, and only then fetches the values, one 2-byte gather
 // per pair, balanced over the 256 threads and written out coalesced next to the indices.  Memory traffic is the
 // bitmap plus the lines that hold a marked element instead of the whole weight set.
-// E = elements per thread (tile of the plan / 256); thread t owns the tile-local positions [t*E, (t+1)*E).
+// E = elements per thread (tile of the plan / 256); thread t owns the tile-local positions [t*E, (t+1)*E).  NT: the gathers
+// carry the non-temporal hint.
 // ---------------------------------------------------------------------------------------------
 
 // the nbits (1..32) bitmap bits of packed positions g .. g+nbits-1, bit k of the result for position g + k
@@ -851,22 +852,24 @@ __device__ __forceinline__ uint32_t bitmap_bits32(const uint32_t *bitmap, uint64
     return nbits >= 32u ? bits : (bits & ((1u << nbits) - 1u));
 }
 
-template <int E>
+template <int E, bool NT>
 __global__ __launch_bounds__(kThreads) void extract_marked_kernel(const ExtractArgs a) {
     static_assert(E == 16 || E == 32 || E == 64 || E == 128, "tile of 4096 .. 32768 elements");
     constexpr int NW = (E + 31) / 32;                    // mask words per thread
     constexpr uint32_t CH = (E < 32) ? (uint32_t)E : 32u; // elements per mask word
-    constexpr int kGather = 4;                           // gathers in flight per thread in the write-out loop
+    constexpr int kGather = (int)(kStage / kThreads);    // gathers in flight per thread
+    static_assert(E * kThreads <= 65536, "positions and values share a word");
     __shared__ uint32_t s_ticket;
     __shared__ uint32_t s_wave_total[kWaves];
     __shared__ uint32_t s_excl;
-    __shared__ uint32_t s_stage[kStage];                 // tile-local positions in rank order
+    __shared__ uint32_t s_stage[kStage];                 // tile-local positions in rank order, then position << 16 | value
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const uint32_t wave = uniform((uint32_t)tid >> 6);
 
     // ---- bucket, ticket, tile: as in extract_kernel (tensor lists only)
-    const WgInfo wi = a.wg_info[blockIdx.x];
-    const uint32_t bucket = wi.bucket, first_tile = wi.first_tile, bucket_tiles = wi.ntiles;
+    const auto *wi = as_table(a.wg_info + blockIdx.x);
+    const uint32_t bucket = wi->bucket, first_tile = wi->first_tile, bucket_tiles = wi->ntiles;
     uint32_t k = 0, epoch = 0;
     const bool chained = bucket_tiles > 1;
     if (chained) {
@@ -878,23 +881,34 @@ __global__ __launch_bounds__(kThreads) void extract_marked_kernel(const ExtractA
     }
     const uint32_t tile = first_tile + k;
     const bool last = (k == bucket_tiles - 1);
-    const TileDesc d = a.tiles[tile];
-    const gptr<const uint16_t> pn = (gptr<const uint16_t>)a.ptrs[d.tensor].new_w + d.tensor_off;
-    const uint32_t len = d.len, idx_base = d.bucket_off;
-    const uint64_t g0 = a.tensor_base[d.tensor] + d.tensor_off;      // packed position of the tile's first element
+    const auto *d = as_table(a.tiles + tile);
+    const uint32_t tensor = d->tensor, tensor_off = d->tensor_off, len = d->len, idx_base = d->bucket_off;
+    const gptr<const uint16_t> pn = (gptr<const uint16_t>)as_global(as_table(a.ptrs + tensor)->new_w) + tensor_off;
+    const uint64_t g0 = *as_table(a.tensor_base + tensor) + tensor_off;      // packed position of the tile's first element
 
-    // ---- this thread's slice of the bitmap and its count
+    // ---- this thread's slice of the bitmap and its count: one 16-byte load and the word behind it where the slice is whole
     const uint32_t e0 = (uint32_t)tid * E;
     uint32_t m[NW];
     uint32_t mine = 0;
+    const uint64_t w0 = (g0 + e0) >> 5;
+    const uint32_t sh = (uint32_t)(g0 & 31u);            // e0 is a multiple of 32 there
+    if (NW == 4 && e0 + E <= len && w0 + 4 < a.bitmap_words) {
+        const u32x4 q = load16_any<false>((gptr<const uint32_t>)a.bitmap + w0);
+        const uint32_t next = a.bitmap[w0 + 4];
+        const uint32_t x[5] = {q.x, q.y, q.z, q.w, next};
 #pragma unroll
-    for (int c = 0; c < NW; ++c) {
-        const uint32_t e = e0 + c * 32u;
-        const uint32_t left = (e < len) ? (len - e) : 0u;
-        const uint32_t nbits = left < CH ? left : CH;
-        m[c] = nbits ? bitmap_bits32(a.bitmap, a.bitmap_words, g0 + e, nbits) : 0u;
-        mine += __popc(m[c]);
+        for (int c = 0; c < NW; ++c) m[c] = (uint32_t)((((unsigned long long)x[c + 1] << 32) | x[c]) >> sh);
+    } else {
+#pragma unroll
+        for (int c = 0; c < NW; ++c) {
+            const uint32_t e = e0 + c * 32u;
+            const uint32_t left = (e < len) ? (len - e) : 0u;
+            const uint32_t nbits = left < CH ? left : CH;
+            m[c] = nbits ? bitmap_bits32(a.bitmap, a.bitmap_words, g0 + e, nbits) : 0u;
+        }
     }
+#pragma unroll
+    for (int c = 0; c < NW; ++c) mine += __popc(m[c]);
     uint32_t counted = 0;
     if (chained && last && tid == 0) counted = count_claimed(a);     // returns behind the bitmap
     const uint32_t inc = wave_inclusive_scan(mine);                  // at most 64 * 128 per wave
@@ -903,40 +917,37 @@ __global__ __launch_bounds__(kThreads) void extract_marked_kernel(const ExtractA
     __syncthreads();
     uint32_t wave_base = 0, tile_total = 0;
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w) {
-        const uint32_t t = s_wave_total[w];
+    for (uint32_t w = 0; w < (uint32_t)kWaves; ++w) {
+        const uint32_t t = uniform(s_wave_total[w]);
         wave_base += (w < wave) ? t : 0u;
         tile_total += t;
     }
-    tile_total = uniform(tile_total);
+    const uint32_t first = wave_base + (inc - mine);                 // rank of this thread's first pair
 
-    // ---- chain with the earlier tiles of the bucket
-    if (wave == 0) {
+    // ---- chain with the earlier tiles of the bucket, as in extract_kernel: published now, looked back from later
+    if (tid == 0 && !last) status_store(a.status + tile, status_word(epoch, tile == first_tile ? kStPrefix : kStAgg, tile_total));
+    auto settle = [&]() -> uint32_t {
         uint32_t excl = 0;
-        if (tile == first_tile) {
-            if (lane == 0 && !last) status_store(a.status + tile, status_word(epoch, kStPrefix, tile_total));
-        } else {
-            if (lane == 0 && !last) status_store(a.status + tile, status_word(epoch, kStAgg, tile_total));
+        if (tile != first_tile) {
             excl = look_back(a, epoch, tile, first_tile, lane);
             if (lane == 0 && !last) status_store(a.status + tile, status_word(epoch, kStPrefix, excl + tile_total));
         }
-        if (chained && last) raise_epoch(a, epoch, counted, lane);
-        if (lane == 0) {
-            s_excl = excl;
-            if (last) {
-                const uint32_t c = excl + tile_total;
+        if (last) {
+            const uint32_t c = excl + tile_total;
+            if (lane == 0) {
                 a.counts[bucket] = c;
                 if ((uint64_t)c > a.cap) atomicOr(a.flags, kFlagOverflow);
             }
+            if (chained) raise_epoch(a, epoch, counted, lane);
         }
-    }
+        return excl;
+    };
 
-    // ---- positions into LDS in rank order, then gather + coalesced write-out, kStage pairs per round
     int32_t *const Ib = a.I + (uint64_t)bucket * a.cap;
     uint16_t *const Vb = a.V + (uint64_t)bucket * a.cap;
-    for (uint32_t r0 = 0; r0 < tile_total; r0 += kStage) {
-        uint32_t rank = wave_base + (inc - mine) - r0;               // wraps for pairs of earlier rounds: skipped below
-        const uint32_t first = wave_base + (inc - mine);
+    // positions of the pairs r0 .. r0 + kStage - 1 into LDS in rank order
+    auto stage_round = [&](uint32_t r0) {
+        uint32_t rank = first - r0;                                  // wraps for pairs of earlier rounds: skipped below
         const bool in_round = first < r0 + kStage && first + mine > r0;   // this thread has pairs of this round
 #pragma unroll
         for (int c = 0; c < NW; ++c) {
@@ -948,26 +959,60 @@ __global__ __launch_bounds__(kThreads) void extract_marked_kernel(const ExtractA
                 ++rank;
             }
         }
-        __syncthreads();
-        const uint32_t excl = s_excl;
-        const uint32_t nst = (tile_total - r0 < kStage) ? (tile_total - r0) : kStage;
-        for (uint32_t k0 = tid; k0 < nst; k0 += kGather * kThreads) {
-            uint32_t local[kGather];
-            uint16_t val[kGather];
+    };
+    // their values, spread evenly over the threads and all in flight together, go back to LDS beside the positions
+    auto gather_round = [&](uint32_t n) {
+        uint32_t local[kGather], val[kGather];
 #pragma unroll
-            for (int u = 0; u < kGather; ++u) {
-                const uint32_t kk = k0 + u * kThreads;
-                local[u] = (kk < nst) ? s_stage[kk] : 0xFFFFFFFFu;
-            }
-#pragma unroll
-            for (int u = 0; u < kGather; ++u) val[u] = (local[u] < len) ? pn[local[u]] : (uint16_t)0;
-#pragma unroll
-            for (int u = 0; u < kGather; ++u) {
-                const uint64_t r = (uint64_t)excl + r0 + k0 + u * kThreads;
-                if (local[u] < len && r < a.cap) { Ib[r] = (int32_t)(idx_base + local[u]); Vb[r] = val[u]; }
-            }
+        for (int u = 0; u < kGather; ++u) {
+            const uint32_t q = (uint32_t)tid + u * kThreads;
+            local[u] = 0;
+            val[u] = 0;
+            if (q < n) local[u] = s_stage[q];
+            if (q < n && local[u] < len) val[u] = NT ? __builtin_nontemporal_load(pn + local[u]) : pn[local[u]];
         }
-        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < kGather; ++u) {
+            const uint32_t q = (uint32_t)tid + u * kThreads;
+            if (q < n) s_stage[q] = (local[u] << 16) | val[u];
+        }
+    };
+    auto write_staged = [&](uint32_t from, uint32_t step, uint64_t rank0, uint32_t n) {
+        for (uint32_t q = from; q < n; q += step) {
+            const uint32_t ent = s_stage[q], local = ent >> 16;
+            const uint64_t r = rank0 + q;
+            if (local < len && r < a.cap) { Ib[r] = (int32_t)(idx_base + local); Vb[r] = (uint16_t)(ent & 0xFFFFu); }
+        }
+    };
+
+    if (tile_total <= kStage) {
+        // The values do not wait for the tile's place in the bucket; when they are there, three of the four waves end, and
+        // wave 0 looks back and writes out.  (Before, the gathers waited for the look-back: the chain of latencies from the
+        // bitmap's address to the payload bounds this kernel, at eight workgroups per CU.)  Before / now, us: four
+        // 30B-A3B-shaped layers at 1.2 % marked 752 / 653, four 32B-shaped at 0.07 % 297 / 197, eight 8B-shaped at 3 % 667 / 607,
+        // one at 0.6 % 50 / 41, 300 odd-sized tensors at 2 % 43 / 33; with all four waves to the end 701 for the first.
+        stage_round(0);
+        lds_barrier();
+        gather_round(tile_total);
+        lds_barrier();
+        if (wave != 0) return;
+        const uint32_t excl = settle();
+        write_staged((uint32_t)lane, 64, excl, tile_total);
+        return;
+    }
+    if (wave == 0) {
+        const uint32_t e = settle();
+        if (lane == 0) s_excl = e;
+    }
+    __syncthreads();
+    const uint32_t excl = uniform(s_excl);
+    for (uint32_t r0 = 0; r0 < tile_total; r0 += kStage) {
+        const uint32_t n = (tile_total - r0 < kStage) ? (tile_total - r0) : kStage;
+        stage_round(r0);
+        lds_barrier();
+        gather_round(n);
+        write_staged((uint32_t)tid, kThreads, (uint64_t)excl + r0, n);       // the thread's own entries
+        lds_barrier();
     }
 }
 

@@ -55,3 +55,68 @@ def test_pairs_of_a_tile_around_the_stage(kind, tile, mode):
         assert np.array_equal(t.cpu().numpy().view(dt), old if mode == "rotate" else want_old)
     finally:
         ctx.close()
+
+
+@pytest.mark.parametrize("tile", [32768, 16384, 8192, 4096])
+@pytest.mark.parametrize("lead", [0, 5, 31, 32])
+def test_marked_pairs_of_a_tile_around_the_stage(tile, lead):
+    """The same for the payload of a bitmap, the tiles starting `lead` bits into a word of it; the last slice ends with the bitmap."""
+    from paper_2605_07330_amd import srs
+    print(f"case marked tile={tile} lead={lead}", flush=True)
+    rng = np.random.default_rng(tile + lead)
+    numel = ([lead] if lead else []) + [40 * tile + 96, 3 * tile // 2 + 7]
+    n, be = sum(numel), 25 * tile
+    mask = np.zeros(n, bool)
+    for lo in range(lead, n, tile):
+        hi = min(n, lo + tile)
+        mask[lo + rng.permutation(hi - lo)[:min(int(rng.choice(COUNTS)), hi - lo)]] = True
+    mask[-1] = True
+    new = rng.integers(0, 1 << 16, n).astype(np.uint16)
+    split = lambda a: [np.ascontiguousarray(x) for x in np.split(a, np.cumsum(numel)[:-1])]  # noqa: E731
+    bits = np.zeros(oracle.bitmap_words(n), np.uint32)
+    oracle.mark_multi(split(new ^ mask), split(new), numel, bits)
+    cap = 3000 * 25
+    want = oracle.extract_marked_multi(split(new), numel, be, bits, cap)[:3]
+    ctx = srs.Context(0)
+    try:
+        ctx.set_option(srs.OPT_TILE_ELEMS, tile)
+        plan = ctx.plan(numel, be)
+        flat = torch.from_numpy(new.view(np.int16)).to(DEV)
+        I, V, counts = srs.alloc_payload(plan.nbuckets, cap, DEV)
+        ctx.extract_marked_multi(plan, list(torch.split(flat, numel)), torch.from_numpy(bits.view(np.int32)).to(DEV), I, V, counts, cap)
+        assert ctx.status() == 0
+        wI, wV, wc = want
+        assert np.array_equal(counts.cpu().numpy().view(np.uint32), wc)
+        gI, gV = I.cpu().numpy().reshape(len(wc), cap), V.cpu().numpy().view(np.uint16).reshape(len(wc), cap)
+        for b, c in enumerate(wc):
+            assert np.array_equal(gI[b, :c], wI[b, :c]) and np.array_equal(gV[b, :c], wV[b, :c]), b
+        plan.close()
+    finally:
+        ctx.close()
+
+
+def test_marked_gather_of_a_large_list():
+    """More than 2^29 elements, whose gathers carry another cache hint: every value against the weights on the device."""
+    from paper_2605_07330_amd import srs
+    n, be = (1 << 29) + 12_345, 1 << 25
+    g = torch.Generator(device=DEV)
+    g.manual_seed(5)
+    new = torch.randint(-32768, 32768, (n,), dtype=torch.int16, device=DEV, generator=g)
+    bits = torch.zeros((n + 31) // 32, dtype=torch.int32, device=DEV)
+    word = torch.randint(0, bits.numel() - 1, (bits.numel() // 4,), device=DEV, generator=g).unique()
+    bits[word] = (1 << 17) | 5
+    at = (word[:, None] * 32 + torch.tensor([0, 2, 17], device=DEV)).flatten()
+    cap = be // 20
+    ctx = srs.Context(0)
+    try:
+        plan = ctx.plan([n - 999, 999], be)
+        I, V, counts = srs.alloc_payload(plan.nbuckets, cap, DEV)
+        ctx.extract_marked_multi(plan, list(torch.split(new, [n - 999, 999])), bits, I, V, counts, cap)
+        assert ctx.status() == 0
+        assert torch.equal(counts.to(torch.int64), torch.bincount(at // be, minlength=plan.nbuckets))
+        live = torch.arange(cap, device=DEV)[None, :] < counts[:, None]
+        pos = (I.view(plan.nbuckets, cap) + torch.arange(plan.nbuckets, device=DEV)[:, None] * be)[live]
+        assert torch.equal(pos, at) and torch.equal(V.view(plan.nbuckets, cap)[live], new[at])
+        plan.close()
+    finally:
+        ctx.close()
