@@ -103,6 +103,9 @@ uint32_t ticket_stride_for(uint64_t nb) { return nb <= 65536 ? 64u : 1u; }
 // first calls need not allocate.
 constexpr uint64_t kFirstTickets = 128 * 64, kFirstStatus = 16384;
 constexpr uint64_t kFirstBytes = 256 + kFirstTickets * sizeof(uint32_t) + kFirstStatus * sizeof(unsigned long long);
+// Behind it, room for the largest index difference of so many payload chunks (srs_encode_indices): fixed, so that the call
+// never allocates.  240 buckets of 424 k payload slots have 49,680.
+constexpr uint64_t kGapWords = 65536;
 
 // A zeroed array of at least `need` elements in *p (capacity *cap; an array of more than `first` elements is an allocation of its
 // own), which may replace a smaller one: allocates and synchronises.
@@ -606,7 +609,7 @@ int srs_create(srs_ctx **out, int device) {
     srs_ctx *ctx = new (std::nothrow) srs_ctx();
     if (!ctx) return SRS_ERR_NOMEM;
     ctx->device = device;
-    if (hipMalloc((void **)&ctx->flags, kFirstBytes) != hipSuccess) {
+    if (hipMalloc((void **)&ctx->flags, kFirstBytes + kGapWords * sizeof(uint32_t)) != hipSuccess) {
         (void)hipGetLastError(); delete ctx; return SRS_ERR_HIP;
     }
     if (hipMemset(ctx->flags, 0, kFirstBytes) != hipSuccess || hipDeviceSynchronize() != hipSuccess) {
@@ -1005,15 +1008,22 @@ int srs_encode_indices(srs_ctx *ctx, const int32_t *I, const uint32_t *counts, u
     SRS_ON_DEVICE(ctx->device);
     const uint64_t cpb = (cap + kApplyChunk - 1) / kApplyChunk;
     if ((uint64_t)nbuckets * cpb > 0x7fffffffull) return SRS_ERR_INVALID;
-    hipLaunchKernelGGL(zero_strided_kernel, dim3((nbuckets + 255) / 256), dim3(256), 0, st, max_gap, (uint64_t)nbuckets, 1u);
-    SRS_HIP(hipGetLastError());
+    uint32_t *const gaps = (uint64_t)nbuckets * cpb <= kGapWords ? ctx->flags + kFirstBytes / sizeof(uint32_t) : nullptr;
+    if (!gaps) {
+        hipLaunchKernelGGL(zero_strided_kernel, dim3((nbuckets + 255) / 256), dim3(256), 0, st, max_gap, (uint64_t)nbuckets, 1u);
+        SRS_HIP(hipGetLastError());
+    }
     ApplyArgs a;
     std::memset(&a, 0, sizeof(a));
     a.nb = nbuckets; a.chunks_per_bucket = (uint32_t)cpb;
     a.I = I; a.counts = counts; a.cap = cap; a.flags = ctx->flags; a.base_stride = base_stride;
     hipLaunchKernelGGL(encode_indices_kernel, dim3((uint32_t)((uint64_t)nbuckets * cpb)), dim3(kThreads), 0, st, a, D,
-                       max_gap, anchors);
+                       max_gap, anchors, gaps);
     SRS_HIP(hipGetLastError());
+    if (gaps) {
+        hipLaunchKernelGGL(max_gap_kernel, dim3(nbuckets), dim3(64), 0, st, gaps, counts, cap, (uint32_t)cpb, max_gap);
+        SRS_HIP(hipGetLastError());
+    }
     return SRS_OK;
 }
 

@@ -1,0 +1,41 @@
+"""Largest index difference of a bucket, from the chunk maxima kept in the context's fixed scratch and, where there are more chunks
+than it holds, from atomics: chunk edges, empty buckets, wide differences in the first, a middle and the last chunk."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.mark.parametrize("nb,cap", [(9, 2048 * 5), (9, 2048 * 5 + 3), (300, 2048 * 218), (301, 2048 * 218), (65536, 8), (65537, 8)])
+def test_chunk_maxima(nb, cap):
+    from paper_2605_07330_amd import srs
+    print(f"case nb={nb} cap={cap}", flush=True)
+    rng = np.random.default_rng(nb)
+    most = min(cap, 2048 * 5)
+    counts = rng.choice([0, 1, most // 2, most - 1, most], nb).astype(np.uint32)
+    counts[:5] = [most, 0, 1, most, most - 1]
+    I = np.zeros((nb, cap), np.int32)
+    for b in range(nb):
+        gaps = rng.integers(1, 300, counts[b])
+        if counts[b] and b % 3:
+            gaps[int(rng.choice([0, counts[b] // 2, counts[b] - 1]))] = int(rng.choice([32767, 32768, 70000]))
+        I[b, :counts[b]] = np.cumsum(gaps)
+    ctx = srs.Context(0)
+    try:
+        D, max_gap, anchors = srs.alloc_encoded(nb, cap, DEV)
+        max_gap.fill_(-7)
+        t = torch.from_numpy(I).to(DEV)
+        n = torch.from_numpy(counts.view(np.int32)).to(DEV)
+        for _ in range(2):
+            ctx.encode_indices(t, n, nb, cap, 0, D, max_gap, anchors)
+        assert ctx.status() == 0
+        want = np.array([np.diff(I[b, :c], prepend=0).max() if c else 0 for b, c in enumerate(counts)])
+        assert np.array_equal(max_gap.cpu().numpy()[:nb], want)
+        got = D.cpu().numpy().view(np.uint16).reshape(nb, cap)
+        for b in range(min(nb, 400)):
+            c = counts[b]
+            assert np.array_equal(got[b, :c], np.diff(I[b, :c], prepend=0).astype(np.uint16)), b
+    finally:
+        ctx.close()
