@@ -101,7 +101,7 @@ typedef enum {
 typedef struct srs_ctx srs_ctx;    /* per-stream scratch: tile status words, per-bucket ticket counters, flag word */
 typedef struct srs_plan srs_plan;  /* immutable bucket / segment / tile tables of one tensor list */
 
-/* Context.  srs_create selects `device`, allocates 420 KiB of device scratch and synchronises.
+/* Context.  srs_create selects `device`, allocates 930 KiB of device scratch and synchronises.
  * The tile-status and ticket arrays grow on demand inside srs_extract* (that one call then allocates
  * and synchronises the device; later calls of the same or smaller size do not). */
 int srs_create(srs_ctx **out, int device);

@@ -60,8 +60,9 @@ struct srs_ctx {
     uint64_t tickets_cap = 0;               // in words
     uint32_t *flags = nullptr;              // device flag word, the epoch kEpochWord words behind it; behind these 256 bytes, in the
                                             // same allocation, the first kFirst* ticket counters and status words
-    uint32_t *vc_scratch = nullptr;         // value codec: per-bucket histograms and codes
-    uint64_t vc_cap = 0;                    // in words
+    uint32_t *vc_scratch = nullptr;         // value codec: vc_cap buckets' histograms (all 0 between calls), then as many codes
+    uint64_t vc_cap = 0;                    // in buckets
+    bool vc_dirty = false;                  // a call ended between filling the histograms and emptying them
     uint32_t spin_limit = 1u << 24;
     uint32_t tile_elems = 32768;
     bool tile_set = false;                  // tile_elems was chosen by the caller: single tensors use it too, whatever their size
@@ -101,9 +102,10 @@ uint32_t ticket_stride_for(uint64_t nb) { return nb <= 65536 ? 64u : 1u; }
 
 // What a context starts out with, in one allocation: enough for half a billion elements in 128 buckets, so that a new context's
 // first calls need not allocate.
-constexpr uint64_t kFirstTickets = 128 * 64, kFirstStatus = 16384;
-constexpr uint64_t kFirstBytes = 256 + kFirstTickets * sizeof(uint32_t) + kFirstStatus * sizeof(unsigned long long);
-// Behind it, room for the largest index difference of so many payload chunks (srs_encode_indices): fixed, so that the call
+constexpr uint64_t kFirstTickets = 128 * 64, kFirstStatus = 16384, kFirstCodec = 256;
+constexpr uint64_t kFirstBytes = 256 + kFirstTickets * sizeof(uint32_t) + kFirstStatus * sizeof(unsigned long long) +
+                                 kFirstCodec * 256 * sizeof(uint32_t);                  // these begin as zeros
+// Behind it, the codes of the value coder for as many buckets, and room for the largest index difference of so many payload chunks (srs_encode_indices): fixed, so that the call
 // never allocates.  240 buckets of 424 k payload slots have 49,680.
 constexpr uint64_t kGapWords = 65536;
 
@@ -609,7 +611,7 @@ int srs_create(srs_ctx **out, int device) {
     srs_ctx *ctx = new (std::nothrow) srs_ctx();
     if (!ctx) return SRS_ERR_NOMEM;
     ctx->device = device;
-    if (hipMalloc((void **)&ctx->flags, kFirstBytes + kGapWords * sizeof(uint32_t)) != hipSuccess) {
+    if (hipMalloc((void **)&ctx->flags, kFirstBytes + (kFirstCodec * 256 + kGapWords) * sizeof(uint32_t)) != hipSuccess) {
         (void)hipGetLastError(); delete ctx; return SRS_ERR_HIP;
     }
     if (hipMemset(ctx->flags, 0, kFirstBytes) != hipSuccess || hipDeviceSynchronize() != hipSuccess) {
@@ -619,6 +621,8 @@ int srs_create(srs_ctx **out, int device) {
     ctx->tickets_cap = kFirstTickets;
     ctx->status = reinterpret_cast<unsigned long long *>(ctx->tickets + kFirstTickets);
     ctx->status_cap = kFirstStatus;
+    ctx->vc_scratch = reinterpret_cast<uint32_t *>(ctx->status + kFirstStatus);
+    ctx->vc_cap = kFirstCodec;
     // this device's copy of the static scratch array (each GPU has its own, at its own address)
     void *sp = nullptr;
     if (hipGetSymbolAddress(&sp, HIP_SYMBOL(scratch)) != hipSuccess || !sp || ((uintptr_t)sp & 255u)) {
@@ -635,7 +639,7 @@ int srs_destroy(srs_ctx *ctx) {
     (void)hipDeviceSynchronize();
     if (ctx->status && ctx->status_cap > kFirstStatus) (void)hipFree(ctx->status);
     if (ctx->tickets && ctx->tickets_cap > kFirstTickets) (void)hipFree(ctx->tickets);
-    if (ctx->vc_scratch) (void)hipFree(ctx->vc_scratch);
+    if (ctx->vc_scratch && ctx->vc_cap > kFirstCodec) (void)hipFree(ctx->vc_scratch);
     if (ctx->flags) (void)hipFree(ctx->flags);
     delete ctx;
     return SRS_OK;
@@ -1008,7 +1012,7 @@ int srs_encode_indices(srs_ctx *ctx, const int32_t *I, const uint32_t *counts, u
     SRS_ON_DEVICE(ctx->device);
     const uint64_t cpb = (cap + kApplyChunk - 1) / kApplyChunk;
     if ((uint64_t)nbuckets * cpb > 0x7fffffffull) return SRS_ERR_INVALID;
-    uint32_t *const gaps = (uint64_t)nbuckets * cpb <= kGapWords ? ctx->flags + kFirstBytes / sizeof(uint32_t) : nullptr;
+    uint32_t *const gaps = (uint64_t)nbuckets * cpb <= kGapWords ? ctx->flags + kFirstBytes / sizeof(uint32_t) + kFirstCodec * 256 : nullptr;
     if (!gaps) {
         hipLaunchKernelGGL(zero_strided_kernel, dim3((nbuckets + 255) / 256), dim3(256), 0, st, max_gap, (uint64_t)nbuckets, 1u);
         SRS_HIP(hipGetLastError());
@@ -1142,28 +1146,35 @@ int srs_encode_values(srs_ctx *ctx, const uint16_t *V, const uint32_t *counts, u
     SRS_ON_DEVICE(ctx->device);
     const uint64_t nchunk = (cap + kVcChunk - 1) / kVcChunk;
     if ((uint64_t)nbuckets * nchunk > 0x7fffffffull) return SRS_ERR_INVALID;
-    const uint64_t words = (uint64_t)nbuckets * 512;
-    if (words > ctx->vc_cap) {
+    if (nbuckets > ctx->vc_cap) {
         SRS_HIP(hipDeviceSynchronize());
-        if (ctx->vc_scratch) SRS_HIP(hipFree(ctx->vc_scratch));
+        if (ctx->vc_scratch && ctx->vc_cap > kFirstCodec) SRS_HIP(hipFree(ctx->vc_scratch));
         ctx->vc_scratch = nullptr; ctx->vc_cap = 0;
-        SRS_HIP(hipMalloc((void **)&ctx->vc_scratch, words * sizeof(uint32_t)));
-        ctx->vc_cap = words;
+        const size_t half = (size_t)nbuckets * 256 * sizeof(uint32_t);
+        SRS_HIP(hipMalloc((void **)&ctx->vc_scratch, 2 * half));
+        if (hipMemset(ctx->vc_scratch, 0, half) != hipSuccess || hipDeviceSynchronize() != hipSuccess) {
+            (void)hipGetLastError(); (void)hipFree(ctx->vc_scratch); ctx->vc_scratch = nullptr;
+            return SRS_ERR_HIP;
+        }
+        ctx->vc_cap = nbuckets;
     }
     ValueCodecArgs a;
     std::memset(&a, 0, sizeof(a));
     a.V = V; a.counts = counts; a.nb = nbuckets; a.cap = cap; a.nchunk = (uint32_t)nchunk;
     a.lens = lens; a.low = low; a.bits = bits; a.chunk_words = chunk_words; a.sub = sub;
-    a.hist = ctx->vc_scratch; a.rcode = ctx->vc_scratch + (uint64_t)nbuckets * 256; a.flags = ctx->flags;
-    const uint64_t nh = (uint64_t)nbuckets * 256;
-    hipLaunchKernelGGL(zero_strided_kernel, dim3((uint32_t)((nh + 255) / 256)), dim3(256), 0, st, a.hist, nh, 1u);
-    SRS_HIP(hipGetLastError());
+    a.hist = ctx->vc_scratch; a.rcode = ctx->vc_scratch + ctx->vc_cap * 256; a.flags = ctx->flags;
     const dim3 grid((uint32_t)((uint64_t)nbuckets * ((nchunk + kVcEncodeChunks - 1) / kVcEncodeChunks)));
     const dim3 hist_grid((uint32_t)((uint64_t)nbuckets * ((nchunk + kVcHistChunks - 1) / kVcHistChunks)));
+    if (ctx->vc_dirty) {
+        const int rc = fill_zero(ctx->vc_scratch, ctx->vc_cap * 256 * sizeof(uint32_t), st);
+        if (rc != SRS_OK) return rc;
+    }
+    ctx->vc_dirty = true;
     hipLaunchKernelGGL(vc_hist_kernel, hist_grid, dim3(kThreads), 0, st, a);
     SRS_HIP(hipGetLastError());
-    hipLaunchKernelGGL(vc_build_kernel, dim3(nbuckets), dim3(kThreads), 0, st, a);
+    hipLaunchKernelGGL(vc_build_kernel, dim3(nbuckets), dim3(kBuildThreads), 0, st, a);
     SRS_HIP(hipGetLastError());
+    ctx->vc_dirty = false;
     hipLaunchKernelGGL(vc_encode_kernel, grid, dim3(kThreads), 0, st, a);
     SRS_HIP(hipGetLastError());
     return SRS_OK;

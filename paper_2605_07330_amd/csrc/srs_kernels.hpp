@@ -1630,7 +1630,7 @@ constexpr uint32_t kVcChunk = 2048, kVcSlotWords = 768, kVcSub = 64, kVcMaxLen =
 struct ValueCodecArgs {
     const uint16_t *V; uint16_t *V_out; const uint32_t *counts; uint32_t nb; uint64_t cap; uint32_t nchunk;
     uint8_t *lens; uint8_t *low; uint32_t *bits; uint32_t *chunk_words; uint16_t *sub;
-    uint32_t *hist;        // [nb*256] scratch
+    uint32_t *hist;        // [nb*256] scratch, all 0 between calls
     uint32_t *rcode;       // [nb*256] scratch: bit-reversed canonical code of each symbol
     uint32_t *flags;
 };
@@ -1714,10 +1714,11 @@ __global__ __launch_bounds__(kThreads) void vc_hist_kernel(const ValueCodecArgs 
 // smallest live nodes are always at the heads of these two queues, and a tie between them goes to the symbol.  One wave
 // runs the merge with both queues in registers and the queue heads in scalar registers: a step is a few readlanes.  Up
 // to kVcWave symbols (the high bytes of weights are 20 to 30) a wave also sorts and measures the depths by itself, and the
-// waves try successive halvings side by side; more symbols take R = 4 registers per lane and queue (entry i in lane i & 63
+// eight waves try successive halvings side by side; more symbols take R = 4 registers per lane and queue (entry i in lane i & 63
 // of register i >> 6) and the whole workgroup around the merge.  Bound by the serial chain.  240 buckets of 335 k
 // values: 147 us when every step searched all nodes for its two minima with 64-bit wave reductions, 49 us by the general
-// path, and 15 us now.
+// path, 15 us with four waves (two tries of four).  The whole value coder with 4 / 8 / 16 waves, us: 240 buckets of 335 k values
+// 101 / 95 / 97, 20 of 250 k 30 / 24 / 26, 8 of 1 M (eight halvings) 39 / 33 / 30, 240 of 10 k 23 / 22 / 24.
 __device__ __forceinline__ uint32_t lane_value(uint32_t x, uint32_t lane) { return (uint32_t)__builtin_amdgcn_readlane((int)x, (int)lane); }
 
 __device__ __forceinline__ void vc_merge(uint32_t used, const uint32_t *sorted_w, const uint8_t *sorted_s, int16_t *parent, int lane) {
@@ -1805,20 +1806,27 @@ __device__ __forceinline__ uint32_t vc_wave_lengths(uint32_t w, uint32_t used, u
     return me < used ? l : 0u;
 }
 
-__global__ __launch_bounds__(kThreads) void vc_build_kernel(const ValueCodecArgs a) {
+constexpr int kBuildThreads = 512, kBuildWaves = kBuildThreads / 64;      // the first 256 threads hold a symbol each
+
+__global__ __launch_bounds__(kBuildThreads) void vc_build_kernel(const ValueCodecArgs a) {
     __shared__ int16_t parent[512];
     __shared__ __align__(16) uint32_t packed_w[256];         // weights of the symbols that occur, in symbol order, then 0
-    __shared__ uint32_t sorted_w[256];
+    __shared__ uint32_t sorted_w[64 * kBuildWaves];
     __shared__ uint8_t sorted_s[256];
     __shared__ uint32_t count_l[kVcMaxLen + 1][kWaves];
-    __shared__ uint32_t s_used[kWaves], s_maxlen, s_fits[kWaves];
-    __shared__ uint8_t s_len[256];
+    __shared__ uint32_t s_used[kWaves], s_maxlen, s_fits[kBuildWaves];
+    __shared__ uint8_t s_len[64 * kBuildWaves];
     const uint32_t b = blockIdx.x, s = threadIdx.x;
     const int lane = s & 63, wave = s >> 6;
-    uint32_t w = a.hist[(uint64_t)b * 256 + s];
-    packed_w[s] = 0;
+    const bool symbol = s < 256;                             // uniform per wave
+    uint32_t w = 0;
+    if (symbol) {
+        w = a.hist[(uint64_t)b * 256 + s];
+        a.hist[(uint64_t)b * 256 + s] = 0;                   // as vc_hist_kernel finds it next time
+        packed_w[s] = 0;
+    }
     const unsigned long long there = __ballot(w != 0);
-    if (lane == 0) s_used[wave] = (uint32_t)__builtin_popcountll(there);
+    if (symbol && lane == 0) s_used[wave] = (uint32_t)__builtin_popcountll(there);
     __syncthreads();
     uint32_t used = 0, place = (uint32_t)__builtin_popcountll(there & ((1ull << lane) - 1ull));
 #pragma unroll
@@ -1830,8 +1838,8 @@ __global__ __launch_bounds__(kThreads) void vc_build_kernel(const ValueCodecArgs
     } else if (used > 1 && used <= kVcWave) {                // uniform
         if (w) packed_w[place] = w;
         __syncthreads();
-        // r halvings make ceil(w / 2^r): the four waves try four numbers of halvings at a time (335 k values take 6)
-        for (uint32_t r0 = 0;; r0 += kWaves) {               // 31 halvings leave weights of 1 and lengths of 6 at most
+        // r halvings make ceil(w / 2^r): the waves try eight numbers of halvings at a time (335 k values take 6)
+        for (uint32_t r0 = 0;; r0 += kBuildWaves) {          // 31 halvings leave weights of 1 and lengths of 6 at most
             const uint32_t r = r0 + (uint32_t)wave;
             const uint32_t wr = (uint32_t)(((uint64_t)packed_w[lane] + (1ull << r) - 1ull) >> r);
             const uint32_t len = vc_wave_lengths(wr, used, sorted_w + 64 * wave, lane);
@@ -1839,17 +1847,17 @@ __global__ __launch_bounds__(kThreads) void vc_build_kernel(const ValueCodecArgs
             const bool fits = !__any(len > kVcMaxLen);
             if (lane == 0) s_fits[wave] = fits ? 1u : 0u;
             __syncthreads();
-            uint32_t hit = kWaves;
+            uint32_t hit = kBuildWaves;
 #pragma unroll
-            for (int v = kWaves - 1; v >= 0; --v) hit = s_fits[v] ? (uint32_t)v : hit;
+            for (int v = kBuildWaves - 1; v >= 0; --v) hit = s_fits[v] ? (uint32_t)v : hit;
             hit = uniform(hit);
-            if (hit < kWaves) { l = w ? (uint32_t)s_len[64 * hit + place] : 0u; break; }
+            if (hit < kBuildWaves) { l = w ? (uint32_t)s_len[64 * hit + place] : 0u; break; }
             __syncthreads();                                 // everybody has read s_fits
         }
     }
     while (used > kVcWave) {                                 // uniform: every thread takes every barrier
         if (w) packed_w[place] = w;
-        parent[s] = -1; parent[s + 256] = -1;
+        if (symbol) { parent[s] = -1; parent[s + 256] = -1; }
         if (s == 0) s_maxlen = 0;
         __syncthreads();
         if (w) {                                             // rank by (weight, symbol): every weight is non-zero
@@ -1879,15 +1887,18 @@ __global__ __launch_bounds__(kThreads) void vc_build_kernel(const ValueCodecArgs
         w = w ? (w + 1) / 2 : 0u;
         __syncthreads();                                     // everybody has read s_maxlen
     }
-    a.lens[(uint64_t)b * 256 + s] = (uint8_t)l;
     // canonical code = first code of its length + number of smaller symbols of the same length
     uint32_t rank = 0;
-    for (uint32_t j = 1; j <= kVcMaxLen; ++j) {
-        const unsigned long long m = __ballot(l == j);
-        if (l == j) rank = (uint32_t)__builtin_popcountll(m & ((1ull << lane) - 1ull));
-        if (lane == 0) count_l[j][wave] = (uint32_t)__builtin_popcountll(m);
+    if (symbol) {
+        a.lens[(uint64_t)b * 256 + s] = (uint8_t)l;
+        for (uint32_t j = 1; j <= kVcMaxLen; ++j) {
+            const unsigned long long m = __ballot(l == j);
+            if (l == j) rank = (uint32_t)__builtin_popcountll(m & ((1ull << lane) - 1ull));
+            if (lane == 0) count_l[j][wave] = (uint32_t)__builtin_popcountll(m);
+        }
     }
     __syncthreads();
+    if (!symbol) return;
     uint32_t first = 0, code = 0;
     for (uint32_t j = 1; j <= kVcMaxLen; ++j) {
         uint32_t cj = 0;
