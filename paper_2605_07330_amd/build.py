@@ -1,4 +1,4 @@
-"""Builds libsrs.so (HIP, gfx950 only) in-tree, next to this file."""
+"""Builds libsrs.so (HIP, gfx950 only) and the binding's _call.so (host code) in-tree, next to this file."""
 from __future__ import annotations
 
 import os
@@ -47,6 +47,26 @@ def clang_asan_runtime() -> str:
     return hits[-1] if hits else ""
 
 
+CALL = os.path.join(HERE, "_call.so")
+CALL_SRC = os.path.join(HERE, "csrc", "call.cpp")
+
+
+def build_call(verbose: bool = False) -> str:
+    """_call.so: the binding's single-tensor calls in C++ (host code only), against the headers of the torch that is installed."""
+    import sysconfig
+    import torch
+    root = os.path.dirname(torch.__file__)
+    cmd = [os.environ.get("CXX", "g++"), "-std=c++17", "-O2", "-fPIC", "-shared", "-w", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           f'-DSRS_TORCH_VERSION="{torch.__version__}"',
+           "-I", sysconfig.get_paths()["include"], "-isystem", os.path.join(root, "include"),
+           "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"), CALL_SRC, "-o", CALL,
+           "-L", os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.check_call(cmd)
+    return CALL
+
+
 C_CONSUMER_SRC = os.path.join(ROOT, "tests", "c_abi", "roundtrip.c")
 C_CONSUMER = os.path.join(ROOT, "tests", "c_abi", "roundtrip")
 
@@ -73,5 +93,6 @@ def is_stale() -> bool:
 
 if __name__ == "__main__":
     build_lib(verbose=True)
+    build_call(verbose=True)
     build_c_consumer(verbose=True)
     print(LIB)

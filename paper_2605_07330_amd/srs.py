@@ -113,6 +113,35 @@ def _check(rc: int, where: str) -> None:
         raise SrsError(rc, where)
 
 
+# The single-tensor calls with their checks in C++ (csrc/call.cpp): None where it is not built or was built for another torch, and each
+# function returns None where it leaves a call to the general way below, which is the same but for the time it takes.
+try:
+    from . import _call
+    if _call.torch_version != torch.__version__:
+        _call = None
+except ImportError:
+    _call = None
+_address = {n: C.cast(getattr(_lib, n), _vp).value for n in ("srs_extract", "srs_apply", "srs_extract_u8", "srs_apply_u8", "srs_extract_cast")}
+
+
+def _extract_native(name: str, ctx: "Context", old, new, be, I, V, counts, cap, stream, width: int, new_width: int) -> bool:
+    if _call is None:
+        return False
+    rc = _call.extract(_address[name], ctx._h.value, old, new, be, I, V, counts, cap, _stream_ptr(stream), width, new_width)
+    if rc:
+        _check(rc, name)
+    return rc is not None
+
+
+def _apply_native(name: str, ctx: "Context", weights, be, I, V, counts, cap, stream, width: int) -> bool:
+    if _call is None:
+        return False
+    rc = _call.apply(_address[name], ctx._h.value, weights, be, I, V, counts, cap, _stream_ptr(stream), width)
+    if rc:
+        _check(rc, name)
+    return rc is not None
+
+
 def version() -> int:
     return _lib.srs_version()
 
@@ -242,6 +271,8 @@ class Context:
     # ---- single tensor --------------------------------------------------------------------
     def extract(self, old: torch.Tensor, new: torch.Tensor, bucket_elems: int, I: torch.Tensor, V: torch.Tensor,
                 counts: torch.Tensor, cap: int, stream: Optional[torch.cuda.Stream] = None) -> None:
+        if _extract_native("srs_extract", self, old, new, bucket_elems, I, V, counts, cap, stream, 2, 2):
+            return
         _dev16(old, "old"), _dev16(new, "new")
         n = old.numel()
         if new.numel() != n:
@@ -267,6 +298,8 @@ class Context:
 
     def apply(self, weights: torch.Tensor, bucket_elems: int, I: torch.Tensor, V: torch.Tensor, counts: torch.Tensor,
               cap: int, stream: Optional[torch.cuda.Stream] = None) -> None:
+        if _apply_native("srs_apply", self, weights, bucket_elems, I, V, counts, cap, stream, 2):
+            return
         _dev16(weights, "weights")
         n = weights.numel()
         if bucket_elems > 0 and cap > 0:
@@ -335,6 +368,8 @@ class Context:
     # ---- one-byte elements (FP8 synchronisation precision) ----------------------------------
     def extract_u8(self, old: torch.Tensor, new: torch.Tensor, bucket_elems: int, I: torch.Tensor, V: torch.Tensor,
                    counts: torch.Tensor, cap: int, stream: Optional[torch.cuda.Stream] = None) -> None:
+        if _extract_native("srs_extract_u8", self, old, new, bucket_elems, I, V, counts, cap, stream, 1, 1):
+            return
         _dev16(old, "old", 1), _dev16(new, "new", 1)
         n = old.numel()
         if new.numel() != n:
@@ -346,6 +381,8 @@ class Context:
 
     def apply_u8(self, weights: torch.Tensor, bucket_elems: int, I: torch.Tensor, V: torch.Tensor,
                  counts: torch.Tensor, cap: int, stream: Optional[torch.cuda.Stream] = None) -> None:
+        if _apply_native("srs_apply_u8", self, weights, bucket_elems, I, V, counts, cap, stream, 1):
+            return
         _dev16(weights, "weights", 1)
         n = weights.numel()
         if bucket_elems > 0 and cap > 0:
@@ -375,6 +412,8 @@ class Context:
     # ---- fused cast + diff ----------------------------------------------------------------
     def extract_cast(self, weights: torch.Tensor, master: torch.Tensor, bucket_elems: int, I: torch.Tensor,
                      V: torch.Tensor, counts: torch.Tensor, cap: int, stream: Optional[torch.cuda.Stream] = None) -> None:
+        if _extract_native("srs_extract_cast", self, weights, master, bucket_elems, I, V, counts, cap, stream, 2, 4):
+            return
         _dev16(weights, "weights")
         if not (master.is_cuda and master.dtype == torch.float32 and master.is_contiguous()
                 and master.numel() == weights.numel()):
