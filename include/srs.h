@@ -66,7 +66,8 @@ typedef enum {
 /* device flags reported by srs_status() */
 #define SRS_FLAG_OVERFLOW  1u  /* extract: some bucket had more than cap changed elements */
 #define SRS_FLAG_BAD_INDEX 2u  /* apply: an index lay outside its bucket's span and was skipped */
-#define SRS_FLAG_TIMEOUT   4u  /* extract: a tile gave up waiting for its predecessors (payload invalid) */
+#define SRS_FLAG_TIMEOUT   4u  /* extract: a tile gave up waiting for its predecessors, or the scratch was found out of order
+                                  because calls that share it had overlapped (payload invalid) */
 
 /* options for srs_set_option() */
 #define SRS_OPT_SPIN_LIMIT 1   /* max polls of a predecessor tile before SRS_FLAG_TIMEOUT (default 1<<24) */
@@ -111,7 +112,9 @@ const char *srs_strerror(int err);
 int srs_version(void);
 
 /* Waits for `stream`, copies the device flag word to *flags (host pointer) and clears it.  After SRS_FLAG_TIMEOUT it also
- * queues kernels that put the context's scratch into its initial state. */
+ * queues kernels that put the context's scratch into its initial state.  No call clears the scratch for the next one: where calls
+ * on one context have overlapped, which is not allowed, later calls may raise SRS_FLAG_TIMEOUT too until this function has
+ * reported it. */
 int srs_status(srs_ctx *ctx, uint32_t *flags, void *stream);
 
 /*

@@ -348,6 +348,19 @@ __device__ __forceinline__ void raise_epoch(const ExtractArgs &a, uint32_t epoch
     if (w >= a.ntiles && w < a.status_cap) status_store(a.status + w, 0ull);
 }
 
+// Epoch and flag that an earlier launch left in a tile's status word.  This one's epoch is among them only where the epoch was
+// not raised since, because calls that share the counters overlapped: the words are no counts then, and publish says so.
+// Only a bucket's first tile looks, which waits for nobody afterwards: free, where all tiles looking costs single tensors of
+// up to 16 M elements 1 to 5 %.
+__device__ __forceinline__ uint32_t left_behind(const ExtractArgs &a, uint32_t tile) {
+    return as_table(reinterpret_cast<const uint32_t *>(a.status + tile))[1];
+}
+// One lane: the tile's count.
+__device__ __forceinline__ void publish(const ExtractArgs &a, uint32_t epoch, uint32_t tile, uint32_t found, bool first, uint32_t total) {
+    if (status_flag(epoch, (unsigned long long)found << 32) != 0) atomicOr(a.flags, kFlagTimeout);
+    status_store(a.status + tile, status_word(epoch, first ? kStPrefix : kStAgg, total));
+}
+
 // ---------------------------------------------------------------------------------------------
 // decoupled look-back, run by all 64 lanes of wave 0.  Returns the number of changed elements in
 // the tiles first_tile .. tile-1 of the same bucket.  Lane l inspects tile (pos - l); the window
@@ -537,10 +550,14 @@ __global__ __launch_bounds__(kThreads, waves_per_simd(V, MULTI, SRC, EB)) void e
         if (tid == 0) s_ticket = claim_tile(a, bucket, bucket_tiles);
         __syncthreads();
         k = uniform(s_ticket);
-        if (k >= bucket_tiles) return;     // cannot happen: each bucket is served by exactly bucket_tiles workgroups
+        if (k >= bucket_tiles) {           // only where calls that share the counters overlapped: the tile is lost
+            if (tid == 0) atomicOr(a.flags, kFlagTimeout);
+            return;
+        }
     }
     const uint32_t tile = first_tile + k;
     const bool last = (k == bucket_tiles - 1);
+    const uint32_t found = (chained && k == 0) ? left_behind(a, tile) : 0u;
 
     // ---- where this tile lives
     constexpr uint32_t NB = CAST ? 4u : (uint32_t)EB;                   // bytes per new weight
@@ -709,7 +726,7 @@ __global__ __launch_bounds__(kThreads, waves_per_simd(V, MULTI, SRC, EB)) void e
     for (int j = 0; j < V; ++j) ex[j] += wave_base;       // from here on: rank inside the tile
 
     // ---- the chain with the earlier tiles of the bucket: this tile's count is published now, and looked back from later
-    if (tid == 0 && !last) status_store(a.status + tile, status_word(epoch, tile == first_tile ? kStPrefix : kStAgg, tile_total));
+    if (tid == 0 && !last) publish(a, epoch, tile, found, tile == first_tile, tile_total);
     // wave 0: changed elements of the bucket in front of the tile
     auto settle = [&]() -> uint32_t {
         uint32_t excl = 0;
@@ -877,10 +894,14 @@ __global__ __launch_bounds__(kThreads) void extract_marked_kernel(const ExtractA
         if (tid == 0) s_ticket = claim_tile(a, bucket, bucket_tiles);
         __syncthreads();
         k = uniform(s_ticket);
-        if (k >= bucket_tiles) return;
+        if (k >= bucket_tiles) {           // as in extract_kernel
+            if (tid == 0) atomicOr(a.flags, kFlagTimeout);
+            return;
+        }
     }
     const uint32_t tile = first_tile + k;
     const bool last = (k == bucket_tiles - 1);
+    const uint32_t found = (chained && k == 0) ? left_behind(a, tile) : 0u;
     const auto *d = as_table(a.tiles + tile);
     const uint32_t tensor = d->tensor, tensor_off = d->tensor_off, len = d->len, idx_base = d->bucket_off;
     const gptr<const uint16_t> pn = (gptr<const uint16_t>)as_global(as_table(a.ptrs + tensor)->new_w) + tensor_off;
@@ -925,7 +946,7 @@ __global__ __launch_bounds__(kThreads) void extract_marked_kernel(const ExtractA
     const uint32_t first = wave_base + (inc - mine);                 // rank of this thread's first pair
 
     // ---- chain with the earlier tiles of the bucket, as in extract_kernel: published now, looked back from later
-    if (tid == 0 && !last) status_store(a.status + tile, status_word(epoch, tile == first_tile ? kStPrefix : kStAgg, tile_total));
+    if (tid == 0 && !last) publish(a, epoch, tile, found, tile == first_tile, tile_total);
     auto settle = [&]() -> uint32_t {
         uint32_t excl = 0;
         if (tile != first_tile) {
