@@ -112,7 +112,8 @@ const char *srs_strerror(int err);
 int srs_version(void);
 
 /* Waits for `stream`, copies the device flag word to *flags (host pointer) and clears it.  After SRS_FLAG_TIMEOUT it also
- * queues kernels that put the context's scratch into its initial state.  No call clears the scratch for the next one: where calls
+ * puts the context's scratch into its initial state, and the static array of srs_extract_noalloc where one of this context's
+ * calls on that raised the flag, and waits again; it then counts as such a call where the header orders them.  No call clears the scratch for the next one: where calls
  * on one context have overlapped, which is not allowed, later calls may raise SRS_FLAG_TIMEOUT too until this function has
  * reported it. */
 int srs_status(srs_ctx *ctx, uint32_t *flags, void *stream);

@@ -53,7 +53,6 @@ static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 struct srs_ctx {
     int device = 0;
     unsigned char *static_scratch = nullptr;   // this device's address of `scratch`
-    bool used_static = false;               // a call of this context has used it
     unsigned long long *status = nullptr;   // tile status words
     uint64_t status_cap = 0;
     uint32_t *tickets = nullptr;            // per-bucket ticket counters
@@ -137,6 +136,7 @@ int extract_scratch(srs_ctx *ctx, uint64_t ntiles, uint64_t nb, uint32_t chained
     if (rc == SRS_OK) rc = grow_zeroed(&ctx->status, &ctx->status_cap, ntiles, 1024, kFirstStatus);
     a.tickets = ctx->tickets; a.status = ctx->status; a.status_cap = ctx->status_cap;
     a.epoch = ctx->flags + kEpochWord;
+    a.timeout = kFlagTimeout;
     return rc;
 }
 
@@ -146,7 +146,7 @@ int extract_scratch_static(srs_ctx *ctx, uint64_t ntiles, uint64_t nb, uint32_t 
     if (!ctx->static_scratch) return SRS_ERR_HIP;
     if (ntiles > kStaticTiles || nb > kStaticTicketWords) return SRS_ERR_TOO_LARGE;
     a.chained = chained;
-    ctx->used_static = true;
+    a.timeout = kFlagTimeout | kFlagStatic;
     a.ticket_stride = (nb * 64u <= kStaticTicketWords) ? 64u : 1u;
     a.status = reinterpret_cast<unsigned long long *>(ctx->static_scratch);
     a.status_cap = kStaticTiles;
@@ -164,12 +164,14 @@ int fill_zero(void *p, uint64_t bytes, hipStream_t st) {
 }
 
 // After a look-back that gave up: every launch leaves the counters as the next one needs them also then, but where it gave up
-// because calls overlapped that may not, they may have been left anywhere.
-int rewind_scratch(srs_ctx *ctx, hipStream_t st) {
+// because calls overlapped that may not, they may have been left anywhere.  The static scratch belongs to all contexts of the
+// GPU: it is rewound only after a launch on it gave up, and done when this returns, as its next user may be on any stream.
+int rewind_scratch(srs_ctx *ctx, bool static_scratch, hipStream_t st) {
     int rc = fill_zero(ctx->tickets, ctx->tickets_cap * sizeof(uint32_t), st);
     if (rc == SRS_OK) rc = fill_zero(ctx->status, ctx->status_cap * sizeof(unsigned long long), st);
     if (rc == SRS_OK) rc = fill_zero(ctx->flags + kEpochWord + kEpochClaimed, 8, st);
-    if (rc == SRS_OK && ctx->used_static) rc = fill_zero(ctx->static_scratch, kStaticScratchBytes, st);
+    if (rc == SRS_OK && static_scratch) rc = fill_zero(ctx->static_scratch, kStaticScratchBytes, st);
+    if (rc == SRS_OK && hipStreamSynchronize(st) != hipSuccess) { (void)hipGetLastError(); return SRS_ERR_HIP; }
     return rc;
 }
 
@@ -671,11 +673,13 @@ int srs_status(srs_ctx *ctx, uint32_t *flags, void *stream) {
     if (!ctx || !flags) return SRS_ERR_INVALID;
     hipStream_t st = (hipStream_t)stream;
     SRS_ON_DEVICE(ctx->device);
-    SRS_HIP(hipMemcpyAsync(flags, ctx->flags, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
+    uint32_t raised = 0;
+    SRS_HIP(hipMemcpyAsync(&raised, ctx->flags, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
     SRS_HIP(hipStreamSynchronize(st));
+    *flags = raised & kFlagsReported;
     hipLaunchKernelGGL(fill_u64_kernel, dim3(1), dim3(64), 0, st, (unsigned long long *)ctx->flags, (uint64_t)1, 0ull);
     SRS_HIP(hipGetLastError());
-    return (*flags & kFlagTimeout) ? rewind_scratch(ctx, st) : SRS_OK;
+    return (raised & kFlagTimeout) ? rewind_scratch(ctx, (raised & kFlagStatic) != 0, st) : SRS_OK;
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -45,6 +45,8 @@ constexpr uint32_t kApplyChunk = 2048; // payload pairs per apply workgroup
 constexpr int kLoadPace = 4;           // s_sleep argument between the streaming loads of an extract that refreshes in place
 
 constexpr uint32_t kFlagOverflow = 1u, kFlagBadIndex = 2u, kFlagTimeout = 4u;
+constexpr uint32_t kFlagsReported = 7u;
+constexpr uint32_t kFlagStatic = 1u << 31;     // with kFlagTimeout: raised by a launch on the library's static scratch; not reported
 constexpr uint32_t kStAgg = 1u, kStPrefix = 2u;   // tile status: aggregate only / inclusive prefix
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -105,6 +107,7 @@ struct ExtractArgs {
     uint32_t *epoch;                // epoch[0]: this launch's epoch; epoch[kEpochClaimed]: buckets whose tickets are all taken
     uint32_t chained;               // buckets of more than one tile
     uint32_t *flags;
+    uint32_t timeout;               // what a tile that gives up raises in them
     uint32_t spin_limit;
     // cumulative changed-index set: one bit per packed position (bit g&31 of word g>>5)
     uint32_t *bitmap; uint64_t bitmap_words; const uint64_t *tensor_base;   // packed position of each tensor's element 0
@@ -357,7 +360,7 @@ __device__ __forceinline__ uint32_t left_behind(const ExtractArgs &a, uint32_t t
 }
 // One lane: the tile's count.
 __device__ __forceinline__ void publish(const ExtractArgs &a, uint32_t epoch, uint32_t tile, uint32_t found, bool first, uint32_t total) {
-    if (status_flag(epoch, (unsigned long long)found << 32) != 0) atomicOr(a.flags, kFlagTimeout);
+    if (status_flag(epoch, (unsigned long long)found << 32) != 0) atomicOr(a.flags, a.timeout);
     status_store(a.status + tile, status_word(epoch, first ? kStPrefix : kStAgg, total));
 }
 
@@ -396,7 +399,7 @@ __device__ __forceinline__ uint32_t look_back(const ExtractArgs &a, uint32_t epo
             }
             if ((pending & need) == 0) break;
             if (++polls > a.spin_limit) {
-                if (lane == 0) atomicOr(a.flags, kFlagTimeout);
+                if (lane == 0) atomicOr(a.flags, a.timeout);
                 need &= ~pending;
                 found_prefix = true;                                         // stop walking back
                 break;
@@ -551,7 +554,7 @@ __global__ __launch_bounds__(kThreads, waves_per_simd(V, MULTI, SRC, EB)) void e
         __syncthreads();
         k = uniform(s_ticket);
         if (k >= bucket_tiles) {           // only where calls that share the counters overlapped: the tile is lost
-            if (tid == 0) atomicOr(a.flags, kFlagTimeout);
+            if (tid == 0) atomicOr(a.flags, a.timeout);
             return;
         }
     }
@@ -895,7 +898,7 @@ __global__ __launch_bounds__(kThreads) void extract_marked_kernel(const ExtractA
         __syncthreads();
         k = uniform(s_ticket);
         if (k >= bucket_tiles) {           // as in extract_kernel
-            if (tid == 0) atomicOr(a.flags, kFlagTimeout);
+            if (tid == 0) atomicOr(a.flags, a.timeout);
             return;
         }
     }

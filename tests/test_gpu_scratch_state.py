@@ -15,13 +15,15 @@ T = 8192
 
 
 class Scratch:
-    """Device words of a context, by the first members of srs_ctx (csrc/srs.hip): device, static scratch, used_static, status words,
+    """Device words of a context, by the first members of srs_ctx (csrc/srs.hip): device, static scratch, status words,
     their number, ticket counters, their number, flag word (the epoch 32 words behind it, the count of claimed buckets 16 behind that)."""
 
     def __init__(self, ctx):
         at = lambda k: C.c_uint64.from_address(ctx._h.value + k).value  # noqa: E731
-        self.static, self.status, self.status_cap, self.tickets, self.flags = at(8), at(24), at(32), at(40), at(56)
+        self.static, self.status, self.status_cap, self.tickets, self.flags = at(8), at(16), at(24), at(32), at(48)
         self.epoch, self.claimed = self.flags + 128, self.flags + 192
+        self.static_tickets = self.static + (8 << 20)
+        self.static_epoch = self.static_tickets + (4 << 18)
         self.hip = C.CDLL(next(x.split()[-1] for x in open("/proc/self/maps") if "libamdhip64" in x))
 
     def read(self, address, words):
@@ -100,3 +102,26 @@ def test_scratch_out_of_order_is_reported(ctx, kind, fault):
     call.run()
     assert ctx.status() == 0
     call.check()
+
+
+def test_only_a_call_on_the_static_scratch_rewinds_it(ctx):
+    """It belongs to every context of the GPU, whose calls on it need not be ordered with this one's look at its flags."""
+    from paper_2605_07330_amd import srs
+    s, own, static = Scratch(ctx), Call(ctx, "one", 3, 3), Call(ctx, "static", 5, 5)
+    static.run()
+    assert ctx.status() == 0
+    before = int(s.read(s.static_epoch, 1)[0])
+    assert before > 0
+    s.write(s.tickets, 5)
+    own.run()
+    assert ctx.status() == srs.FLAG_TIMEOUT
+    assert int(s.read(s.static_epoch, 1)[0]) == before and s.read(s.static, 8).any()
+    s.write(s.static_tickets, 7)
+    static.run()
+    assert ctx.status() == srs.FLAG_TIMEOUT
+    assert not s.read(s.static, 8).any() and int(s.read(s.static_tickets, 1)[0]) == 0
+    static.run()
+    own.run()
+    assert ctx.status() == 0
+    static.check()
+    own.check()
