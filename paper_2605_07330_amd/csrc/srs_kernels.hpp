@@ -320,8 +320,8 @@ template <class T> __device__ __forceinline__ const T __attribute__((address_spa
 // graph gets a new one each time: a workgroup reads it before it takes its ticket; the one that takes a bucket's last
 // ticket counts the bucket, and the one that counts the last bucket raises the epoch, when every workgroup of the
 // launch has read it, whatever else becomes of them.  The 30 bits of an epoch in a status word come round after 2^30
-// launches; that nothing written so long ago is left, the same workgroup sees to, which wipes 64 words behind those in use,
-// other ones each time.
+// launches; nothing written so long ago is left then: every tile of a launch that has chains writes its word, and the workgroup that
+// raises the epoch wipes 64 words behind those, other ones each time.
 // The kernel that cleared both ahead of each launch took 1.4 us where little else ran and 4.7 us in a busy stream, and the
 // host 2.5 us.  Extract and apply with it / without, us: 64 K elements 13.7 / 11.0, 1 M in four buckets 13.5 / 12.1, 4 M in
 // four 17.5 / 16.0, 300 odd-sized tensors 147.5 / 146.1.
@@ -358,10 +358,10 @@ __device__ __forceinline__ void raise_epoch(const ExtractArgs &a, uint32_t epoch
 __device__ __forceinline__ uint32_t left_behind(const ExtractArgs &a, uint32_t tile) {
     return as_table(reinterpret_cast<const uint32_t *>(a.status + tile))[1];
 }
-// One lane: the tile's count.
-__device__ __forceinline__ void publish(const ExtractArgs &a, uint32_t epoch, uint32_t tile, uint32_t found, bool first, uint32_t total) {
+// One lane: the tile's count.  A bucket's last or only tile, whose word nobody reads, leaves 0 there.
+__device__ __forceinline__ void publish(const ExtractArgs &a, uint32_t epoch, uint32_t tile, uint32_t found, bool first, bool last, uint32_t total) {
     if (status_flag(epoch, (unsigned long long)found << 32) != 0) atomicOr(a.flags, a.timeout);
-    status_store(a.status + tile, status_word(epoch, first ? kStPrefix : kStAgg, total));
+    status_store(a.status + tile, last ? 0ull : status_word(epoch, first ? kStPrefix : kStAgg, total));
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -729,7 +729,7 @@ __global__ __launch_bounds__(kThreads, waves_per_simd(V, MULTI, SRC, EB)) void e
     for (int j = 0; j < V; ++j) ex[j] += wave_base;       // from here on: rank inside the tile
 
     // ---- the chain with the earlier tiles of the bucket: this tile's count is published now, and looked back from later
-    if (tid == 0 && !last) publish(a, epoch, tile, found, tile == first_tile, tile_total);
+    if (tid == 0 && a.chained) publish(a, epoch, tile, found, tile == first_tile, last, tile_total);
     // wave 0: changed elements of the bucket in front of the tile
     auto settle = [&]() -> uint32_t {
         uint32_t excl = 0;
@@ -949,7 +949,7 @@ __global__ __launch_bounds__(kThreads) void extract_marked_kernel(const ExtractA
     const uint32_t first = wave_base + (inc - mine);                 // rank of this thread's first pair
 
     // ---- chain with the earlier tiles of the bucket, as in extract_kernel: published now, looked back from later
-    if (tid == 0 && !last) publish(a, epoch, tile, found, tile == first_tile, tile_total);
+    if (tid == 0 && a.chained) publish(a, epoch, tile, found, tile == first_tile, last, tile_total);
     auto settle = [&]() -> uint32_t {
         uint32_t excl = 0;
         if (tile != first_tile) {

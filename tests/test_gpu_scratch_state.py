@@ -125,3 +125,25 @@ def test_only_a_call_on_the_static_scratch_rewinds_it(ctx):
     assert ctx.status() == 0
     static.check()
     own.check()
+
+
+def test_no_word_outlives_the_epochs(ctx):
+    """A word that one layout's launch wrote is overwritten by every launch that has a tile there, read or not, and wiped behind them:
+    none can meet its own epoch again when that comes round."""
+    s, long, short = Scratch(ctx), Call(ctx, "one", 40, 40), Call(ctx, "one", 5, 2)      # the short one: buckets of 2, 2 and 1 tiles
+    long.run()
+    assert ctx.status() == 0
+    epoch = int(s.read(s.epoch, 1)[0]) - 1
+    short.run()
+    assert ctx.status() == 0
+    words = s.read(s.status, 80).reshape(-1, 2)[:, 1]
+    assert (words[5:39] != 0).all() and (words[[1, 3, 4]] == 0).all() and (words[[0, 2]] >> 2 == epoch + 1).all(), words
+    for _ in range(s.status_cap // 64 + 1):
+        short.run()
+    assert ctx.status() == 0
+    short.check()
+    words = s.read(s.status, 2 * s.status_cap).reshape(-1, 2)[:, 1]
+    assert (words[5:] == 0).all() and (words[[1, 3, 4]] == 0).all()
+    long.run()
+    assert ctx.status() == 0
+    long.check()
