@@ -2,6 +2,7 @@
 // The operations and their conventions are documented in include/srs.h.
 #include "srs.h"
 #include "device_guard.hpp"
+#include "scratch_array.hpp"
 #include "srs_kernels.hpp"
 
 #include <hip/hip_runtime.h>
@@ -32,6 +33,15 @@ struct HipDeviceApi {
 };
 typedef srs::BasicDeviceGuard<HipDeviceApi> DeviceGuard;
 
+struct HipScratchApi {
+    static bool synchronize() { return hipDeviceSynchronize() == hipSuccess; }
+    static bool allocate(void **out, size_t bytes) { return hipMalloc(out, bytes) == hipSuccess; }
+    static bool release(void *p) { return hipFree(p) == hipSuccess; }
+    static bool zero(void *p, size_t bytes) { return hipMemset(p, 0, bytes) == hipSuccess && synchronize(); }
+    static void clear_error() { (void)hipGetLastError(); }
+};
+template <class T> using ScratchArray = srs::BasicScratchArray<HipScratchApi, T>;
+
 #define SRS_ON_DEVICE(device)            \
     DeviceGuard device_guard_(device);   \
     if (!device_guard_.ok) return SRS_ERR_HIP
@@ -53,14 +63,11 @@ static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 struct srs_ctx {
     int device = 0;
     unsigned char *static_scratch = nullptr;   // this device's address of `scratch`
-    unsigned long long *status = nullptr;   // tile status words
-    uint64_t status_cap = 0;
-    uint32_t *tickets = nullptr;            // per-bucket ticket counters
-    uint64_t tickets_cap = 0;               // in words
+    ScratchArray<unsigned long long> status;  // tile status words
+    ScratchArray<uint32_t> tickets;         // per-bucket ticket counters
     uint32_t *flags = nullptr;              // device flag word, the epoch kEpochWord words behind it; behind these 256 bytes, in the
-                                            // same allocation, the first kFirst* ticket counters and status words
-    uint32_t *vc_scratch = nullptr;         // value codec: vc_cap buckets' histograms (all 0 between calls), then as many codes
-    uint64_t vc_cap = 0;                    // in buckets
+                                            // same allocation, the pieces that the arrays begin as and what is fixed in size
+    ScratchArray<uint32_t> vc;              // value codec: buckets' histograms (all 0 between calls), then as many buckets' codes
     bool vc_dirty = false;                  // a call ended between filling the histograms and emptying them
     uint32_t spin_limit = 1u << 24;
     uint32_t tile_elems = 32768;
@@ -108,36 +115,19 @@ constexpr uint64_t kFirstBytes = 256 + kFirstTickets * sizeof(uint32_t) + kFirst
 // never allocates.  240 buckets of 424 k payload slots have 49,680.
 constexpr uint64_t kGapWords = 65536;
 
-// A zeroed array of at least `need` elements in *p (capacity *cap; an array of more than `first` elements is an allocation of its
-// own), which may replace a smaller one: allocates and synchronises.
-template <class T>
-int grow_zeroed(T **p, uint64_t *cap, uint64_t need, uint64_t slack, uint64_t first) {
-    if (need <= *cap) return SRS_OK;
-    SRS_HIP(hipDeviceSynchronize());
-    if (*p && *cap > first) SRS_HIP(hipFree(*p));
-    *p = nullptr; *cap = 0;
-    const uint64_t n = (need + need / 4 + slack) / 2 * 2;
-    SRS_HIP(hipMalloc((void **)p, n * sizeof(T)));
-    if (hipMemset(*p, 0, n * sizeof(T)) != hipSuccess || hipDeviceSynchronize() != hipSuccess) {
-        (void)hipGetLastError(); (void)hipFree(*p); *p = nullptr;
-        return SRS_ERR_HIP;
-    }
-    *cap = n;
-    return SRS_OK;
-}
-
 // The status words, ticket counters and epoch of an extract launch of ntiles tiles in nb buckets, `chained` of which have more
 // than one tile (none: nothing of it is used).  Nothing is cleared between launches.
 int extract_scratch(srs_ctx *ctx, uint64_t ntiles, uint64_t nb, uint32_t chained, ExtractArgs &a) {
     a.chained = chained;
     if (chained == 0) return SRS_OK;
     a.ticket_stride = ticket_stride_for(nb);
-    int rc = grow_zeroed(&ctx->tickets, &ctx->tickets_cap, nb * a.ticket_stride, 4096, kFirstTickets);
-    if (rc == SRS_OK) rc = grow_zeroed(&ctx->status, &ctx->status_cap, ntiles, 1024, kFirstStatus);
-    a.tickets = ctx->tickets; a.status = ctx->status; a.status_cap = ctx->status_cap;
+    const uint64_t words = nb * a.ticket_stride;            // a quarter more than asked for, so that lists of growing size move seldom
+    if (words > ctx->tickets.cap && !ctx->tickets.grow(words + words / 4 + 4096)) return SRS_ERR_HIP;
+    if (ntiles > ctx->status.cap && !ctx->status.grow(ntiles + ntiles / 4 + 1024)) return SRS_ERR_HIP;
+    a.tickets = ctx->tickets.p; a.status = ctx->status.p; a.status_cap = ctx->status.cap;
     a.epoch = ctx->flags + kEpochWord;
     a.timeout = kFlagTimeout;
-    return rc;
+    return SRS_OK;
 }
 
 // The same on the static scratch: nothing is allocated, sizes beyond the array are refused.  Ticket counters sit
@@ -167,8 +157,8 @@ int fill_zero(void *p, uint64_t bytes, hipStream_t st) {
 // because calls overlapped that may not, they may have been left anywhere.  The static scratch belongs to all contexts of the
 // GPU: it is rewound only after a launch on it gave up, and done when this returns, as its next user may be on any stream.
 int rewind_scratch(srs_ctx *ctx, bool static_scratch, hipStream_t st) {
-    int rc = fill_zero(ctx->tickets, ctx->tickets_cap * sizeof(uint32_t), st);
-    if (rc == SRS_OK) rc = fill_zero(ctx->status, ctx->status_cap * sizeof(unsigned long long), st);
+    int rc = fill_zero(ctx->tickets.p, ctx->tickets.cap * sizeof(uint32_t), st);
+    if (rc == SRS_OK) rc = fill_zero(ctx->status.p, ctx->status.cap * sizeof(unsigned long long), st);
     if (rc == SRS_OK) rc = fill_zero(ctx->flags + kEpochWord + kEpochClaimed, 8, st);
     if (rc == SRS_OK && static_scratch) rc = fill_zero(ctx->static_scratch, kStaticScratchBytes, st);
     if (rc == SRS_OK && hipStreamSynchronize(st) != hipSuccess) { (void)hipGetLastError(); return SRS_ERR_HIP; }
@@ -619,12 +609,9 @@ int srs_create(srs_ctx **out, int device) {
     if (hipMemset(ctx->flags, 0, kFirstBytes) != hipSuccess || hipDeviceSynchronize() != hipSuccess) {
         (void)hipGetLastError(); (void)hipFree(ctx->flags); delete ctx; return SRS_ERR_HIP;
     }
-    ctx->tickets = ctx->flags + 64;
-    ctx->tickets_cap = kFirstTickets;
-    ctx->status = reinterpret_cast<unsigned long long *>(ctx->tickets + kFirstTickets);
-    ctx->status_cap = kFirstStatus;
-    ctx->vc_scratch = reinterpret_cast<uint32_t *>(ctx->status + kFirstStatus);
-    ctx->vc_cap = kFirstCodec;
+    ctx->tickets.begin(ctx->flags + 64, kFirstTickets);
+    ctx->status.begin(reinterpret_cast<unsigned long long *>(ctx->tickets.p + kFirstTickets), kFirstStatus);
+    ctx->vc.begin(reinterpret_cast<uint32_t *>(ctx->status.p + kFirstStatus), kFirstCodec * 512);
     // this device's copy of the static scratch array (each GPU has its own, at its own address)
     void *sp = nullptr;
     if (hipGetSymbolAddress(&sp, HIP_SYMBOL(scratch)) != hipSuccess || !sp || ((uintptr_t)sp & 255u)) {
@@ -639,9 +626,9 @@ int srs_destroy(srs_ctx *ctx) {
     if (!ctx) return SRS_ERR_INVALID;
     DeviceGuard device_guard_(ctx->device);
     (void)hipDeviceSynchronize();
-    if (ctx->status && ctx->status_cap > kFirstStatus) (void)hipFree(ctx->status);
-    if (ctx->tickets && ctx->tickets_cap > kFirstTickets) (void)hipFree(ctx->tickets);
-    if (ctx->vc_scratch && ctx->vc_cap > kFirstCodec) (void)hipFree(ctx->vc_scratch);
+    ctx->status.release();
+    ctx->tickets.release();
+    ctx->vc.release();
     if (ctx->flags) (void)hipFree(ctx->flags);
     delete ctx;
     return SRS_OK;
@@ -1150,27 +1137,17 @@ int srs_encode_values(srs_ctx *ctx, const uint16_t *V, const uint32_t *counts, u
     SRS_ON_DEVICE(ctx->device);
     const uint64_t nchunk = (cap + kVcChunk - 1) / kVcChunk;
     if ((uint64_t)nbuckets * nchunk > 0x7fffffffull) return SRS_ERR_INVALID;
-    if (nbuckets > ctx->vc_cap) {
-        SRS_HIP(hipDeviceSynchronize());
-        if (ctx->vc_scratch && ctx->vc_cap > kFirstCodec) SRS_HIP(hipFree(ctx->vc_scratch));
-        ctx->vc_scratch = nullptr; ctx->vc_cap = 0;
-        const size_t half = (size_t)nbuckets * 256 * sizeof(uint32_t);
-        SRS_HIP(hipMalloc((void **)&ctx->vc_scratch, 2 * half));
-        if (hipMemset(ctx->vc_scratch, 0, half) != hipSuccess || hipDeviceSynchronize() != hipSuccess) {
-            (void)hipGetLastError(); (void)hipFree(ctx->vc_scratch); ctx->vc_scratch = nullptr;
-            return SRS_ERR_HIP;
-        }
-        ctx->vc_cap = nbuckets;
-    }
+    if (!ctx->vc.grow((uint64_t)nbuckets * 512)) return SRS_ERR_HIP;
+    const uint64_t half = ctx->vc.cap / 2;                  // of it, the histograms
     ValueCodecArgs a;
     std::memset(&a, 0, sizeof(a));
     a.V = V; a.counts = counts; a.nb = nbuckets; a.cap = cap; a.nchunk = (uint32_t)nchunk;
     a.lens = lens; a.low = low; a.bits = bits; a.chunk_words = chunk_words; a.sub = sub;
-    a.hist = ctx->vc_scratch; a.rcode = ctx->vc_scratch + ctx->vc_cap * 256; a.flags = ctx->flags;
+    a.hist = ctx->vc.p; a.rcode = ctx->vc.p + half; a.flags = ctx->flags;
     const dim3 grid((uint32_t)((uint64_t)nbuckets * ((nchunk + kVcEncodeChunks - 1) / kVcEncodeChunks)));
     const dim3 hist_grid((uint32_t)((uint64_t)nbuckets * ((nchunk + kVcHistChunks - 1) / kVcHistChunks)));
     if (ctx->vc_dirty) {
-        const int rc = fill_zero(ctx->vc_scratch, ctx->vc_cap * 256 * sizeof(uint32_t), st);
+        const int rc = fill_zero(ctx->vc.p, half * sizeof(uint32_t), st);
         if (rc != SRS_OK) return rc;
     }
     ctx->vc_dirty = true;

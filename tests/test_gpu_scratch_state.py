@@ -15,12 +15,12 @@ T = 8192
 
 
 class Scratch:
-    """Device words of a context, by the first members of srs_ctx (csrc/srs.hip): device, static scratch, status words,
-    their number, ticket counters, their number, flag word (the epoch 32 words behind it, the count of claimed buckets 16 behind that)."""
+    """Device words of a context, by the first members of srs_ctx (csrc/srs.hip): device, static scratch, the arrays
+    of status words and of ticket counters (where, how many, where and how many at first), flag word (the epoch 32 words behind it, the count of claimed buckets 16 behind that)."""
 
     def __init__(self, ctx):
         at = lambda k: C.c_uint64.from_address(ctx._h.value + k).value  # noqa: E731
-        self.static, self.status, self.status_cap, self.tickets, self.flags = at(8), at(16), at(24), at(32), at(48)
+        self.static, self.status, self.status_cap, self.tickets, self.flags = at(8), at(16), at(24), at(48), at(80)
         self.epoch, self.claimed = self.flags + 128, self.flags + 192
         self.static_tickets = self.static + (8 << 20)
         self.static_epoch = self.static_tickets + (4 << 18)
