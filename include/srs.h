@@ -22,7 +22,8 @@
  *     one incomplete vector at either end of a tile.
  *   - `stream` is a hipStream_t passed as void* (NULL = the default stream).  Every call is
  *     asynchronous on it and does no host synchronisation, except where stated.
- *   - Payload layout: bucket b owns the slots I[b*cap .. b*cap+cap) and V[b*cap .. b*cap+cap).
+ *   - Payload layout: bucket b owns the slots I[b*cap .. b*cap+cap) and V[b*cap .. b*cap+cap).  With more than one bucket,
+ *     and in the encoded forms with one too, more than 2^60 slots in all are SRS_ERR_INVALID.
  *     counts[b] is always the TRUE number of changed elements of bucket b.  If it exceeds cap only
  *     the first cap pairs (ascending) are stored and the SRS_FLAG_OVERFLOW device flag is raised;
  *     the snapshot is refreshed all the same, and the caller sends that bucket as a dense copy of

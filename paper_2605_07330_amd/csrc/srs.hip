@@ -19,6 +19,10 @@ namespace {
 
 constexpr uint64_t kMaxIndexable = 0x7fffffffull;   // int32 indices (Sec. 3.2: tensors below 2^31 elements)
 
+// Byte offsets of all buckets' slots have to fit 64 bits with room to spare; the only bucket's slots begin at 0 whatever the capacity.
+constexpr uint64_t kMaxSlots = 1ull << 60;
+bool slots_ok(uint64_t nb, uint64_t cap) { return nb <= 1 || cap <= kMaxSlots / nb; }
+
 #define SRS_HIP(expr)                                   \
     do {                                                \
         hipError_t e_ = (expr);                         \
@@ -501,6 +505,7 @@ int extract_single(srs_ctx *ctx, void *old_snapshot, const void *new_w, uint64_t
     if (!ctx || bucket_elems == 0 || cap == 0 || n > kMaxIndexable || bucket_elems > kMaxIndexable) return SRS_ERR_INVALID;
     if (n == 0) return SRS_OK;
     if (!old_snapshot || !new_w || !I || !V || !counts) return SRS_ERR_INVALID;
+    if (!slots_ok((n + bucket_elems - 1) / bucket_elems, cap)) return SRS_ERR_INVALID;
     const uintptr_t amask = (uintptr_t)eb - 1u;                     // elements are naturally aligned
     if (((uintptr_t)old_snapshot | (uintptr_t)V) & amask) return SRS_ERR_INVALID;
     if ((uintptr_t)new_w & (cast ? 3u : amask)) return SRS_ERR_INVALID;
@@ -548,7 +553,7 @@ int extract_multi(srs_ctx *ctx, srs_plan *plan, const srs_tensor_pair *t,
     if (src == kSrcBitmap && (!bitmap || ((uintptr_t)bitmap & 3u))) return SRS_ERR_INVALID;
     if (!ctx || !plan || cap == 0 || plan->device != ctx->device) return SRS_ERR_INVALID;
     if (plan->total == 0) return SRS_OK;
-    if (!t || !I || !V || !counts) return SRS_ERR_INVALID;
+    if (!t || !I || !V || !counts || !slots_ok(plan->nbuckets, cap)) return SRS_ERR_INVALID;
     const uintptr_t amask = (uintptr_t)eb - 1u;
     if (((uintptr_t)V & amask) || (((uintptr_t)I | (uintptr_t)counts) & 3u)) return SRS_ERR_INVALID;
     if (eb == 1 && plan->tile_elems < 8192) return SRS_ERR_INVALID;
@@ -694,6 +699,7 @@ static int apply_single(srs_ctx *ctx, void *weights, uint64_t n, uint64_t bucket
     if (!ctx || bucket_elems == 0 || cap == 0 || n > kMaxIndexable || bucket_elems > kMaxIndexable) return SRS_ERR_INVALID;
     if (n == 0) return SRS_OK;
     if (!weights || !I || !V || !counts) return SRS_ERR_INVALID;
+    if (!slots_ok((n + bucket_elems - 1) / bucket_elems, cap)) return SRS_ERR_INVALID;
     if (((uintptr_t)weights | (uintptr_t)V) & ((uintptr_t)eb - 1u)) return SRS_ERR_INVALID;
     if (((uintptr_t)I | (uintptr_t)counts) & 3u) return SRS_ERR_INVALID;
     hipStream_t st = (hipStream_t)stream;
@@ -865,7 +871,7 @@ static int apply_multi(srs_ctx *ctx, srs_plan *plan, const srs_tensor *t,
                        const int32_t *I, const void *V, const uint32_t *counts, uint64_t cap, void *stream, int eb) {
     if (!ctx || !plan || cap == 0 || plan->device != ctx->device) return SRS_ERR_INVALID;
     if (plan->total == 0) return SRS_OK;
-    if (!t || !I || !V || !counts) return SRS_ERR_INVALID;
+    if (!t || !I || !V || !counts || !slots_ok(plan->nbuckets, cap)) return SRS_ERR_INVALID;
     const uintptr_t amask = (uintptr_t)eb - 1u;
     if (((uintptr_t)V & amask) || (((uintptr_t)I | (uintptr_t)counts) & 3u)) return SRS_ERR_INVALID;
     if (!weight_pointers_ok(plan, t, amask)) return SRS_ERR_INVALID;
@@ -895,7 +901,7 @@ int srs_tensor_indices(srs_ctx *ctx, srs_plan *plan, const int32_t *I, const uin
                        uint32_t *tensor_id, int32_t *tensor_idx, void *stream) {
     if (!ctx || !plan || cap == 0 || plan->device != ctx->device) return SRS_ERR_INVALID;
     if (plan->total == 0) return SRS_OK;
-    if (!I || !counts || !tensor_id || !tensor_idx) return SRS_ERR_INVALID;
+    if (!I || !counts || !tensor_id || !tensor_idx || !slots_ok(plan->nbuckets, cap)) return SRS_ERR_INVALID;
     if (((uintptr_t)I | (uintptr_t)counts | (uintptr_t)tensor_id | (uintptr_t)tensor_idx) & 3u) return SRS_ERR_INVALID;
     hipStream_t st = (hipStream_t)stream;
     SRS_ON_DEVICE(ctx->device);
@@ -994,7 +1000,7 @@ uint64_t srs_anchor_count(uint32_t nbuckets, uint64_t cap) {
 
 int srs_encode_indices(srs_ctx *ctx, const int32_t *I, const uint32_t *counts, uint32_t nbuckets, uint64_t cap,
                        uint64_t base_stride, uint16_t *D, uint32_t *max_gap, int32_t *anchors, void *stream) {
-    if (!ctx || cap == 0 || base_stride > kMaxIndexable) return SRS_ERR_INVALID;
+    if (!ctx || cap == 0 || cap > kMaxSlots || base_stride > kMaxIndexable) return SRS_ERR_INVALID;
     if (nbuckets == 0) return SRS_OK;
     if (!I || !counts || !D || !max_gap || !anchors) return SRS_ERR_INVALID;
     if (((uintptr_t)D & 1u) || (((uintptr_t)I | (uintptr_t)counts | (uintptr_t)max_gap | (uintptr_t)anchors) & 3u))
@@ -1027,7 +1033,7 @@ int srs_apply_encoded(srs_ctx *ctx, void *weights, uint64_t n, uint64_t bucket_e
                       const int32_t *anchors, uint64_t cap, void *stream) {
     if (!ctx || bucket_elems == 0 || cap == 0 || n > kMaxIndexable || bucket_elems > kMaxIndexable) return SRS_ERR_INVALID;
     if (n == 0) return SRS_OK;
-    if (!weights || ((uintptr_t)weights & 1u) || !encoded_args_ok(D, I_wide, V, counts, max_gap, anchors)) return SRS_ERR_INVALID;
+    if (cap > kMaxSlots || !weights || ((uintptr_t)weights & 1u) || !encoded_args_ok(D, I_wide, V, counts, max_gap, anchors)) return SRS_ERR_INVALID;
     hipStream_t st = (hipStream_t)stream;
     SRS_ON_DEVICE(ctx->device);
     const uint64_t nb = (n + bucket_elems - 1) / bucket_elems;
@@ -1050,7 +1056,7 @@ int srs_apply_multi_encoded(srs_ctx *ctx, srs_plan *plan, const srs_tensor *t, c
                             uint64_t cap, void *stream) {
     if (!ctx || !plan || cap == 0 || plan->device != ctx->device) return SRS_ERR_INVALID;
     if (plan->total == 0) return SRS_OK;
-    if (!t || !encoded_args_ok(D, I_wide, V, counts, max_gap, anchors)) return SRS_ERR_INVALID;
+    if (cap > kMaxSlots || !t || !encoded_args_ok(D, I_wide, V, counts, max_gap, anchors)) return SRS_ERR_INVALID;
     if (!weight_pointers_ok(plan, t, 1u)) return SRS_ERR_INVALID;
     hipStream_t st = (hipStream_t)stream;
     SRS_ON_DEVICE(ctx->device);
@@ -1128,7 +1134,7 @@ uint64_t srs_value_chunks(uint64_t cap) { return (cap + kVcChunk - 1) / kVcChunk
 
 int srs_encode_values(srs_ctx *ctx, const uint16_t *V, const uint32_t *counts, uint32_t nbuckets, uint64_t cap,
                       uint8_t *lens, uint8_t *low, uint32_t *bits, uint32_t *chunk_words, uint16_t *sub, void *stream) {
-    if (!ctx || cap == 0) return SRS_ERR_INVALID;
+    if (!ctx || cap == 0 || cap > kMaxSlots) return SRS_ERR_INVALID;
     if (nbuckets == 0) return SRS_OK;
     if (!V || !counts || !lens || !low || !bits || !chunk_words || !sub) return SRS_ERR_INVALID;
     if ((((uintptr_t)V | (uintptr_t)sub) & 1u) || (((uintptr_t)counts | (uintptr_t)bits | (uintptr_t)chunk_words) & 3u))
@@ -1164,7 +1170,7 @@ int srs_encode_values(srs_ctx *ctx, const uint16_t *V, const uint32_t *counts, u
 int srs_decode_values(srs_ctx *ctx, const uint8_t *lens, const uint8_t *low, const uint32_t *bits,
                       const uint32_t *chunk_words, const uint16_t *sub, const uint32_t *counts, uint32_t nbuckets,
                       uint64_t cap, uint16_t *V_out, void *stream) {
-    if (!ctx || cap == 0) return SRS_ERR_INVALID;
+    if (!ctx || cap == 0 || cap > kMaxSlots) return SRS_ERR_INVALID;
     if (nbuckets == 0) return SRS_OK;
     if (!lens || !low || !bits || !chunk_words || !sub || !counts || !V_out) return SRS_ERR_INVALID;
     if ((((uintptr_t)V_out | (uintptr_t)sub) & 1u) || (((uintptr_t)counts | (uintptr_t)bits | (uintptr_t)chunk_words) & 3u))

@@ -164,6 +164,12 @@ def _dev16(t: torch.Tensor, what: str, width: int = 2) -> None:
         raise TypeError(f"{what}: expected a contiguous {8 * width}-bit tensor on the GPU")
 
 
+def _not_negative(where: str, *sizes: int) -> None:
+    """ctypes would pass -k as 2^64 - k."""
+    if min(sizes) < 0:
+        raise SrsError(ERR_INVALID, where)
+
+
 def _payload_ok(I: torch.Tensor, V: torch.Tensor, counts: torch.Tensor, nb: int, cap: int, width: int = 2) -> None:
     if not (I.is_cuda and I.dtype == torch.int32 and I.is_contiguous() and I.numel() >= nb * cap):
         raise TypeError("I: expected contiguous int32 GPU tensor of at least nb*cap elements")
@@ -279,6 +285,7 @@ class Context:
             raise ValueError("old/new size mismatch")
         if bucket_elems > 0 and cap > 0:
             _payload_ok(I, V, counts, (n + bucket_elems - 1) // bucket_elems, cap)
+        _not_negative("srs_extract", cap)
         _check(_lib.srs_extract(self._h, old.data_ptr(), new.data_ptr(), n, bucket_elems, I.data_ptr(), V.data_ptr(),
                                 counts.data_ptr(), cap, _stream_ptr(stream)), "srs_extract")
 
@@ -292,6 +299,7 @@ class Context:
             raise ValueError("old/new size mismatch")
         if bucket_elems > 0 and cap > 0:
             _payload_ok(I, V, counts, (n + bucket_elems - 1) // bucket_elems, cap)
+        _not_negative("srs_extract_noalloc", cap)
         _check(_lib.srs_extract_noalloc(self._h, old.data_ptr(), new.data_ptr(), n, bucket_elems, I.data_ptr(),
                                         V.data_ptr(), counts.data_ptr(), cap, _stream_ptr(stream)),
                "srs_extract_noalloc")
@@ -304,6 +312,7 @@ class Context:
         n = weights.numel()
         if bucket_elems > 0 and cap > 0:
             _payload_ok(I, V, counts, (n + bucket_elems - 1) // bucket_elems, cap)
+        _not_negative("srs_apply", cap)
         _check(_lib.srs_apply(self._h, weights.data_ptr(), n, bucket_elems, I.data_ptr(), V.data_ptr(),
                               counts.data_ptr(), cap, _stream_ptr(stream)), "srs_apply")
 
@@ -342,6 +351,7 @@ class Context:
             pairs = self.bind_pairs(plan, old, new)
         if cap > 0:
             _payload_ok(I, V, counts, plan.nbuckets, cap)
+        _not_negative("srs_extract_multi", cap)
         _check(_lib.srs_extract_multi(self._h, plan._h, pairs, I.data_ptr(), V.data_ptr(), counts.data_ptr(), cap,
                                       _stream_ptr(stream)), "srs_extract_multi")
 
@@ -351,6 +361,7 @@ class Context:
             tensors = self.bind_weights(plan, weights)
         if cap > 0:
             _payload_ok(I, V, counts, plan.nbuckets, cap)
+        _not_negative("srs_apply_multi", cap)
         _check(_lib.srs_apply_multi(self._h, plan._h, tensors, I.data_ptr(), V.data_ptr(), counts.data_ptr(), cap,
                                     _stream_ptr(stream)), "srs_apply_multi")
 
@@ -362,6 +373,7 @@ class Context:
                 raise TypeError(f"{what}: expected contiguous 32-bit GPU tensor of at least nb*cap elements")
         if not (counts.is_cuda and counts.element_size() == 4 and counts.numel() >= plan.nbuckets):
             raise TypeError("counts: expected 32-bit GPU tensor of at least nb elements")
+        _not_negative("srs_tensor_indices", cap)
         _check(_lib.srs_tensor_indices(self._h, plan._h, I.data_ptr(), counts.data_ptr(), cap, tensor_id.data_ptr(),
                                        tensor_idx.data_ptr(), _stream_ptr(stream)), "srs_tensor_indices")
 
@@ -376,6 +388,7 @@ class Context:
             raise ValueError("old/new size mismatch")
         if bucket_elems > 0 and cap > 0:
             _payload_ok(I, V, counts, (n + bucket_elems - 1) // bucket_elems, cap, 1)
+        _not_negative("srs_extract_u8", cap)
         _check(_lib.srs_extract_u8(self._h, old.data_ptr(), new.data_ptr(), n, bucket_elems, I.data_ptr(),
                                    V.data_ptr(), counts.data_ptr(), cap, _stream_ptr(stream)), "srs_extract_u8")
 
@@ -387,6 +400,7 @@ class Context:
         n = weights.numel()
         if bucket_elems > 0 and cap > 0:
             _payload_ok(I, V, counts, (n + bucket_elems - 1) // bucket_elems, cap, 1)
+        _not_negative("srs_apply_u8", cap)
         _check(_lib.srs_apply_u8(self._h, weights.data_ptr(), n, bucket_elems, I.data_ptr(), V.data_ptr(),
                                  counts.data_ptr(), cap, _stream_ptr(stream)), "srs_apply_u8")
 
@@ -397,6 +411,7 @@ class Context:
             pairs = self.bind_pairs(plan, old, new, 1)
         if cap > 0:
             _payload_ok(I, V, counts, plan.nbuckets, cap, 1)
+        _not_negative("srs_extract_multi_u8", cap)
         _check(_lib.srs_extract_multi_u8(self._h, plan._h, pairs, I.data_ptr(), V.data_ptr(), counts.data_ptr(), cap,
                                          _stream_ptr(stream)), "srs_extract_multi_u8")
 
@@ -406,6 +421,7 @@ class Context:
             tensors = self.bind_weights(plan, weights, 1)
         if cap > 0:
             _payload_ok(I, V, counts, plan.nbuckets, cap, 1)
+        _not_negative("srs_apply_multi_u8", cap)
         _check(_lib.srs_apply_multi_u8(self._h, plan._h, tensors, I.data_ptr(), V.data_ptr(), counts.data_ptr(), cap,
                                        _stream_ptr(stream)), "srs_apply_multi_u8")
 
@@ -421,6 +437,7 @@ class Context:
         n = weights.numel()
         if bucket_elems > 0 and cap > 0:
             _payload_ok(I, V, counts, (n + bucket_elems - 1) // bucket_elems, cap)
+        _not_negative("srs_extract_cast", cap)
         _check(_lib.srs_extract_cast(self._h, weights.data_ptr(), master.data_ptr(), n, bucket_elems, I.data_ptr(),
                                      V.data_ptr(), counts.data_ptr(), cap, _stream_ptr(stream)), "srs_extract_cast")
 
@@ -444,6 +461,7 @@ class Context:
             pairs = self.bind_cast_pairs(plan, weights, master)
         if cap > 0:
             _payload_ok(I, V, counts, plan.nbuckets, cap)
+        _not_negative("srs_extract_cast_multi", cap)
         _check(_lib.srs_extract_cast_multi(self._h, plan._h, pairs, I.data_ptr(), V.data_ptr(), counts.data_ptr(), cap,
                                            _stream_ptr(stream)), "srs_extract_cast_multi")
 
@@ -478,6 +496,7 @@ class Context:
         self._bitmap_ok(plan, bitmap)
         if cap > 0:
             _payload_ok(I, V, counts, plan.nbuckets, cap)
+        _not_negative("srs_extract_marked_multi", cap)
         _check(_lib.srs_extract_marked_multi(self._h, plan._h, tensors, bitmap.data_ptr(), I.data_ptr(), V.data_ptr(),
                                              counts.data_ptr(), cap, _stream_ptr(stream)), "srs_extract_marked_multi")
 
@@ -488,6 +507,7 @@ class Context:
         if not (V.is_cuda and V.element_size() == 2 and V.is_contiguous() and V.numel() >= nbuckets * cap):
             raise TypeError("V: expected contiguous 16-bit GPU tensor of at least nb*cap elements")
         _value_stream_ok(enc, nbuckets, cap)
+        _not_negative("srs_encode_values", nbuckets, cap)
         _check(_lib.srs_encode_values(self._h, V.data_ptr(), counts.data_ptr(), nbuckets, cap, enc["lens"].data_ptr(),
                                       enc["low"].data_ptr(), enc["bits"].data_ptr(), enc["chunk_words"].data_ptr(),
                                       enc["sub"].data_ptr(), _stream_ptr(stream)), "srs_encode_values")
@@ -497,6 +517,7 @@ class Context:
         if not (V_out.is_cuda and V_out.element_size() == 2 and V_out.is_contiguous() and V_out.numel() >= nbuckets * cap):
             raise TypeError("V_out: expected contiguous 16-bit GPU tensor of at least nb*cap elements")
         _value_stream_ok(enc, nbuckets, cap)
+        _not_negative("srs_decode_values", nbuckets, cap)
         _check(_lib.srs_decode_values(self._h, enc["lens"].data_ptr(), enc["low"].data_ptr(), enc["bits"].data_ptr(),
                                       enc["chunk_words"].data_ptr(), enc["sub"].data_ptr(), counts.data_ptr(), nbuckets,
                                       cap, V_out.data_ptr(), _stream_ptr(stream)), "srs_decode_values")
@@ -508,6 +529,7 @@ class Context:
         if cap > 0:
             _payload_ok(I, D, counts, nbuckets, cap)
             _encoded_ok(D, max_gap, anchors, nbuckets, cap)
+        _not_negative("srs_encode_indices", nbuckets, cap)
         _check(_lib.srs_encode_indices(self._h, I.data_ptr(), counts.data_ptr(), nbuckets, cap, base_stride,
                                        D.data_ptr(), max_gap.data_ptr(), anchors.data_ptr(), _stream_ptr(stream)),
                "srs_encode_indices")
@@ -521,6 +543,7 @@ class Context:
             nb = (n + bucket_elems - 1) // bucket_elems
             _payload_ok(I_wide, V, counts, nb, cap)
             _encoded_ok(D, max_gap, anchors, nb, cap)
+        _not_negative("srs_apply_encoded", cap)
         _check(_lib.srs_apply_encoded(self._h, weights.data_ptr(), n, bucket_elems, D.data_ptr(), I_wide.data_ptr(),
                                       V.data_ptr(), counts.data_ptr(), max_gap.data_ptr(), anchors.data_ptr(), cap,
                                       _stream_ptr(stream)), "srs_apply_encoded")
@@ -534,6 +557,7 @@ class Context:
         if cap > 0:
             _payload_ok(I_wide, V, counts, plan.nbuckets, cap)
             _encoded_ok(D, max_gap, anchors, plan.nbuckets, cap)
+        _not_negative("srs_apply_multi_encoded", cap)
         _check(_lib.srs_apply_multi_encoded(self._h, plan._h, tensors, D.data_ptr(), I_wide.data_ptr(), V.data_ptr(),
                                             counts.data_ptr(), max_gap.data_ptr(), anchors.data_ptr(), cap,
                                             _stream_ptr(stream)), "srs_apply_multi_encoded")
@@ -547,6 +571,7 @@ class Context:
                               ("n_dense", n_dense, 1)):
             if not (t.is_cuda and t.element_size() == 4 and t.is_contiguous() and t.numel() >= need):
                 raise TypeError(f"{name}: expected contiguous 32-bit GPU tensor of at least {need} elements")
+        _not_negative("srs_route", nbuckets, max_dense, cap)
         _check(_lib.srs_route(self._h, counts.data_ptr(), nbuckets, bucket_elems, total_elems, cap, bytes_per_pair,
                               max_dense, route_slot.data_ptr(), sparse_counts.data_ptr(), dense_bucket.data_ptr(),
                               n_dense.data_ptr(), _stream_ptr(stream)), "srs_route")
