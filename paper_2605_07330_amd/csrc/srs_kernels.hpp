@@ -414,21 +414,20 @@ __device__ __forceinline__ uint32_t look_back(const ExtractArgs &a, uint32_t epo
     return excl;
 }
 
-// Refresh by lines of a tile read on extract_kernel's grid (ow: first grid position of the wave, lv: this lane's first from there,
-// nw: grid positions of the wave below it form whole vectors, m: change
+// Refresh by lines of a tile read on extract_kernel's grid (og: grid position 0, g0: this lane's first, m: change
 // masks, x: what to write): 8 consecutive grid vectors from a 128-byte boundary on, which begins q lanes before lane 0's
 // vector; the line across the end of a row has its other vectors in the next row.
 template <int V, class T>
-__device__ __forceinline__ void refresh_lines(gptr<T> ow, uint32_t lv, uint32_t nw, bool in_head, const uint32_t (&m)[V],
+__device__ __forceinline__ void refresh_lines(gptr<T> og, uint32_t g0, uint32_t nbody, bool in_head, const uint32_t (&m)[V],
                                               const u32x4 (&x)[V], int lane) {
     constexpr uint32_t ROW = 64u * 16u / sizeof(T);
-    const uint32_t q = ((uint32_t)(uintptr_t)ow >> 4) & 7u;             // uniform
+    const uint32_t q = ((uint32_t)(uintptr_t)og >> 4) & 7u;             // uniform
     if (q == 0) {
 #pragma unroll
         for (int j = 0; j < V; ++j) {
             const unsigned long long changed = __ballot(m[j] != 0);
-            if (((uint32_t)(changed >> (lane & ~7)) & 0xFFu) && lv + j * ROW < nw && (j > 0 || !in_head))
-                store16_nt(scalar_base(ow + (j & ~3) * ROW) + lv + (j & 3) * ROW, x[j]);
+            const uint32_t g = g0 + j * ROW;
+            if (((uint32_t)(changed >> (lane & ~7)) & 0xFFu) && g < nbody && (j > 0 || !in_head)) store16_nt(og + g, x[j]);
         }
     } else {
         const int first = (int)(((uint32_t)lane + q) & ~7u) - (int)q;                            // -7 .. 63
@@ -438,8 +437,8 @@ __device__ __forceinline__ void refresh_lines(gptr<T> ow, uint32_t lv, uint32_t 
             const unsigned long long next = (j + 1 < V) ? __ballot(m[(j + 1) % V] != 0) : 0ull;
             uint32_t line = (first < 0) ? (uint32_t)((cur << -first) | (prev >> (64 + first))) : (uint32_t)(cur >> first);
             if (first > 56) line |= (uint32_t)(next << (64 - first));
-            if ((line & 0xFFu) && lv + j * ROW < nw && (j > 0 || !in_head))
-                store16_nt(scalar_base(ow + (j & ~3) * ROW) + lv + (j & 3) * ROW, x[j]);
+            const uint32_t g = g0 + j * ROW;
+            if ((line & 0xFFu) && g < nbody && (j > 0 || !in_head)) store16_nt(og + g, x[j]);
             prev = cur; cur = next;
         }
     }
@@ -590,11 +589,14 @@ __global__ __launch_bounds__(kThreads, waves_per_simd(V, MULTI, SRC, EB)) void e
     // incomplete vector in front (thread 0's first) and one behind the last whole vector (thread kThreads-1 takes it, as
     // a vector of its own that ranks after all others).  Those two are read as the tile's first and last 16 bytes, at any
     // address, and shifted to their place; a tile shorter than a vector is read element by element.
-    // Lanes that have no vector read the tile's first 16 bytes as well, and a tile shorter than a vector reads the flag word:
-    // one run of loads without a branch in it serves every tile, and all of them are in flight together.  Measured with what
-    // follows below, us, extract only: 300 odd-sized tensors end to end (108 M elements, 1 % changed) 119 -> 107, with the
-    // snapshot rotated and the new weights six bytes off 98 -> 80.
-    u32x4 xo[V], xn[V], f1[CAST ? V : 1], to, tn, tn1;
+    // All loads of a tile are in flight together: lanes that have no vector read the tile's first 16 bytes as well, and a tile
+    // shorter than a vector reads the flag word.  Measured with what follows below, us, extract only, element by element / so:
+    // 300 odd-sized tensors end to end (108 M elements, 1 % changed) 119 / 106, with the snapshot rotated and the new weights six
+    // bytes off 98 / 80.  Whole tiles have a run of loads without a branch; in the others a wave leaves out fours of vectors that
+    // it has none of, and does not pace what is left.  One run for both was slower wherever tiles are short, us: those 300
+    // tensors in buckets of 9000 elements at 5 % in place 222 / 170, of 3000 at 1 % 441 / 295, cast in buckets of 9000 283 / 247,
+    // one tensor of 1000 elements 3.5 / 3.3; and it took a spill in tiles of 16384 with masters and one-byte elements.
+    u32x4 xo[V], xn[V], f1[CAST ? V : 1], to, tn, tn1;                   // f1, tn1: second halves of master vectors; to, tn: the tail
     const uint32_t h = (uint32_t)((uintptr_t)po & 15u) / EB;
     const uint32_t glen = len + h;                                      // grid positions h .. glen-1 exist
     const uint32_t nbody = (glen < TILE ? glen : TILE) / VE * VE;       // positions below it form whole vectors (but for h)
@@ -610,50 +612,92 @@ __global__ __launch_bounds__(kThreads, waves_per_simd(V, MULTI, SRC, EB)) void e
     const bool short_tile = len < VE;                                   // uniform
     const u32x4 none = {0u, 0u, 0u, 0u};
     constexpr bool H = NT || LINES;
-    const gptr<const uint8_t> ob = scalar_base(short_tile ? (gptr<const uint8_t>)as_global(a.flags) : (gptr<const uint8_t>)og);
-    const gptr<const uint8_t> nb = scalar_base(short_tile ? (gptr<const uint8_t>)as_global(a.flags)
-                                               : CAST ? (gptr<const uint8_t>)fg : (gptr<const uint8_t>)ng);
-    const uint32_t spare = short_tile ? 0u : h;
-    auto has_vector = [&](int j) -> bool { return lv + j * ROW < nw && !(j == 0 && in_head); };
-    auto position = [&](int j) -> uint32_t { return has_vector(j) ? wbase + lv + j * ROW : spare; };
-
-    __builtin_amdgcn_sched_barrier(0);
-    uint32_t t_pos = has_tail && !short_tile ? glen - VE : spare;
-    asm volatile("" : "+v"(t_pos));       // uniform: the compiler would wait for the loads to move them to scalar registers
-    tn = load16_any<false>(nb + t_pos * NB);
-    if (CAST) tn1 = load16_any<false>(nb + (t_pos * NB + 16u));
-    __builtin_amdgcn_sched_barrier(0);
-    auto pace = [&](auto clocks) {
-        constexpr int C = decltype(clocks)::value;
-        if constexpr (C > 0) {
-            __builtin_amdgcn_sched_barrier(0); __builtin_amdgcn_s_sleep(C); __builtin_amdgcn_sched_barrier(0);
+    uint32_t m[V], ex[V], counted = 0;
+    const std::integral_constant<int, CAST ? kLoadPace / 2 : (RG >= 0) ? kLoadPace : 0> p;
+    auto stream_tile = [&](auto whole) {
+        constexpr bool W = decltype(whole)::value;           // every vector exists, but for thread 0's first
+        const gptr<const uint8_t> ob = scalar_base(!W && short_tile ? (gptr<const uint8_t>)as_global(a.flags) : (gptr<const uint8_t>)og);
+        const gptr<const uint8_t> nb = scalar_base(!W && short_tile ? (gptr<const uint8_t>)as_global(a.flags)
+                                                   : CAST ? (gptr<const uint8_t>)fg : (gptr<const uint8_t>)ng);
+        const uint32_t spare = !W && short_tile ? 0u : h;
+        auto has_vector = [&](int j) -> bool { return (W || lv + j * ROW < nw) && !(j == 0 && in_head); };
+        auto position = [&](int j) -> uint32_t { return (W && j) || has_vector(j) ? wbase + lv + j * ROW : spare; };
+        auto pace = [&](auto clocks) {
+            constexpr int C = decltype(clocks)::value;
+            if constexpr (W && C > 0) {
+                __builtin_amdgcn_sched_barrier(0); __builtin_amdgcn_s_sleep(C); __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        constexpr int G = V < 4 ? V : 4;                     // an incomplete tile loads or leaves out so many vectors together
+        __builtin_amdgcn_sched_barrier(0);
+        uint32_t t_pos = has_tail && !short_tile ? glen - VE : spare;
+        asm volatile("" : "+v"(t_pos));       // uniform: the compiler would wait for the loads to move them to scalar registers
+        tn = load16_any<false>(nb + t_pos * NB);
+        if (CAST) tn1 = load16_any<false>(nb + (t_pos * NB + 16u));
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < V; i += G) {
+            if (W || i * ROW < nw) {
+#pragma unroll
+                for (int j = i; j < i + G; ++j) {
+                    xn[j] = load16_any<H && !CAST>(nb + position(j) * NB); pace(p);
+                    if (CAST) { f1[j] = load16_any<false>(nb + (position(j) * NB + 16u)); pace(p); }
+                }
+            } else {
+#pragma unroll
+                for (int j = i; j < i + G; ++j) { xn[j] = none; if (CAST) f1[j] = none; }
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        fresh();
+        to = load16_any<false>(ob + t_pos * (uint32_t)EB);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < V; i += G) {
+            if (W || i * ROW < nw) {
+#pragma unroll
+                for (int j = i; j < i + G; ++j) { xo[j] = load16_any<H>(ob + position(j) * (uint32_t)EB); pace(p); }
+            } else {
+#pragma unroll
+                for (int j = i; j < i + G; ++j) xo[j] = none;
+            }
+        }
+        if (chained && last && tid == 0) counted = count_claimed(a);           // returns with the loads
+        fresh();
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 0; j < V; ++j) {
+            if (CAST) xn[j] = round8_bf16(xn[j], f1[j]);
+            m[j] = EL::diff_mask(xo[j], xn[j]);
+            if (!W && !has_vector(j)) m[j] = 0;
+            if (j % 4 == 3) __builtin_amdgcn_sched_barrier(0);
         }
     };
-    const std::integral_constant<int, CAST ? kLoadPace / 2 : (RG >= 0) ? kLoadPace : 0> p;
-#pragma unroll
-    for (int j = 0; j < V; ++j) {
-        xn[j] = load16_any<H && !CAST>(nb + position(j) * NB); pace(p);
-        if (CAST) { f1[j] = load16_any<false>(nb + (position(j) * NB + 16u)); pace(p); }
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    fresh();
-    to = load16_any<false>(ob + t_pos * (uint32_t)EB);
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int j = 0; j < V; ++j) { xo[j] = load16_any<H>(ob + position(j) * (uint32_t)EB); pace(p); }
+    if (glen >= TILE) stream_tile(std::true_type{});
+    else stream_tile(std::false_type{});
 
-    uint32_t counted = 0;
-    if (chained && last && tid == 0) counted = count_claimed(a);           // returns with the loads
-
-    // ---- change masks and their counts, the tail's first (its loads went out ahead of each stream)
-    fresh();
-    uint32_t m[V], ex[V];
     auto refresh_incomplete = [&](uint32_t at, uint32_t mm, u32x4 x) {      // element by element
         for (; mm; mm &= mm - 1u) {
             const uint32_t e = (uint32_t)__builtin_ctz(mm);
             og[at + e] = (T)EL::pattern(x, e);
         }
     };
+    if (in_head) {
+        // the front: elements 0 .. VE-h-1 of the tile, to positions h .. VE-1
+        u32x4 vo, vn;
+        if (short_tile) {
+            const uint32_t hi = glen < VE ? 0u : VE;                    // (a tile within one vector is all tail)
+            vo = EL::load_window(og, h, hi);
+            if constexpr (CAST) vn = load8_window_cast(fg, h, hi);
+            else vn = EL::load_window(ng, h, hi);
+        } else {
+            vo = shift_up(xo[0], h * EB);
+            vn = shift_up(xn[0], h * EB);
+        }
+        xn[0] = vn;
+        m[0] = EL::diff_mask(vo, vn);
+        if (LINES) refresh_incomplete(0, m[0], vn);
+    }
     if (has_tail && tid == kThreads - 1) {
         uint32_t md;
         u32x4 vn;
@@ -673,30 +717,6 @@ __global__ __launch_bounds__(kThreads, waves_per_simd(V, MULTI, SRC, EB)) void e
         s_tail_mask = md;
         if (LINES) refresh_incomplete(nbody, md, vn);
     }
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int j = 0; j < V; ++j) {
-        if (CAST) xn[j] = round8_bf16(xn[j], f1[j]);
-        m[j] = EL::diff_mask(xo[j], xn[j]);
-        if (!has_vector(j)) m[j] = 0;
-        if (j == 0 && in_head) {
-            // the front: elements 0 .. VE-h-1 of the tile, to positions h .. VE-1
-            u32x4 vo, vn;
-            if (short_tile) {
-                const uint32_t hi = glen < VE ? 0u : VE;                    // (a tile within one vector is all tail)
-                vo = EL::load_window(og, h, hi);
-                if constexpr (CAST) vn = load8_window_cast(fg, h, hi);
-                else vn = EL::load_window(ng, h, hi);
-            } else {
-                vo = shift_up(xo[0], h * EB);
-                vn = shift_up(xn[0], h * EB);
-            }
-            xn[0] = vn;
-            m[0] = EL::diff_mask(vo, vn);
-            if (LINES) refresh_incomplete(0, m[0], vn);
-        }
-        if (j % 4 == 3) __builtin_amdgcn_sched_barrier(0);
-    }
 
     // ---- wave scan (two vectors per register), then the rank of this lane's first changed element of each vector
     uint32_t wave_total = 0;
@@ -711,7 +731,7 @@ __global__ __launch_bounds__(kThreads, waves_per_simd(V, MULTI, SRC, EB)) void e
         ex[2 * q + 1] = wave_total + (exc >> 16);
         wave_total += tot >> 16;
     }
-    if (LINES) refresh_lines<V, T>(og + wbase, lv, nw, in_head, m, xn, lane);
+    if (LINES) refresh_lines<V, T>(og, wbase + lv, nbody, in_head, m, xn, lane);
     fresh();
     if (lane == 0) s_wave_total[wave] = wave_total;
     __syncthreads();
@@ -1126,8 +1146,7 @@ __global__ __launch_bounds__(kThreads) void mark_kernel(const ExtractArgs a) {
     uint32_t m[V];
 #pragma unroll
     for (int j = 0; j < V; ++j) m[j] = diff_mask8(xo[j], xn[j]);
-    const uint32_t wbase = uniform((uint32_t)wave) * (V * 512u);
-    if (CAST) refresh_lines<V, uint16_t>(og + wbase, (uint32_t)lane * 8u, nbody > wbase ? nbody - wbase : 0u, in_head, m, xn, lane);   // write the cast back where it changed something
+    if (CAST) refresh_lines<V, uint16_t>(og, g0, nbody, in_head, m, xn, lane);   // write the cast back where it changed something
 #pragma unroll
     for (int j = 0; j < V; ++j)
         if (m[j]) mark(g0 + j * 512, m[j]);

@@ -1,0 +1,63 @@
+"""Tiles that do not fill their workgroup: lengths around every four vectors of a wave (what an incomplete tile loads or leaves out
+together), around the waves' shares, a vector and a whole tile, at every alignment, against the oracle, tolerance 0."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def lengths(tile, ve):
+    """Tensor lengths of a list; each is a tile of its own (or two)."""
+    row = 64 * ve
+    at = {1, 2, ve, 2 * ve, row, tile // 4, tile // 2, tile - row, tile, tile + row}
+    at |= {4 * row * k for k in range(1, tile // (4 * row) + 1)}
+    return sorted({max(1, a + d) for a in at for d in (-ve - 1, -1, 0, 1, ve + 3)})
+
+
+@pytest.mark.parametrize("mode", ["lines", "elements", "rotate"])
+@pytest.mark.parametrize("kind,tile", [("bf16", 32768), ("bf16", 8192), ("bf16", 4096), ("u8", 32768), ("u8", 8192), ("cast", 32768), ("cast", 16384), ("cast", 4096)])
+def test_lengths_around_the_loads(kind, tile, mode):
+    from paper_2605_07330_amd import srs
+    if kind == "cast" and mode == "rotate":
+        pytest.skip("the cast has no snapshot option")
+    print(f"case {kind} tile={tile} {mode}", flush=True)
+    dt = np.uint8 if kind == "u8" else np.uint16
+    rng = np.random.default_rng(tile)
+    numel = [int(x) for x in rng.permutation(lengths(tile, 16 // dt().itemsize))]
+    n, be = sum(numel), 5 * tile + 13                        # a bucket holds several tensors and cuts some
+    mask = rng.random(n) < 0.02
+    mask[np.cumsum([0, *numel[:-1]])] = True                 # the first and the last element of each tensor
+    mask[np.cumsum(numel) - 1] = True
+    if kind == "cast":
+        new = (rng.standard_normal(n) * 0.02).astype(np.float32)
+        old = (oracle.round_bf16(new) ^ mask.astype(np.uint16)).astype(np.uint16)
+    else:
+        old = rng.integers(0, 1 << (8 * dt().itemsize), n).astype(dt)
+        new = (old ^ mask.astype(dt)).astype(dt)
+    split = lambda a: [np.ascontiguousarray(x) for x in np.split(a, np.cumsum(numel)[:-1])]  # noqa: E731
+    after = [x.copy() for x in split(old)]
+    name = {"bf16": "extract_multi", "u8": "extract_multi_u8", "cast": "extract_cast_multi"}[kind]
+    wI, wV, wc = getattr(oracle, name)(after, split(new), numel, be, be)[:3]
+    ctx = srs.Context(0)
+    try:
+        ctx.set_option(srs.OPT_TILE_ELEMS, tile)
+        ctx.set_option(srs.OPT_REFRESH_GROUP, 0 if mode == "elements" else 8)
+        ctx.set_option(srs.OPT_SNAPSHOT, 1 if mode == "rotate" else 0)
+        plan = ctx.plan(numel, be)
+        as_torch = lambda a: torch.from_numpy(a.view(np.int16) if a.dtype == np.uint16 else a).to(DEV)  # noqa: E731
+        t, u = as_torch(old.copy()), as_torch(new)           # end to end: every alignment
+        I, V, counts = (srs.alloc_payload_u8 if kind == "u8" else srs.alloc_payload)(plan.nbuckets, be, DEV)
+        getattr(ctx, name)(plan, list(torch.split(t, numel)), list(torch.split(u, numel)), I, V, counts, be)
+        assert ctx.status() == 0
+        assert np.array_equal(counts.cpu().numpy().view(np.uint32), wc)
+        gI, gV = I.cpu().numpy().reshape(len(wc), be), V.cpu().numpy().view(dt).reshape(len(wc), be)
+        for b, c in enumerate(wc):
+            assert np.array_equal(gI[b, :c], wI[b, :c]) and np.array_equal(gV[b, :c], wV[b, :c]), b
+        assert np.array_equal(t.cpu().numpy().view(dt), old if mode == "rotate" else np.concatenate(after))
+        plan.close()
+    finally:
+        ctx.close()

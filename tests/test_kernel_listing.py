@@ -48,3 +48,9 @@ def test_one_stream_after_the_other(kernels, name, vectors):
 def test_resident_waves(kernels, name, waves):
     """The path of incomplete tiles must not take registers from the path of whole ones."""
     assert int(re.search(r"; Occupancy: (\d+)", kernels[name]).group(1)) >= waves
+
+
+def test_no_extract_kernel_spills(kernels):
+    """Occupancy that is reached by keeping registers in scratch memory is none."""
+    spilled = {n: s for n, b in kernels.items() if n.startswith("extract_") and (s := int(re.search(r"; ScratchSize: (\d+)", b).group(1)))}
+    assert not spilled
