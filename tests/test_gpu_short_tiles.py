@@ -61,3 +61,45 @@ def test_lengths_around_the_loads(kind, tile, mode):
         plan.close()
     finally:
         ctx.close()
+
+
+@pytest.mark.parametrize("mode", ["lines", "rotate"])
+@pytest.mark.parametrize("kind,tile", [("bf16", 32768), ("cast", 32768), ("u8", 32768), ("bf16", 8192)])
+@pytest.mark.parametrize("per", [1, 3, 40])
+def test_pairs_around_what_one_wave_writes_out(kind, tile, mode, per):
+    """Tiles with as many pairs as one wave still writes out, one fewer and one more, and full rounds, in chains and alone in their
+    buckets; a capacity that cuts some off."""
+    from paper_2605_07330_amd import srs
+    if kind == "cast" and mode == "rotate":
+        pytest.skip("the cast has no snapshot option")
+    print(f"case {kind} tile={tile} {mode} per={per}", flush=True)
+    dt = np.uint8 if kind == "u8" else np.uint16
+    rng = np.random.default_rng(per)
+    n, be = 40 * tile, per * tile
+    mask = np.zeros(n, bool)
+    for k in range(40):
+        mask[k * tile + rng.permutation(tile)[:int(rng.choice([0, 1, 64, 1023, 1024, 1025, 2047, 2048]))]] = True
+    if kind == "cast":
+        new = (rng.standard_normal(n) * 0.02).astype(np.float32)
+        old = (oracle.round_bf16(new) ^ mask.astype(np.uint16)).astype(np.uint16)
+    else:
+        old = rng.integers(0, 1 << (8 * dt().itemsize), n).astype(dt)
+        new = (old ^ mask.astype(dt)).astype(dt)
+    cap, after = per * 1200, old.copy()
+    wI, wV, wc = {"bf16": oracle.extract, "u8": oracle.extract_u8, "cast": oracle.extract_cast}[kind](after, new, be, cap)[:3]
+    ctx = srs.Context(0)
+    try:
+        ctx.set_option(srs.OPT_TILE_ELEMS, tile)
+        ctx.set_option(srs.OPT_SNAPSHOT, 1 if mode == "rotate" else 0)
+        as_torch = lambda a: torch.from_numpy(a.view(np.int16) if a.dtype == np.uint16 else a).to(DEV)  # noqa: E731
+        t, u = as_torch(old.copy()), as_torch(new)
+        I, V, counts = (srs.alloc_payload_u8 if kind == "u8" else srs.alloc_payload)(len(wc), cap, DEV)
+        {"bf16": ctx.extract, "u8": ctx.extract_u8, "cast": ctx.extract_cast}[kind](t, u, be, I, V, counts, cap)
+        assert ctx.status() == (srs.FLAG_OVERFLOW if (np.asarray(wc) > cap).any() else 0)
+        assert np.array_equal(counts.cpu().numpy().view(np.uint32)[:len(wc)], wc)
+        gI, gV = I.cpu().numpy().reshape(len(wc), cap), V.cpu().numpy().view(dt).reshape(len(wc), cap)
+        for b, c in enumerate(np.minimum(wc, cap)):
+            assert np.array_equal(gI[b, :c], wI[b, :c]) and np.array_equal(gV[b, :c], wV[b, :c]), b
+        assert np.array_equal(t.cpu().numpy().view(dt), old if mode == "rotate" else after)
+    finally:
+        ctx.close()
