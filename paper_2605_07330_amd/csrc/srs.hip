@@ -88,6 +88,8 @@ struct srs_plan {
     uint32_t ntensors = 0, nbuckets = 0, nsegments = 0, ntiles = 0, tile_elems = 0;
     uint32_t max_bucket_tiles = 0;          // most tiles in any one bucket
     uint32_t chained_buckets = 0;           // buckets of more than one tile
+    std::vector<uint32_t> whole_tiles;      // [ntensors] tiles of the full size whose offset in the tensor is a multiple of 16 bytes
+    uint64_t aligned_tiles = 0;             // of them, those of tensors whose snapshot in h_pairs lies on a 16-byte boundary
     TileDesc *d_tiles = nullptr;
     uint64_t *d_tensor_base = nullptr;      // [ntensors] packed position of each tensor's element 0
     WgInfo *d_wg_info = nullptr;            // [ntiles] bucket served by each workgroup of extract, and that bucket's tiles
@@ -197,8 +199,19 @@ int launch_extract_u8(const srs_ctx *ctx, uint32_t tile_elems, const ExtractArgs
 // (0.2 GB) 33 / 39; eight 8B-shaped layers (3.1 GB) 636 / 607, four 32B-shaped (3.9 GB) 209 / 197, four 30B-A3B-shaped 672 / 653.
 constexpr uint64_t kHintedGatherWords = (1ull << 29) / 32;      // in words of the bitmap: 2^29 elements
 
+// Lists nine of ten of whose tiles are whole and aligned go to extract_whole_kernel: refreshed in place always, with the snapshot left
+// alone from kManyChains buckets of several tiles on.  extract_kernel / it, us, extract only:
+// - share of whole tiles, in place at 1 %, 1 G elements: 50 % 935 / 954, 75 % 945 / 947, 83 % 918 / 915, 90 % 925 / 924, 95 % 908 /
+//   914, 98 % 903 / 896, all but a few 901 / 895; 200 M: 50 % 188.3 / 189.5, 75 % 184.7 / 184.8, 90 % 186.3 / 185.9, 95 % 185.5 / 183.6.
+// - in place, all whole: one 8B-shaped layer at 0.6 % 0, four at 1 % -0.7 %, eight 32B-shaped -0.5 to -1 %, six 30B-A3B-shaped
+//   -0.7 %, the 8B-shaped set 6990 / 6930.
+// - snapshot left alone, mean of four to eight placements: one and two 8B-shaped layers (6 and 12 buckets) -1 to +3 %, sixteen at
+//   1 % (92) +1.6 %; from there on the layouts differ: ten 32B-shaped (145) at 0.1 % -0.7 %, fourteen (203) -0.3 %, twelve
+//   30B-A3B-shaped skewed (225) -0.6 %, where a fast placement of the buffers shows most: 4735 / 4640; 8B-shaped (184) up to +0.9 %.
+constexpr uint32_t kManyChains = 128;
+
 template <bool MULTI>
-int launch_extract(const srs_ctx *ctx, uint32_t tile_elems, const ExtractArgs &a, hipStream_t st, int src, int eb = 2) {
+int launch_extract(const srs_ctx *ctx, uint32_t tile_elems, const ExtractArgs &a, hipStream_t st, int src, int eb = 2, bool whole = false) {
     if (eb == 1) return launch_extract_u8<MULTI>(ctx, tile_elems, a, st);
     const dim3 grid(a.ntiles), block(kThreads);
     if (src == kSrcBitmap) {                   // the bitmap says where the changes are: gather, do not stream
@@ -229,6 +242,18 @@ int launch_extract(const srs_ctx *ctx, uint32_t tile_elems, const ExtractArgs &a
         else if (ctx->refresh_group == 8) hipLaunchKernelGGL((extract_kernel<VV, MULTI, 8>), grid, block, 0, st, a);  \
         else hipLaunchKernelGGL((extract_kernel<VV, MULTI, 0>), grid, block, 0, st, a);                               \
     } while (0)
+    if constexpr (MULTI) {
+        if (whole && src == kSrcBf16 && tile_elems == 32768 && ctx->snapshot_mode == 0 && ctx->refresh_group == 8) {
+            hipLaunchKernelGGL((extract_whole_kernel<8>), grid, block, 0, st, a);
+            SRS_HIP(hipGetLastError());
+            return SRS_OK;
+        }
+        if (whole && src == kSrcBf16 && tile_elems == 32768 && ctx->snapshot_mode != 0 && a.chained >= kManyChains) {
+            hipLaunchKernelGGL((extract_whole_kernel<-1>), grid, block, 0, st, a);
+            SRS_HIP(hipGetLastError());
+            return SRS_OK;
+        }
+    }
     switch (tile_elems) {
         case 4096: SRS_LAUNCH(2); break;
         case 8192: SRS_LAUNCH(4); break;
@@ -340,6 +365,9 @@ bool weight_pointers_ok(const srs_plan *plan, const srs_tensor *t, uintptr_t mas
     return true;
 }
 
+// Is it a list for extract_whole_kernel?
+bool mostly_whole(const srs_plan *plan) { return plan->aligned_tiles * 10 >= (uint64_t)plan->ntiles * 9; }
+
 // keeps the device copy of the extract-side pointer table in step with the caller's array
 int upload_pair_pointers(srs_plan *plan, const srs_tensor_pair *t, hipStream_t st) {
     bool same = plan->pairs_valid;
@@ -348,6 +376,9 @@ int upload_pair_pointers(srs_plan *plan, const srs_tensor_pair *t, hipStream_t s
     if (!same) {
         for (uint32_t k = 0; k < plan->ntensors; ++k)
             plan->h_pairs[k] = PtrPair{(uint16_t *)t[k].old_snapshot, t[k].new_w};
+        plan->aligned_tiles = 0;
+        for (uint32_t k = 0; k < plan->ntensors; ++k)
+            if (((uintptr_t)t[k].old_snapshot & 15u) == 0) plan->aligned_tiles += plan->whole_tiles[k];
         plan->pairs_valid = false;
         SRS_HIP(hipMemcpyAsync(plan->d_pairs, plan->h_pairs.data(), plan->ntensors * sizeof(PtrPair), hipMemcpyHostToDevice, st));
         plan->pairs_valid = true;
@@ -576,7 +607,7 @@ int extract_multi(srs_ctx *ctx, srs_plan *plan, const srs_tensor_pair *t,
     a.flags = ctx->flags;
     a.spin_limit = ctx->spin_limit;
     a.bitmap = const_cast<uint32_t *>(bitmap); a.bitmap_words = (plan->total + 31) / 32; a.tensor_base = plan->d_tensor_base;
-    rc = launch_extract<true>(ctx, plan->tile_elems, a, st, src, eb);
+    rc = launch_extract<true>(ctx, plan->tile_elems, a, st, src, eb, mostly_whole(plan));
     if (rc != SRS_OK || !second_pass) return rc;
     return launch_second_pass<true>(ctx, plan, a, plan->be, plan->tile_elems, eb, st);
 }
@@ -764,6 +795,8 @@ int srs_plan_create(srs_ctx *ctx, const uint64_t *numel, uint32_t ntensors, uint
         p->h_wptrs.assign(ntensors, nullptr);
         p->has_elems.resize(ntensors);
         for (uint32_t k = 0; k < ntensors; ++k) p->has_elems[k] = numel[k] != 0;
+        p->whole_tiles.assign(ntensors, 0);
+        for (const TileDesc &d : L.tiles) p->whole_tiles[d.tensor] += (d.len == p->tile_elems && d.tensor_off % 8 == 0);
     } catch (const std::bad_alloc &) {
         delete p; return SRS_ERR_NOMEM;
     }

@@ -313,6 +313,11 @@ template <class T> __device__ __forceinline__ const T __attribute__((address_spa
     return (const T __attribute__((address_space(4))) *)p;
 }
 
+template <bool SCALAR, class T> __device__ __forceinline__ auto table(const T *p) {
+    if constexpr (SCALAR) return as_table(p);
+    else return p;
+}
+
 // ---------------------------------------------------------------------------------------------
 // Tickets and status words need no clearing between launches.  A ticket counter is incremented exactly once per tile
 // of its bucket and wraps to 0 with the last (atomic increment with a limit); status words carry the epoch of the launch that
@@ -494,8 +499,8 @@ __device__ __forceinline__ u32x4 shift_down(u32x4 v, uint32_t bytes) {
     return r;
 }
 
-template <int V, bool MULTI, int RG, int SRC = kSrcBf16, int EB = 2>
-__global__ __launch_bounds__(kThreads, waves_per_simd(V, MULTI, SRC, EB)) void extract_kernel(const ExtractArgs a) {
+template <int V, bool MULTI, int RG, int SRC, int EB, bool WHOLE>
+__device__ __forceinline__ void extract_tile(const ExtractArgs &a) {
     // A snapshot that is not written is read exactly once, like the new weights: both streams then carry the
     // non-temporal hint (measured 4 % faster).  With element-wise refresh the hint on either stream measures slower,
     // on the snapshot by 5 ms: 2-byte refresh stores must find their line still cached, hinted or not.
@@ -566,11 +571,11 @@ __global__ __launch_bounds__(kThreads, waves_per_simd(V, MULTI, SRC, EB)) void e
     uint32_t len, idx_base;
     gptr<T> po; gptr<const uint8_t> pn;
     if (MULTI) {
-        const auto *d = as_table(a.tiles + tile);
+        const auto *d = table<!WHOLE>(a.tiles + tile);
         const uint32_t tensor = d->tensor, off = d->tensor_off;
         len = d->len;
         idx_base = d->bucket_off;                       // index = position inside the bucket
-        const auto *t = as_table(a.ptrs + tensor);
+        const auto *t = table<!WHOLE>(a.ptrs + tensor);
         po = (gptr<T>)t->old_w + off;
         pn = (gptr<const uint8_t>)as_global(t->new_w) + (uint64_t)off * NB;
     } else {
@@ -613,109 +618,144 @@ __global__ __launch_bounds__(kThreads, waves_per_simd(V, MULTI, SRC, EB)) void e
     const u32x4 none = {0u, 0u, 0u, 0u};
     constexpr bool H = NT || LINES;
     uint32_t m[V], ex[V], counted = 0;
-    const std::integral_constant<int, CAST ? kLoadPace / 2 : (RG >= 0) ? kLoadPace : 0> p;
-    auto stream_tile = [&](auto whole) {
-        constexpr bool W = decltype(whole)::value;           // every vector exists, but for thread 0's first
-        const gptr<const uint8_t> ob = scalar_base(!W && short_tile ? (gptr<const uint8_t>)as_global(a.flags) : (gptr<const uint8_t>)og);
-        const gptr<const uint8_t> nb = scalar_base(!W && short_tile ? (gptr<const uint8_t>)as_global(a.flags)
-                                                   : CAST ? (gptr<const uint8_t>)fg : (gptr<const uint8_t>)ng);
-        const uint32_t spare = !W && short_tile ? 0u : h;
-        auto has_vector = [&](int j) -> bool { return (W || lv + j * ROW < nw) && !(j == 0 && in_head); };
-        auto position = [&](int j) -> uint32_t { return (W && j) || has_vector(j) ? wbase + lv + j * ROW : spare; };
-        auto pace = [&](auto clocks) {
-            constexpr int C = decltype(clocks)::value;
-            if constexpr (W && C > 0) {
-                __builtin_amdgcn_sched_barrier(0); __builtin_amdgcn_s_sleep(C); __builtin_amdgcn_sched_barrier(0);
-            }
-        };
-        constexpr int G = V < 4 ? V : 4;                     // an incomplete tile loads or leaves out so many vectors together
-        __builtin_amdgcn_sched_barrier(0);
-        uint32_t t_pos = has_tail && !short_tile ? glen - VE : spare;
-        asm volatile("" : "+v"(t_pos));       // uniform: the compiler would wait for the loads to move them to scalar registers
-        tn = load16_any<false>(nb + t_pos * NB);
-        if (CAST) tn1 = load16_any<false>(nb + (t_pos * NB + 16u));
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int i = 0; i < V; i += G) {
-            if (W || i * ROW < nw) {
-#pragma unroll
-                for (int j = i; j < i + G; ++j) {
-                    xn[j] = load16_any<H && !CAST>(nb + position(j) * NB); pace(p);
-                    if (CAST) { f1[j] = load16_any<false>(nb + (position(j) * NB + 16u)); pace(p); }
-                }
-            } else {
-#pragma unroll
-                for (int j = i; j < i + G; ++j) { xn[j] = none; if (CAST) f1[j] = none; }
-            }
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        fresh();
-        to = load16_any<false>(ob + t_pos * (uint32_t)EB);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int i = 0; i < V; i += G) {
-            if (W || i * ROW < nw) {
-#pragma unroll
-                for (int j = i; j < i + G; ++j) { xo[j] = load16_any<H>(ob + position(j) * (uint32_t)EB); pace(p); }
-            } else {
-#pragma unroll
-                for (int j = i; j < i + G; ++j) xo[j] = none;
-            }
-        }
-        if (chained && last && tid == 0) counted = count_claimed(a);           // returns with the loads
-        fresh();
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int j = 0; j < V; ++j) {
-            if (CAST) xn[j] = round8_bf16(xn[j], f1[j]);
-            m[j] = EL::diff_mask(xo[j], xn[j]);
-            if (!W && !has_vector(j)) m[j] = 0;
-            if (j % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+    auto pace = [&](auto on) {
+        constexpr int C = !decltype(on)::value || RG < 0 ? 0 : CAST ? kLoadPace / 2 : kLoadPace;
+        if constexpr (C > 0) {
+            __builtin_amdgcn_sched_barrier(0); __builtin_amdgcn_s_sleep(C); __builtin_amdgcn_sched_barrier(0);
         }
     };
-    if (glen >= TILE) stream_tile(std::true_type{});
-    else stream_tile(std::false_type{});
-
     auto refresh_incomplete = [&](uint32_t at, uint32_t mm, u32x4 x) {      // element by element
         for (; mm; mm &= mm - 1u) {
             const uint32_t e = (uint32_t)__builtin_ctz(mm);
             og[at + e] = (T)EL::pattern(x, e);
         }
     };
-    if (in_head) {
-        // the front: elements 0 .. VE-h-1 of the tile, to positions h .. VE-1
-        u32x4 vo, vn;
-        if (short_tile) {
-            const uint32_t hi = glen < VE ? 0u : VE;                    // (a tile within one vector is all tail)
-            vo = EL::load_window(og, h, hi);
-            if constexpr (CAST) vn = load8_window_cast(fg, h, hi);
-            else vn = EL::load_window(ng, h, hi);
+    if constexpr (WHOLE) {
+        // Lists nearly all of whose tiles are whole and lie on the 16-byte boundaries: addresses per lane with immediate offsets,
+        // tables by vector loads, and nothing in the way of the other tiles, which are read as simply as can be: even the
+        // branch around the other form's code costs such a list up to 1 %.  Where the host takes which is said there.
+        static_assert(!CAST && EB == 2, "16-bit weights on both sides");
+        const uint32_t g0 = ((uint32_t)tid >> 6) * (V * ROW) + (uint32_t)lane * VE;
+        if (h == 0 && glen == TILE) {
+#pragma unroll
+            for (int j = 0; j < V; ++j) { xn[j] = load16_any<H>(ng + g0 + j * ROW); pace(std::true_type{}); }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int j = 0; j < V; ++j) { xo[j] = load16<H>(og + g0 + j * ROW); pace(std::true_type{}); }
         } else {
-            vo = shift_up(xo[0], h * EB);
-            vn = shift_up(xn[0], h * EB);
+#pragma unroll
+            for (int j = 0; j < V; ++j) {
+                const uint32_t g = g0 + j * ROW;
+                const bool there = g < nbody && (j > 0 || !in_head);
+                xo[j] = there ? load16<H>(og + g) : none;
+                xn[j] = there ? load16_any<H>(ng + g) : none;
+            }
+            const bool front = in_head && nbody != 0;
+            if (front || (has_tail && tid == kThreads - 1)) {
+                const uint32_t at = front ? 0u : nbody;
+                const uint32_t lo = (h > at) ? h - at : 0u, hi = front ? VE : glen - nbody;
+                const u32x4 vo = EL::load_window(og + at, lo, hi), vn = EL::load_window(ng + at, lo, hi);
+                if (front) { xo[0] = vo; xn[0] = vn; }
+                const uint32_t md = EL::diff_mask(vo, vn);
+                if (!front) { s_tail = vn; s_tail_mask = md; }
+                if (LINES) refresh_incomplete(at, md, vn);
+            }
         }
-        xn[0] = vn;
-        m[0] = EL::diff_mask(vo, vn);
-        if (LINES) refresh_incomplete(0, m[0], vn);
-    }
-    if (has_tail && tid == kThreads - 1) {
-        uint32_t md;
-        u32x4 vn;
-        if (short_tile) {
-            const uint32_t lo = (h > nbody) ? h - nbody : 0u, hi = glen - nbody;
-            const u32x4 vo = EL::load_window(og + nbody, lo, hi);
-            if constexpr (CAST) vn = load8_window_cast(fg + nbody, lo, hi);
-            else vn = EL::load_window(ng + nbody, lo, hi);
-            md = EL::diff_mask(vo, vn);
-        } else {
-            const uint32_t down = (VE - (glen - nbody)) * EB;
-            if (CAST) tn = round8_bf16(tn, tn1);
-            vn = shift_down(tn, down);
-            md = EL::diff_mask(shift_down(to, down), vn);
+        if (chained && last && tid == 0) counted = count_claimed(a);           // returns with the loads
+#pragma unroll
+        for (int j = 0; j < V; ++j) m[j] = EL::diff_mask(xo[j], xn[j]);
+    } else {
+        auto stream_tile = [&](auto whole) {
+            constexpr bool W = decltype(whole)::value;           // every vector exists, but for thread 0's first
+            const gptr<const uint8_t> ob = scalar_base(!W && short_tile ? (gptr<const uint8_t>)as_global(a.flags) : (gptr<const uint8_t>)og);
+            const gptr<const uint8_t> nb = scalar_base(!W && short_tile ? (gptr<const uint8_t>)as_global(a.flags)
+                                                       : CAST ? (gptr<const uint8_t>)fg : (gptr<const uint8_t>)ng);
+            const uint32_t spare = !W && short_tile ? 0u : h;
+            auto has_vector = [&](int j) -> bool { return (W || lv + j * ROW < nw) && !(j == 0 && in_head); };
+            auto position = [&](int j) -> uint32_t { return (W && j) || has_vector(j) ? wbase + lv + j * ROW : spare; };
+            constexpr int G = V < 4 ? V : 4;                     // an incomplete tile loads or leaves out so many vectors together
+            __builtin_amdgcn_sched_barrier(0);
+            uint32_t t_pos = has_tail && !short_tile ? glen - VE : spare;
+            asm volatile("" : "+v"(t_pos));       // uniform: the compiler would wait for the loads to move them to scalar registers
+            tn = load16_any<false>(nb + t_pos * NB);
+            if (CAST) tn1 = load16_any<false>(nb + (t_pos * NB + 16u));
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < V; i += G) {
+                if (W || i * ROW < nw) {
+#pragma unroll
+                    for (int j = i; j < i + G; ++j) {
+                        xn[j] = load16_any<H && !CAST>(nb + position(j) * NB); pace(whole);
+                        if (CAST) { f1[j] = load16_any<false>(nb + (position(j) * NB + 16u)); pace(whole); }
+                    }
+                } else {
+#pragma unroll
+                    for (int j = i; j < i + G; ++j) { xn[j] = none; if (CAST) f1[j] = none; }
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            fresh();
+            to = load16_any<false>(ob + t_pos * (uint32_t)EB);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < V; i += G) {
+                if (W || i * ROW < nw) {
+#pragma unroll
+                    for (int j = i; j < i + G; ++j) { xo[j] = load16_any<H>(ob + position(j) * (uint32_t)EB); pace(whole); }
+                } else {
+#pragma unroll
+                    for (int j = i; j < i + G; ++j) xo[j] = none;
+                }
+            }
+            if (chained && last && tid == 0) counted = count_claimed(a);           // returns with the loads
+            fresh();
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int j = 0; j < V; ++j) {
+                if (CAST) xn[j] = round8_bf16(xn[j], f1[j]);
+                m[j] = EL::diff_mask(xo[j], xn[j]);
+                if (!W && !has_vector(j)) m[j] = 0;
+                if (j % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        if (glen >= TILE) stream_tile(std::true_type{});
+        else stream_tile(std::false_type{});
+
+        if (in_head) {
+            // the front: elements 0 .. VE-h-1 of the tile, to positions h .. VE-1
+            u32x4 vo, vn;
+            if (short_tile) {
+                const uint32_t hi = glen < VE ? 0u : VE;                    // (a tile within one vector is all tail)
+                vo = EL::load_window(og, h, hi);
+                if constexpr (CAST) vn = load8_window_cast(fg, h, hi);
+                else vn = EL::load_window(ng, h, hi);
+            } else {
+                vo = shift_up(xo[0], h * EB);
+                vn = shift_up(xn[0], h * EB);
+            }
+            xn[0] = vn;
+            m[0] = EL::diff_mask(vo, vn);
+            if (LINES) refresh_incomplete(0, m[0], vn);
         }
-        s_tail = vn;
-        s_tail_mask = md;
-        if (LINES) refresh_incomplete(nbody, md, vn);
+        if (has_tail && tid == kThreads - 1) {
+            uint32_t md;
+            u32x4 vn;
+            if (short_tile) {
+                const uint32_t lo = (h > nbody) ? h - nbody : 0u, hi = glen - nbody;
+                const u32x4 vo = EL::load_window(og + nbody, lo, hi);
+                if constexpr (CAST) vn = load8_window_cast(fg + nbody, lo, hi);
+                else vn = EL::load_window(ng + nbody, lo, hi);
+                md = EL::diff_mask(vo, vn);
+            } else {
+                const uint32_t down = (VE - (glen - nbody)) * EB;
+                if (CAST) tn = round8_bf16(tn, tn1);
+                vn = shift_down(tn, down);
+                md = EL::diff_mask(shift_down(to, down), vn);
+            }
+            s_tail = vn;
+            s_tail_mask = md;
+            if (LINES) refresh_incomplete(nbody, md, vn);
+        }
     }
 
     // ---- wave scan (two vectors per register), then the rank of this lane's first changed element of each vector
@@ -887,6 +927,17 @@ __global__ __launch_bounds__(kThreads, waves_per_simd(V, MULTI, SRC, EB)) void e
         write_staged((uint32_t)tid, kThreads, (uint64_t)excl + r0, (tile_total - r0 < kStage) ? (tile_total - r0) : kStage);
         lds_barrier();
     }
+}
+
+template <int V, bool MULTI, int RG, int SRC = kSrcBf16, int EB = 2>
+__global__ __launch_bounds__(kThreads, waves_per_simd(V, MULTI, SRC, EB)) void extract_kernel(const ExtractArgs a) {
+    extract_tile<V, MULTI, RG, SRC, EB, false>(a);
+}
+
+// for lists nearly all of whose tiles are whole and aligned
+template <int RG>
+__global__ __launch_bounds__(kThreads, waves_per_simd(16, true, kSrcBf16, 2)) void extract_whole_kernel(const ExtractArgs a) {
+    extract_tile<16, true, RG, kSrcBf16, 2, true>(a);
 }
 
 // ---------------------------------------------------------------------------------------------

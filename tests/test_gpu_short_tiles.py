@@ -103,3 +103,48 @@ def test_pairs_around_what_one_wave_writes_out(kind, tile, mode, per):
         assert np.array_equal(t.cpu().numpy().view(dt), old if mode == "rotate" else after)
     finally:
         ctx.close()
+
+
+@pytest.mark.parametrize("mode", ["lines", "elements", "rotate", "second"])
+@pytest.mark.parametrize("form", ["whole", "most", "nine", "eight", "shifted", "one_shifted", "chains", "fewer_chains"])
+def test_lists_of_whole_tiles(form, mode):
+    """Lists on both sides of the share of whole aligned tiles from which another kernel takes them, one with a few tensors off the
+    16-byte boundaries, and the plan called again with other pointers."""
+    from paper_2605_07330_amd import srs
+    T = 32768
+    numel = {"whole": [3 * T] * 12, "most": [19 * T + 40, 8, 17 * T + 8, T], "nine": [9 * T + 24] * 4, "eight": [8 * T + 24] * 4, "shifted": [6 * T] * 5,
+             "one_shifted": [2 * T] * 6 + [7, 13 * T + 24] + [2 * T] * 3, "chains": [64 * T] * 4, "fewer_chains": [64 * T] * 3 + [62 * T]}[form]
+    print(f"case {form} {mode}", flush=True)
+    rng = np.random.default_rng(len(form))
+    n, be = sum(numel), 2 * T if form.endswith("chains") else 8 * T + 512      # 128 and 127 buckets of two tiles
+    pad = [0 if form != "shifted" else 1 for _ in numel]     # elements in front of each tensor
+    if form == "one_shifted":
+        pad[3] = 3
+    as_torch = lambda a: torch.from_numpy(a.view(np.int16)).to(DEV)  # noqa: E731
+    split = lambda a: [np.ascontiguousarray(x) for x in np.split(a, np.cumsum(numel)[:-1])]  # noqa: E731
+    ctx = srs.Context(0)
+    try:
+        ctx.set_option(srs.OPT_REFRESH_GROUP, 0 if mode == "elements" else 8)
+        ctx.set_option(srs.OPT_SNAPSHOT, {"rotate": 1, "second": 2}.get(mode, 0))
+        plan = ctx.plan(numel, be)
+        for again in range(3):
+            if again == 1:                                  # the same list, off or on the boundaries
+                pad = [1 - min(p, 1) for p in pad]
+            old = rng.integers(0, 1 << 16, n).astype(np.uint16)
+            new = (old ^ (rng.random(n) < (0.004, 0.04, 0.2)[again])).astype(np.uint16)
+            after = [x.copy() for x in split(old)]
+            wI, wV, wc = oracle.extract_multi(after, split(new), numel, be, be)[:3]
+            put = lambda a: [torch.empty(len(x) + p, dtype=torch.int16, device=DEV)[p:].copy_(as_torch(x)) for x, p in zip(split(a), pad)]  # noqa: E731
+            t, u = put(old), put(new)
+            I, V, counts = srs.alloc_payload(plan.nbuckets, be, DEV)
+            ctx.extract_multi(plan, t, u, I, V, counts, be)
+            assert ctx.status() == 0
+            assert np.array_equal(counts.cpu().numpy().view(np.uint32), wc)
+            gI, gV = I.cpu().numpy().reshape(len(wc), be), V.cpu().numpy().view(np.uint16).reshape(len(wc), be)
+            for b, c in enumerate(wc):
+                assert np.array_equal(gI[b, :c], wI[b, :c]) and np.array_equal(gV[b, :c], wV[b, :c]), b
+            got = np.concatenate([x.cpu().numpy().view(np.uint16) for x in t])
+            assert np.array_equal(got, old if mode == "rotate" else np.concatenate(after))
+        plan.close()
+    finally:
+        ctx.close()

@@ -52,5 +52,22 @@ def test_resident_waves(kernels, name, waves):
 
 def test_no_extract_kernel_spills(kernels):
     """Occupancy that is reached by keeping registers in scratch memory is none."""
-    spilled = {n: s for n, b in kernels.items() if n.startswith("extract_") and (s := int(re.search(r"; ScratchSize: (\d+)", b).group(1)))}
+    spilled = {n: s for n, b in kernels.items() if "extract_" in n and (s := int(re.search(r"; ScratchSize: (\d+)", b).group(1)))}
     assert not spilled
+
+
+@pytest.mark.parametrize("name", ["extract_whole_kernel<8>", "extract_whole_kernel<-1>"])
+def test_whole_tiles_load_from_immediate_offsets(kernels, name):
+    """The kernel for lists of whole aligned tiles: 16 loads of each stream with nothing but pauses and additions to their addresses
+    between them, no choice of a position."""
+    body = kernels[name]
+    runs, run = [], []
+    for line in body.split("\n"):
+        op = line.strip().split(" ")[0]
+        if op.startswith("global_load_dwordx4"):
+            run.append(op)
+        elif op and op[0] != ";" and not re.match(r"(s_sleep|s_nop|v_add_co_u32|v_addc_co_u32|v_lshl_add_u64|v_add_u32|s_mov|s_waitcnt)", op):
+            if len(run) >= 4:
+                runs.append(len(run))
+            run = []
+    assert 32 in runs or runs.count(16) >= 2, runs
