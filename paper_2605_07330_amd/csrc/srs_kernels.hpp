@@ -325,8 +325,9 @@ template <bool SCALAR, class T> __device__ __forceinline__ auto table(const T *p
 // graph gets a new one each time: a workgroup reads it before it takes its ticket; the one that takes a bucket's last
 // ticket counts the bucket, and the one that counts the last bucket raises the epoch, when every workgroup of the
 // launch has read it, whatever else becomes of them.  The 30 bits of an epoch in a status word come round after 2^30
-// launches; nothing written so long ago is left then: every tile of a launch that has chains writes its word, and the workgroup that
-// raises the epoch wipes 64 words behind those, other ones each time.
+// launches; nothing written so long ago is left then: the tiles of chains write their words in every launch, tiles alone in
+// their buckets wipe theirs now and then, and the workgroup that raises the epoch wipes 64 words behind the launch's tiles, other
+// ones each time.
 // The kernel that cleared both ahead of each launch took 1.4 us where little else ran and 4.7 us in a busy stream, and the
 // host 2.5 us.  Extract and apply with it / without, us: 64 K elements 13.7 / 11.0, 1 M in four buckets 13.5 / 12.1, 4 M in
 // four 17.5 / 16.0, 300 odd-sized tensors 147.5 / 146.1.
@@ -363,7 +364,12 @@ __device__ __forceinline__ void raise_epoch(const ExtractArgs &a, uint32_t epoch
 __device__ __forceinline__ uint32_t left_behind(const ExtractArgs &a, uint32_t tile) {
     return as_table(reinterpret_cast<const uint32_t *>(a.status + tile))[1];
 }
-// One lane: the tile's count.  A bucket's last or only tile, whose word nobody reads, leaves 0 there.
+// One lane of a bucket's only tile, which has no use for its word: leaves 0 there in one launch of 2^14, other tiles each time.
+// (In every launch that takes the marked extract of 600 tensors in buckets of 3000 elements 5 %.)
+__device__ __forceinline__ void wipe_alone(const ExtractArgs &a, uint32_t tile) {
+    if ((((tile >> 6) ^ *as_table(a.epoch)) & 0x3FFFu) == 0) status_store(a.status + tile, 0ull);
+}
+// One lane: the tile's count.  A bucket's last tile, whose word nobody reads, leaves 0 there.
 __device__ __forceinline__ void publish(const ExtractArgs &a, uint32_t epoch, uint32_t tile, uint32_t found, bool first, bool last, uint32_t total) {
     if (status_flag(epoch, (unsigned long long)found << 32) != 0) atomicOr(a.flags, a.timeout);
     status_store(a.status + tile, last ? 0ull : status_word(epoch, first ? kStPrefix : kStAgg, total));
@@ -789,7 +795,10 @@ __device__ __forceinline__ void extract_tile(const ExtractArgs &a) {
     for (int j = 0; j < V; ++j) ex[j] += wave_base;       // from here on: rank inside the tile
 
     // ---- the chain with the earlier tiles of the bucket: this tile's count is published now, and looked back from later
-    if (tid == 0 && a.chained) publish(a, epoch, tile, found, tile == first_tile, last, tile_total);
+    if (tid == 0) {
+        if (chained) publish(a, epoch, tile, found, tile == first_tile, last, tile_total);
+        else if (a.chained) wipe_alone(a, tile);
+    }
     // wave 0: changed elements of the bucket in front of the tile
     auto settle = [&]() -> uint32_t {
         uint32_t excl = 0;
@@ -1039,7 +1048,10 @@ __global__ __launch_bounds__(kThreads) void extract_marked_kernel(const ExtractA
     const uint32_t first = wave_base + (inc - mine);                 // rank of this thread's first pair
 
     // ---- chain with the earlier tiles of the bucket, as in extract_kernel: published now, looked back from later
-    if (tid == 0 && a.chained) publish(a, epoch, tile, found, tile == first_tile, last, tile_total);
+    if (tid == 0) {
+        if (chained) publish(a, epoch, tile, found, tile == first_tile, last, tile_total);
+        else if (a.chained) wipe_alone(a, tile);
+    }
     auto settle = [&]() -> uint32_t {
         uint32_t excl = 0;
         if (tile != first_tile) {
@@ -1076,6 +1088,16 @@ __global__ __launch_bounds__(kThreads) void extract_marked_kernel(const ExtractA
     };
     // their values, spread evenly over the threads and all in flight together, go back to LDS beside the positions
     auto gather_round = [&](uint32_t n) {
+        if (n <= (uint32_t)kThreads) {                                  // one each (uniform)
+            const uint32_t q = (uint32_t)tid;
+            if (q < n) {
+                const uint32_t local = s_stage[q];
+                uint32_t val = 0;
+                if (local < len) val = NT ? __builtin_nontemporal_load(pn + local) : pn[local];
+                s_stage[q] = (local << 16) | val;
+            }
+            return;
+        }
         uint32_t local[kGather], val[kGather];
 #pragma unroll
         for (int u = 0; u < kGather; ++u) {
@@ -1107,6 +1129,21 @@ __global__ __launch_bounds__(kThreads) void extract_marked_kernel(const ExtractA
         // one at 0.6 % 50 / 41, 300 odd-sized tensors at 2 % 43 / 33; with all four waves to the end 701 for the first.
         stage_round(0);
         lds_barrier();
+        // A pair each at most and nothing to wait for: out they go.  With all of what follows for such tiles too the extract of 600
+        // tensors in buckets of 3000 elements took 141 us at 0.2 % marked and 197 at 2 %, where it had taken 129 and 179 before the
+        // values went through LDS; so 131 and 187.
+        if (!chained && tile_total <= (uint32_t)kThreads) {
+            if ((uint32_t)tid < tile_total) {
+                const uint32_t local = s_stage[tid];
+                if (local < len && (uint32_t)tid < a.cap) {
+                    const uint16_t val = NT ? __builtin_nontemporal_load(pn + local) : pn[local];
+                    Ib[tid] = (int32_t)(idx_base + local);
+                    Vb[tid] = val;
+                }
+            }
+            if (wave == 0) settle();
+            return;
+        }
         gather_round(tile_total);
         lds_barrier();
         if (wave != 0) return;

@@ -148,3 +148,41 @@ def test_lists_of_whole_tiles(form, mode):
         plan.close()
     finally:
         ctx.close()
+
+
+@pytest.mark.parametrize("tile", [32768, 4096])
+@pytest.mark.parametrize("per", [1, 2])
+def test_marked_pairs_around_one_each(tile, per):
+    """The payload of a bitmap where tiles hold about as many pairs as there are threads, alone in their buckets or two in one, whole and
+    short ones; a capacity that cuts some off."""
+    from paper_2605_07330_amd import srs
+    print(f"case tile={tile} per={per}", flush=True)
+    rng = np.random.default_rng(tile + per)
+    numel = [30 * tile, 7, 3 * tile + 300, 5]
+    n, be = sum(numel), per * tile
+    mask = np.zeros(n, bool)
+    for lo in range(0, n, tile):
+        hi = min(n, lo + tile)
+        mask[lo + rng.permutation(hi - lo)[:int(rng.choice([0, 1, 64, 200, 255, 256, 257, 300]))]] = True
+    new = rng.integers(0, 1 << 16, n).astype(np.uint16)
+    split = lambda a: [np.ascontiguousarray(x) for x in np.split(a, np.cumsum(numel)[:-1])]  # noqa: E731
+    bits = np.zeros(oracle.bitmap_words(n), np.uint32)
+    oracle.mark_multi(split(new ^ mask), split(new), numel, bits)
+    cap = 250 * per
+    wI, wV, wc = oracle.extract_marked_multi(split(new), numel, be, bits, cap)[:3]
+    ctx = srs.Context(0)
+    try:
+        ctx.set_option(srs.OPT_TILE_ELEMS, tile)
+        plan = ctx.plan(numel, be)
+        I, V, counts = srs.alloc_payload(plan.nbuckets, cap, DEV)
+        flat = torch.from_numpy(new.view(np.int16)).to(DEV)
+        ctx.extract_marked_multi(plan, list(torch.split(flat, numel)), torch.from_numpy(bits.view(np.int32)).to(DEV), I, V, counts, cap)
+        assert ctx.status() == srs.FLAG_OVERFLOW and (wc > cap).any()
+        assert np.array_equal(counts.cpu().numpy().view(np.uint32), wc)
+        gI, gV = I.cpu().numpy().reshape(len(wc), cap), V.cpu().numpy().view(np.uint16).reshape(len(wc), cap)
+        for b, c in enumerate(np.minimum(wc, cap)):
+            assert np.array_equal(gI[b, :c], wI[b, :c]) and np.array_equal(gV[b, :c], wV[b, :c]), b
+            assert (gI[b, c:] == -1).all()
+        plan.close()
+    finally:
+        ctx.close()
