@@ -1864,7 +1864,7 @@ __global__ __launch_bounds__(kThreads) void vc_hist_kernel(const ValueCodecArgs 
 // smallest live nodes are always at the heads of these two queues, and a tie between them goes to the symbol.  One wave
 // runs the merge with both queues in registers and the queue heads in scalar registers: a step is a few readlanes.  Up
 // to kVcWave symbols (the high bytes of weights are 20 to 30) a wave also sorts and measures the depths by itself, and the
-// eight waves try successive halvings side by side; more symbols take R = 4 registers per lane and queue (entry i in lane i & 63
+// four or eight waves try successive halvings side by side; more symbols take R = 4 registers per lane and queue (entry i in lane i & 63
 // of register i >> 6) and the whole workgroup around the merge.  Bound by the serial chain.  240 buckets of 335 k
 // values: 147 us when every step searched all nodes for its two minima with 64-bit wave reductions, 49 us by the general
 // path, 15 us with four waves (two tries of four).  The whole value coder with 4 / 8 / 16 waves, us: 240 buckets of 335 k values
@@ -1956,16 +1956,16 @@ __device__ __forceinline__ uint32_t vc_wave_lengths(uint32_t w, uint32_t used, u
     return me < used ? l : 0u;
 }
 
-constexpr int kBuildThreads = 512, kBuildWaves = kBuildThreads / 64;      // the first 256 threads hold a symbol each
-
-__global__ __launch_bounds__(kBuildThreads) void vc_build_kernel(const ValueCodecArgs a) {
+// W waves; the first 256 threads hold a symbol each
+template <int W>
+__global__ __launch_bounds__(64 * W) void vc_build_kernel(const ValueCodecArgs a) {
     __shared__ int16_t parent[512];
     __shared__ __align__(16) uint32_t packed_w[256];         // weights of the symbols that occur, in symbol order, then 0
-    __shared__ uint32_t sorted_w[64 * kBuildWaves];
+    __shared__ uint32_t sorted_w[64 * W];
     __shared__ uint8_t sorted_s[256];
     __shared__ uint32_t count_l[kVcMaxLen + 1][kWaves];
-    __shared__ uint32_t s_used[kWaves], s_maxlen, s_fits[kBuildWaves];
-    __shared__ uint8_t s_len[64 * kBuildWaves];
+    __shared__ uint32_t s_used[kWaves], s_maxlen, s_fits[W];
+    __shared__ uint8_t s_len[64 * W];
     const uint32_t b = blockIdx.x, s = threadIdx.x;
     const int lane = s & 63, wave = s >> 6;
     const bool symbol = s < 256;                             // uniform per wave
@@ -1988,8 +1988,8 @@ __global__ __launch_bounds__(kBuildThreads) void vc_build_kernel(const ValueCode
     } else if (used > 1 && used <= kVcWave) {                // uniform
         if (w) packed_w[place] = w;
         __syncthreads();
-        // r halvings make ceil(w / 2^r): the waves try eight numbers of halvings at a time (335 k values take 6)
-        for (uint32_t r0 = 0;; r0 += kBuildWaves) {          // 31 halvings leave weights of 1 and lengths of 6 at most
+        // r halvings make ceil(w / 2^r): the waves try W numbers of halvings at a time (335 k values take 6)
+        for (uint32_t r0 = 0;; r0 += W) {          // 31 halvings leave weights of 1 and lengths of 6 at most
             const uint32_t r = r0 + (uint32_t)wave;
             const uint32_t wr = (uint32_t)(((uint64_t)packed_w[lane] + (1ull << r) - 1ull) >> r);
             const uint32_t len = vc_wave_lengths(wr, used, sorted_w + 64 * wave, lane);
@@ -1997,11 +1997,11 @@ __global__ __launch_bounds__(kBuildThreads) void vc_build_kernel(const ValueCode
             const bool fits = !__any(len > kVcMaxLen);
             if (lane == 0) s_fits[wave] = fits ? 1u : 0u;
             __syncthreads();
-            uint32_t hit = kBuildWaves;
+            uint32_t hit = W;
 #pragma unroll
-            for (int v = kBuildWaves - 1; v >= 0; --v) hit = s_fits[v] ? (uint32_t)v : hit;
+            for (int v = W - 1; v >= 0; --v) hit = s_fits[v] ? (uint32_t)v : hit;
             hit = uniform(hit);
-            if (hit < kBuildWaves) { l = w ? (uint32_t)s_len[64 * hit + place] : 0u; break; }
+            if (hit < W) { l = w ? (uint32_t)s_len[64 * hit + place] : 0u; break; }
             __syncthreads();                                 // everybody has read s_fits
         }
     }

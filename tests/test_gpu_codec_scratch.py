@@ -1,6 +1,8 @@
 """Scratch of the two codings.  Largest index difference of a bucket, from the chunk maxima kept in the context's fixed scratch and, where there are more chunks
 than it holds, from atomics: chunk edges, empty buckets, wide differences in the first, a middle and the last chunk.
 Histograms that every call of the value coder finds empty."""
+import heapq
+
 import numpy as np
 import pytest
 import torch
@@ -44,22 +46,79 @@ def test_chunk_maxima(nb, cap):
         ctx.close()
 
 
-@pytest.mark.parametrize("halvings", [0, 3, 4, 7, 8, 12])
-def test_value_code_after_other_calls(halvings):
-    """Codes that need so many halvings of the weights, on one context in calls of growing and shrinking bucket counts: the histograms
-    begin empty each time."""
+def lengths(weights):
+    """Code length of each symbol of a Huffman code: the two smallest by (weight, symbols before nodes, age) merge."""
+    heap = [(int(w), 0, s, (s,)) for s, w in enumerate(weights) if w]
+    heapq.heapify(heap)
+    depth = np.zeros(256, int)
+    for k in range(len(heap) - 1):
+        a, b = heapq.heappop(heap), heapq.heappop(heap)
+        depth[list(a[3] + b[3])] += 1
+        heapq.heappush(heap, (a[0] + b[0], 1, k, a[3] + b[3]))
+    return depth
+
+
+def halvings_needed(weights):
+    """(How often the weights are halved, rounding up, until no code is longer than 12 bits, and the lengths then.)"""
+    w, r = np.asarray(weights, np.int64), 0
+    while lengths(w).max() > 12:
+        w, r = (w + 1) // 2, r + 1
+    return r, lengths(w)
+
+
+def steep(symbols, seed):
+    """Counts 1, 2, 4, .. of so many high bytes: the more of them, the more halvings."""
+    weights = np.zeros(256, np.int64)
+    weights[np.random.default_rng(seed).permutation(256)[:symbols]] = 1 << np.arange(symbols)
+    return weights
+
+
+# high bytes, halvings; slots for 65,536 values or fewer take four tries at a time, more of them eight
+@pytest.mark.parametrize("symbols,halvings", [(13, 0), (14, 2), (15, 3), (16, 4), (17, 5), (19, 7), (20, 8), (21, 9), (23, 11), (27, 15), (28, 16)])
+def test_code_after_so_many_halvings(symbols, halvings):
     from paper_2605_07330_amd import srs
-    rng = np.random.default_rng(halvings)
+    weights = [steep(symbols, seed) for seed in range(2)]
+    want = [halvings_needed(w) for w in weights]
+    assert [r for r, _ in want] == [halvings] * 2
+    total = int(weights[0].sum())
+    print(f"case symbols={symbols} values={total}", flush=True)
+    caps = [total] if total > 65536 else [total, 65536, 65537]                # both widths where the values fit either
+    ctx = srs.Context(0)
+    try:
+        for cap in caps:
+            V = torch.zeros((2, cap), dtype=torch.int16, device=DEV)
+            for b, w in enumerate(weights):
+                high = torch.repeat_interleave(torch.arange(256, device=DEV), torch.from_numpy(w).to(DEV))
+                V[b, :total] = ((high[torch.randperm(total, device=DEV)] << 8) | 0x5A).to(torch.int32).to(torch.int16)
+            n = torch.full((2,), total, dtype=torch.int32, device=DEV)
+            enc = srs.alloc_value_stream(2, cap, DEV)
+            for _ in range(2):
+                ctx.encode_values(V, n, 2, cap, enc)
+            assert ctx.status() == 0
+            assert np.array_equal(enc["lens"].cpu().numpy().reshape(2, 256), np.stack([x for _, x in want]))
+            out = torch.zeros_like(V)
+            ctx.decode_values(enc, n, 2, cap, out)
+            assert ctx.status() == 0 and torch.equal(out[:, :total], V[:, :total])
+            if total < 200_000:
+                assert np.array_equal(oracle.encode_values(V.cpu().numpy().view(np.uint16), np.full(2, total, np.uint32))["lens"], np.stack([x for _, x in want]))
+    finally:
+        ctx.close()
+
+
+@pytest.mark.parametrize("slope", [1.1, 1.46, 1.58, 1.94, 2.06, 2.54])
+def test_value_code_after_other_calls(slope):
+    """Geometric weights, on one context in calls of growing and shrinking bucket counts: the histograms begin empty each time."""
+    from paper_2605_07330_amd import srs
+    rng = np.random.default_rng(round((slope - 1.1) / 0.12))
     ctx = srs.Context(0)
     try:
         for nb in (3, 300, 1, 257, 3):
             cap = 40_000 if nb < 10 else 2100
-            steep = 1.1 + 0.12 * halvings                       # geometric weights: the steeper, the deeper the code
             values = np.zeros((nb, cap), np.uint16)
             counts = rng.integers(0, cap + 1, nb).astype(np.uint32)
             counts[0] = cap
             for b in range(nb):
-                high = np.minimum(rng.exponential(1 / np.log(steep), cap).astype(np.int64), 39) * 5 % 256
+                high = np.minimum(rng.exponential(1 / np.log(slope), cap).astype(np.int64), 39) * 5 % 256
                 values[b] = (high << 8) | rng.integers(0, 256, cap)
             enc = srs.alloc_value_stream(nb, cap, DEV)
             V = torch.from_numpy(values.view(np.int16)).to(DEV)
