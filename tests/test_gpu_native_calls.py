@@ -120,7 +120,8 @@ def test_same_as_through_ctypes(kind, form, monkeypatch):
     assert call is not None, "_call.so is not built: python -m paper_2605_07330_amd.build"
     native, taken, errors, flags, got = _outcome(kind, form, call, monkeypatch)
     _, _, want_errors, want_flags, want = _outcome(kind, form, None, monkeypatch)
-    assert taken[0] == native
+    # apply goes its own way: it takes no new weights, and a clone of strided ones is contiguous
+    assert taken == [native, native or form in ("strided", "width", "host", "sizes")]
     assert errors == want_errors and flags == want_flags
     for g, w in zip(got, want):
         assert g.shape == w.shape and torch.equal(g.contiguous().view(torch.uint8), w.contiguous().view(torch.uint8))
