@@ -1,15 +1,17 @@
-"""Builds libsrs.so (HIP, gfx950 only) and the binding's _call.so (host code) in-tree, next to this file."""
+"""Builds libsrs.so (HIP, gfx950 only) and the binding's _call module (host code) in-tree, next to this file."""
 from __future__ import annotations
 
 import os
+import shutil
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "libsrs.so")
 SOURCES = [os.path.join(HERE, "csrc", "srs.hip")]
-HEADERS = [os.path.join(HERE, "csrc", "srs_kernels.hpp"), os.path.join(ROOT, "include", "srs.h")]
+HEADERS = [os.path.join(HERE, "csrc", f) for f in ("srs_kernels.hpp", "device_guard.hpp", "scratch_array.hpp")] + [os.path.join(ROOT, "include", "srs.h")]
 
 
 def hipcc_command(out: str = LIB, extra=()) -> list:
@@ -47,19 +49,28 @@ def clang_asan_runtime() -> str:
     return hits[-1] if hits else ""
 
 
-CALL = os.path.join(HERE, "_call.so")
+CALL = os.path.join(HERE, "_call" + sysconfig.get_config_var("EXT_SUFFIX"))      # the tag keeps another Python from loading it
 CALL_SRC = os.path.join(HERE, "csrc", "call.cpp")
 
 
 def build_call(verbose: bool = False) -> str:
-    """_call.so: the binding's single-tensor calls in C++ (host code only), against the headers of the torch that is installed."""
-    import sysconfig
+    """The binding's single-tensor calls in C++ (host code only), against the headers of the Python and the torch that are installed.
+    Returns "" where there is no compiler or there are no headers for it: the calls then go through ctypes, which takes longer."""
     import torch
-    root = os.path.dirname(torch.__file__)
-    cmd = [os.environ.get("CXX", "g++"), "-std=c++17", "-O2", "-fPIC", "-shared", "-w", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
-           f'-DSRS_TORCH_VERSION="{torch.__version__}"',
-           "-I", sysconfig.get_paths()["include"], "-isystem", os.path.join(root, "include"),
-           "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"), CALL_SRC, "-o", CALL,
+    cxx, root, python = os.environ.get("CXX", "g++"), os.path.dirname(torch.__file__), sysconfig.get_paths()["include"]
+    include = os.path.join(root, "include")
+    for path in (CALL, os.path.join(HERE, "_call.so")):                          # nothing older is left to be loaded
+        if os.path.exists(path):
+            os.remove(path)
+    needs = {f"the compiler {cxx}": shutil.which(cxx), "torch's headers": os.path.exists(os.path.join(include, "torch", "csrc", "autograd", "python_variable.h")),
+             "Python's headers": os.path.exists(os.path.join(python, "Python.h"))}
+    missing = [what for what, there in needs.items() if not there]
+    if missing:
+        print(f"{os.path.basename(CALL)} is not built: {', '.join(missing)} not found; single-tensor calls go through ctypes", file=sys.stderr, flush=True)
+        return ""
+    cmd = [cxx, "-std=c++17", "-O2", "-fPIC", "-shared", "-Wall", "-Wextra", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           f'-DSRS_TORCH_VERSION="{torch.__version__}"', "-isystem", python, "-isystem", include,
+           "-isystem", os.path.join(include, "torch", "csrc", "api", "include"), CALL_SRC, "-o", CALL,
            "-L", os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
     if verbose:
         print(" ".join(cmd), flush=True)

@@ -16,7 +16,7 @@ const at::Tensor *on_gpu(PyObject *o, size_t width) {
     if (!THPVariable_CheckExact(o)) return nullptr;
     const at::Tensor &t = THPVariable_Unpack(o);
     if (!t.defined() || at::isTensorSubclassLike(t) || !t.is_cuda() || t.layout() != at::kStrided) return nullptr;
-    if (t.element_size() != width || !t.is_contiguous()) return nullptr;
+    if ((size_t)t.element_size() != width || !t.is_contiguous()) return nullptr;
     return &t;
 }
 

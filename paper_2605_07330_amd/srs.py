@@ -11,6 +11,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import warnings
 from typing import List, Optional, Sequence
 
 import torch  # loads the HIP runtime that libsrs.so binds to
@@ -118,8 +119,11 @@ def _check(rc: int, where: str) -> None:
 try:
     from . import _call
     if _call.torch_version != torch.__version__:
+        warnings.warn(f"_call was built for torch {_call.torch_version}, this is {torch.__version__}: single-tensor calls take longer "
+                      "(python -m paper_2605_07330_amd.build)", RuntimeWarning)
         _call = None
-except ImportError:
+except ImportError as e:
+    warnings.warn(f"_call does not load, single-tensor calls take longer (python -m paper_2605_07330_amd.build): {e}", RuntimeWarning)
     _call = None
 _address = {n: C.cast(getattr(_lib, n), _vp).value for n in ("srs_extract", "srs_apply", "srs_extract_u8", "srs_apply_u8", "srs_extract_cast")}
 

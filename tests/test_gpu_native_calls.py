@@ -117,7 +117,7 @@ def _outcome(kind, form, call, monkeypatch):
 @pytest.mark.parametrize("form", FORMS)
 def test_same_as_through_ctypes(kind, form, monkeypatch):
     call = srs._call
-    assert call is not None, "_call.so is not built: python -m paper_2605_07330_amd.build"
+    assert call is not None, "_call is not built: python -m paper_2605_07330_amd.build"
     native, taken, errors, flags, got = _outcome(kind, form, call, monkeypatch)
     _, _, want_errors, want_flags, want = _outcome(kind, form, None, monkeypatch)
     # apply goes its own way: it takes no new weights, and a clone of strided ones is contiguous
