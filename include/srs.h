@@ -100,12 +100,14 @@ typedef enum {
                                   11.8 ms on a 30.5 G-element list, both with SRS_OPT_INTERLEAVE = 256; at 16 bits and 0.1 %: 3.5 % faster; from 0.3 %
                                   up the default is faster).  Ignored, like 1, by the fused-cast and cumulative calls. */
 
-typedef struct srs_ctx srs_ctx;    /* per-stream scratch: tile status words, per-bucket ticket counters, flag word */
+typedef struct srs_ctx srs_ctx;    /* per-stream scratch: tile status words, per-bucket ticket counters and the epoch of srs_extract*,
+                                      histograms and codes of srs_encode_values, chunk maxima of srs_encode_indices, flag word.
+                                      What one call leaves there the next one builds on: see "one context per stream" above */
 typedef struct srs_plan srs_plan;  /* immutable bucket / segment / tile tables of one tensor list */
 
 /* Context.  srs_create selects `device`, allocates 930 KiB of device scratch and synchronises.
- * The tile-status and ticket arrays grow on demand inside srs_extract* (that one call then allocates
- * and synchronises the device; later calls of the same or smaller size do not). */
+ * The tile-status and ticket arrays grow on demand inside srs_extract*, the histograms inside srs_encode_values (that one call
+ * then allocates and synchronises the device; later calls of the same or smaller size do not). */
 int srs_create(srs_ctx **out, int device);
 int srs_destroy(srs_ctx *ctx);                       /* synchronises the device, frees scratch */
 int srs_set_option(srs_ctx *ctx, int option, uint64_t value);
@@ -114,9 +116,9 @@ int srs_version(void);
 
 /* Waits for `stream`, copies the device flag word to *flags (host pointer) and clears it.  After SRS_FLAG_TIMEOUT it also
  * puts the context's scratch into its initial state, and the static array of srs_extract_noalloc where one of this context's
- * calls on that raised the flag, and waits again; it then counts as such a call where the header orders them.  No call clears the scratch for the next one: where calls
- * on one context have overlapped, which is not allowed, later calls may raise SRS_FLAG_TIMEOUT too until this function has
- * reported it. */
+ * calls on that raised the flag, and waits again; it then counts as such a call wherever those have to be ordered.  No call clears
+ * the scratch for the next one: where calls on one context have overlapped, which is not allowed, later calls may raise
+ * SRS_FLAG_TIMEOUT too until this function has reported it. */
 int srs_status(srs_ctx *ctx, uint32_t *flags, void *stream);
 
 /*

@@ -117,8 +117,11 @@ uint32_t ticket_stride_for(uint64_t nb) { return nb <= 65536 ? 64u : 1u; }
 constexpr uint64_t kFirstTickets = 128 * 64, kFirstStatus = 16384, kFirstCodec = 256;
 constexpr uint64_t kFirstBytes = 256 + kFirstTickets * sizeof(uint32_t) + kFirstStatus * sizeof(unsigned long long) +
                                  kFirstCodec * 256 * sizeof(uint32_t);                  // these begin as zeros
-// Behind it, the codes of the value coder for as many buckets, and room for the largest index difference of so many payload chunks (srs_encode_indices): fixed, so that the call
-// never allocates.  240 buckets of 424 k payload slots have 49,680.
+// Behind it, the codes of the value coder for as many buckets, and room for the largest index difference of so many chunks of
+// payload slots (srs_encode_indices): fixed, so that the call never allocates.  Payloads with more chunks of slots, live or not, take
+// the maxima by atomics, as all did before.  By atomics / by chunk words, us: 240 buckets of 335 k pairs in 424 k slots (49,920
+// chunks) 103 / 93, 20 of 250 k in 313 k (3060) 28 / 9.5, the same in 32 M slots each (327,680) 146 / does not fit, 910 of 335 k
+// (189,280) 381 / does not fit.
 constexpr uint64_t kGapWords = 65536;
 
 // The status words, ticket counters and epoch of an extract launch of ntiles tiles in nb buckets, `chained` of which have more

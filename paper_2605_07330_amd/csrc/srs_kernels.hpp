@@ -477,8 +477,9 @@ __device__ __forceinline__ void refresh_lines(gptr<T> og, uint32_t g0, uint32_t 
 // source for the host code.)
 constexpr int kSrcBf16 = 0, kSrcFp32 = 1, kSrcBitmap = 2;
 
-// Waves per SIMD are demanded where a few registers more would cost one.  Lists of one-byte elements in tiles of 16384,
-// 6 waves / 8, us: five 32B-shaped layers in place at 0.3 % 1228 / 1174, rotated 1066 / 1025, four 8B-shaped 433 / 428.
+// Waves per SIMD are demanded where a few registers more would cost one; of the present kernels only lists of one-byte elements in
+// tiles of 16384 would have one fewer without.  7 waves / 8, us: five 32B-shaped layers in place at 0.3 % 1247 / 1206, rotated
+// 1089 / 1040, four 8B-shaped 519 / 522, one of them 132 / 136.
 constexpr int waves_per_simd(int v, bool multi, int src, int eb) {
     return (v >= 16 && src == kSrcBf16) ? 3 : (v == 8 && src == kSrcFp32) ? 4 : (v == 4 && eb == 1 && multi) ? 8 : 1;
 }
