@@ -521,6 +521,11 @@ uint64_t single_tiles(uint64_t n, uint64_t be, uint64_t tile) {
 // One-byte elements: a tile takes half as long to read; no more than one per CU, 192 in one bucket, and buckets of up to 16384
 // elements are one tile.  8192 / 16384 / 32768, us: 16 K 4.9 / 4.3 / 6.1, 1 M in one bucket 6.5 / 6.7 / 8.5, 2 M 8.6 / 7.4 / 8.7, 4 M 12.6 /
 // 9.2 / 9.4, in four 7.5 / 7.2 / 8.2, 8 M in one 21.9 / 14.1 / 11.4.
+// The cast and the extract that leaves the snapshot alone follow the same lines.  With the rule before (256 tiles at most, the
+// smallest such; a clearing launch) / with this one, us, at 0.2 %, cast: 300 K in one bucket 8.1 / 6.3, 1 M 10.8 / 8.0, 4 M 14.8 /
+// 12.6, in nine 17.4 / 10.5, 12 M in one 27.7 / 25.8; snapshot left alone: 1 M in one 10.5 / 6.9, 4 M 13.1 / 10.1, in nine
+// 13.2 / 8.0, 7 M 15.8 / 13.2.  Both sides of the lines' price, at 40 % changed: 1 M in one bucket refreshed 12.8 / 14.2, cast
+// 12.4 / 14.4, 7 M in nine 28.9 / 32.5 and 32.1 / 35; 16 K in one bucket with the second pass at 0.2 % 8.0 / 8.7.
 uint32_t single_tile_elems(const srs_ctx *ctx, uint64_t n, uint64_t be, int eb) {
     if (ctx->tile_set) return ctx->tile_elems;
     const uint64_t bucket = be < n ? be : n, most = (eb == 1) ? 256 : 768, alone = (eb == 1) ? 16384 : 8192;
